@@ -36,8 +36,8 @@
  * A call works on the calling thread's current device: `stream` (0 for the
  * null stream) must belong to it, else GT_ERROR_INVALID_VALUE.
  * `out` must not overlap Q, K or V.  Q, K, V and out must be 16-byte aligned.
- * Workspace (degree-bin lists, the light-row order of narrow-row shapes,
- * partial softmax states of split rows and the work-list counters) is owned
+ * Workspace (the lists of long and light rows, partial softmax states of split
+ * rows and the work-list counters; up to 256 MiB by default) is owned
  * by the library and private to each call while its kernels run: a call
  * takes a free workspace block of the device and, after enqueueing its
  * kernels, hands it back tagged with an event recorded on `stream`.  A later
@@ -46,7 +46,7 @@
  * device-side wait on the event; otherwise it allocates a new block from the
  * library's memory pool of the device (hipMallocFromPoolAsync on `stream`).
  * The host never waits for the device, nothing is kept per stream, and free
- * blocks above 256 MiB per device go back to the pool; gt_workspace_release()
+ * blocks above 1 GiB per device go back to the pool; gt_workspace_release()
  * returns all free blocks to the device.  On a stream being captured into a
  * graph the workspace is allocated and freed stream-ordered instead (both
  * become graph nodes).
@@ -118,29 +118,28 @@ gt_status gt_attn_fwd_bf16(const int64_t* rowptr, const int32_t* colidx, const u
  * Work-partition overrides (Appendix B.1 and D.1: degree-aware allocation of
  * rows to wavefronts, with light/heavy thresholds and per-chunk edge counts
  * that the paper tunes by grid search).  A field <= 0 selects the default.
+ *   The features are worked on slice by slice (the heads of 256 bytes, or one
+ *   head where that is more), each with the same partition:
  *   light_max_deg : rows of degree <= this are handled by one lane group
- *                   (a sub-wavefront) each (default 8 steps of the group)
- *   heavy_min_deg : rows of degree >= this are scheduled first; those longer
- *                   than one chunk are split into chunks processed by
- *                   different wavefronts and merged afterwards; rows in
- *                   between get one wavefront each (default 256; on graphs
- *                   whose default chunk exceeds 1024 and where a wavefront
- *                   holds two or more rows, a quarter of that chunk, except
- *                   for the GATv2 forward)
- *   chunk_edges   : CSR entries per chunk of a split row, rounded up to a
- *                   multiple of 64; a row is cut into at most 32 chunks, so
- *                   very long rows get longer chunks (default: from the
- *                   call's gather time at about 7 TB/s and one microsecond
- *                   per step: up to half of it in steps, at most 1024
- *                   entries, down to 64 on small graphs; where an eighth of
- *                   it exceeds 1024 entries, that eighth, up to 8192 (not for
- *                   the GATv2 forward).  With fp32 4x32 features the
- *                   graph-transformer forward gets 1024 on the arxiv-shaped
- *                   169K-node graph and 8192 on R-MAT scale 21; the GATv2
- *                   forward 768 and 1024)
- *   grid_blocks   : workgroups of the attention kernel, rounded up to a
- *                   multiple of 8 (default: about two light work items per
- *                   wavefront, within 4x..64x the resident workgroups)
+ *                   (a sub-wavefront) each (default 32 to 256, by what a
+ *                   piece of a longer row saves; 64 where the dense-tile path
+ *                   is on)
+ *   heavy_min_deg : rows of degree >= this (and of a degree octave all of which
+ *                   are) are split into pieces processed by different lane
+ *                   groups, each eighth of a row's pieces on one XCD, and
+ *                   merged afterwards; rows in between get one wavefront each
+ *                   (default: the power of two above light_max_deg's default)
+ *   chunk_edges   : CSR entries per piece of a split row at most, rounded up to
+ *                   a multiple of 64; a row is cut into at most 32 such pieces,
+ *                   so very long rows get longer ones, and rows of a degree
+ *                   octave that starts at no more than this stay whole
+ *                   (default: eight pieces, more from 512 entries on (1024
+ *                   where the gathers of a call take more than about 400 us),
+ *                   up to 256, of 32 to 64 (64 to 128) entries)
+ *   grid_blocks   : workgroups of the attention kernel per slice, rounded up to
+ *                   a multiple of 16 (default: a wavefront per two batches of
+ *                   light rows, and up to eight times the resident workgroups
+ *                   for the longer rows)
  *   dense_tiles   : threshold of the matrix-core path for locally dense
  *                   graphs (Section 3.3 and Appendix D.3: block-sparse
  *                   tiles); bf16 features with H*D <= 128 only, ignored
@@ -337,7 +336,8 @@ const char* gt_last_error_message(void);
  * Kernel timing for benchmarking.  While enabled, every attention call
  * records HIP events on its stream around its three phases: [0] partition
  * (counter reset + degree binning), [1] the attention kernels (the dense-tile
- * kernel, when enabled, and the CSR kernel), [2] the merge of split rows.  gt_profile_collect waits for the recorded events, adds their
+ * kernel, when enabled, and the CSR kernel; large calls launch it once per
+ * slice, with the merges in between), [2] the (last) merge of split rows.  gt_profile_collect waits for the recorded events, adds their
  * elapsed milliseconds into ms[0..2], sets *calls, and clears the record.
  * Enabling or disabling also clears it.  Process-wide, thread-safe.
  */

@@ -9,29 +9,25 @@
 //     out[i,h,:] = sum_e softmax_e(<a[h,:], LeakyReLU(L[i,h,:] + R[j_e,h,:])>) R[j_e,h,:]
 // where each CSR entry gathers one row (R serves as key and value).
 //
-// Mapping (designed for 64-wide wavefronts, not taken from the paper's
-// one-block-per-(node, head) CUDA layout):
-//   * A node row of all heads, H*D elements, is R = H*D*sizeof(T) contiguous
-//     bytes.  A lane group of G = min(64, R/16) lanes covers it with one
-//     16-byte load per lane (NV = R/(16*G) loads when R > 1 KiB), so every
-//     gathered K/V row is one fully coalesced request, and a wave holds
-//     P = 64/G independent groups.
+// Mapping (designed for 64-wide wavefronts and eight XCDs with an L2 each, not
+// taken from the paper's one-block-per-(node, head) CUDA layout):
+//   * A call runs over slices of the node row: the heads of 256 bytes, or one
+//     head of D elements where that is more.  A lane group of G lanes covers a
+//     slice with one 16-byte load per lane, so every gathered K/V slice is one
+//     coalesced request of whole cache lines, and a wave holds P = 64/G groups.
 //   * A head's D elements occupy HL = D*sizeof(T)/16 consecutive lanes; the
 //     score of a head is reduced across those lanes with DPP lane swaps.
 //   * Degree-aware work split (Appendix B.1; Appendix D.1 for the chunked
-//     heavy-node scheme): light rows get one group each, medium rows one wave
-//     (the P groups split the row's entries and are merged across lanes),
-//     heavy rows are cut into chunks processed by different waves whose
-//     partial (max, sum, acc) states are merged in chunk order by a second
-//     kernel, so results are bitwise reproducible and need no float atomics.
+//     heavy-node scheme): light rows get one group each; longer rows are cut
+//     into pieces of one group each, the q-th eighth of a row's entries on XCD q
+//     (see gt_rows.hpp), whose partial (max, sum, acc) states are merged in a
+//     fixed order by a second kernel, so results are bitwise reproducible and
+//     need no float atomics.
 //   * Each group processes U entries per step: all U K-row and V-row loads
 //     are issued before any is consumed, then one online-softmax update
 //     covers the U entries (one rescale per step instead of one per entry).
 //   * Neighbour indices are staged in LDS tiles loaded with one coalesced
 //     4-byte load per lane.
-//   * Light rows are assigned XCD-contiguously: the workgroups resident on
-//     one XCD process one contiguous range of rows, so rows with shared
-//     neighbourhoods (community-ordered ids) share that XCD's L2.
 
 #include <hip/hip_runtime.h>
 
@@ -130,28 +126,6 @@ struct HeavyRow {
     int32_t pad;
 };
 
-struct AttnParams {
-    const int64_t* rowptr;
-    const int32_t* colidx;
-    const char* Q;
-    const char* K;
-    const char* V;
-    char* out;
-    float* lse;  // [N][H] natural-log logsumexp of the scaled scores, or nullptr
-    int64_t N;
-    float c;  // scale * log2(e); log2(e) for GATv2
-    const float* att;  // GATv2 attention vector [H][D]
-    float slope;       // GATv2 LeakyReLU negative slope
-    int32_t light_max;
-    int32_t cap_items;
-    const int32_t* counters;
-    const int32_t* med_list;
-    const ChunkItem* chunks;
-    float* part_acc;   // [slot][H*D]
-    float2* part_ml;   // [slot][H]: (running max in log2 units, sum)
-    const int32_t* light_list;  // [N]: light rows in step order per partition block, -1 elsewhere
-};
-
 struct PartParams {
     const int64_t* rowptr;
     int64_t N;
@@ -177,16 +151,6 @@ struct PartParams {
     // the workspace's other counter set, zeroed by block 0 for the next call
     // that takes this workspace (nullptr: none)
     int32_t* zero_next = nullptr;
-};
-
-struct MergeParams {
-    int32_t cap_heavy;
-    const int32_t* counters;
-    const HeavyRow* heavy;
-    const float* part_acc;
-    const float2* part_ml;
-    char* out;
-    float* lse;
 };
 
 // ------------------------------------------------------------ element codecs
@@ -324,30 +288,69 @@ __device__ __forceinline__ float lse_of(float m, float l) {
     return l > 0.0f ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
+#include "gt_rows.hpp"
+
 // ------------------------------------------------------------ per-lane state
+
+// Entries per step of a lane group: 8, or 4 where short rows dominate the work
+// of a step: for the GATv2 score, whose steps are arithmetic-heavy, and for rows
+// narrow enough that a wave holds four or more of them.  A shorter step spends
+// less on the padding of short rows and holds fewer registers.
+template <typename T, int HS, int D, int KIND>
+struct StepOf {
+    static constexpr int kU = Geo<T, HS, D>::kU;
+    static constexpr int value = ((KIND == KIND_GATV2 || Geo<T, HS, D>::kP >= 4) && kU >= 8) ? kU / 2 : kU;
+};
+
+// What the lanes of a wavefront share while it works on one slice of HS heads:
+// base pointers at the slice's first element (of node 0), the stride between
+// nodes and the score's constants.  KIND_GATV2: each lane also keeps its part of
+// the attention vector, in two forms, since
+// a * LeakyReLU(x) = a(1+s)/2 * x + a(1-s)/2 * |x| (exact for any slope s): an
+// element then costs one add and two FMAs (|x| is a free operand modifier)
+// instead of a compare, a select and a multiply more.
+template <typename T, int HS, int D, int KIND>
+struct RowState;
+
+template <typename T, int HS, int D, int KIND>
+struct AttnOp {
+    using Gm = Geo<T, HS, D>;
+    using State = RowState<T, HS, D, KIND>;
+    static constexpr bool kGat = KIND == KIND_GATV2;
+    static constexpr int kG = Gm::kG;
+    static constexpr int kU = StepOf<T, HS, D, KIND>::value;
+    // Light rows in the partition's step order pay where a wave holds four or
+    // more rows (its groups then wait on their longest row), and for the GATv2
+    // score, whose steps are arithmetic-heavy, already at two.
+    static constexpr bool kSorted = Gm::kP >= 4 || (kGat && Gm::kP >= 2);
+    static constexpr int kSlotFloats = HS * D;
+    const char* Q;
+    const char* K;
+    const char* V;
+    char* out;
+    float* lse;      // at the slice's first head, or nullptr
+    float* part_acc;  // [slot][HS * D]
+    float2* part_ml;  // [slot][HS]: (running max in log2 units, sum)
+    int row_shift;    // log2 of the bytes of one node row (all heads)
+    int heads;
+    float c;  // scale * log2(e); log2(e) for GATv2
+    float a[kGat ? Gm::kEPV : 1];   // a(1+s)/2
+    float a2[kGat ? Gm::kEPV : 1];  // a(1-s)/2
+
+    __device__ __forceinline__ uint64_t offset(int32_t row, int lig) const {
+        return ((uint64_t)(uint32_t)row << row_shift) + (uint32_t)lig * 16u;
+    }
+};
 
 // One lane's share of a row's running state.  KIND_GT: q holds Q[i] and each
 // entry loads K[j] (score) and V[j] (value).  KIND_GATV2: q holds L[i] and each
-// entry loads only R[j], which gives both the score and the value.  The
-// LeakyReLU term uses a * LeakyReLU(x) = a(1+s)/2 * x + a(1-s)/2 * |x| (exact
-// for any slope s): a holds the lane's slice of a(1+s)/2 and a2 of a(1-s)/2,
-// so an element costs one add and two FMAs (|x| is a free operand modifier)
-// instead of a compare, a select and a multiply more.
-// Entries per step of a row: the geometry's step, halved (8 -> 4) where short
-// rows dominate the work of a step: for the GATv2 score, whose steps are
-// arithmetic-heavy, and for rows narrow enough that a wave holds four or more
-// of them.  A shorter step spends less on the padding of short rows and holds
-// fewer registers.
-template <typename T, int H, int D, int KIND>
-struct StepOf {
-    static constexpr int kU = Geo<T, H, D>::kU;
-    static constexpr int value = ((KIND == KIND_GATV2 || Geo<T, H, D>::kP >= 4) && kU >= 8) ? kU / 2 : kU;
-};
-
-template <typename T, int H, int D, int KIND = KIND_GT>
+// entry loads only R[j], which gives both the score and the value.
+template <typename T, int HS, int D, int KIND = KIND_GT>
 struct RowState {
-    using Gm = Geo<T, H, D>;
-    static constexpr int kU = StepOf<T, H, D, KIND>::value;
+    using Op = AttnOp<T, HS, D, KIND>;
+    using Gm = Geo<T, HS, D>;
+    static_assert(Gm::kNV == 1, "a slice is one 16-byte vector per lane");
+    static constexpr int kU = StepOf<T, HS, D, KIND>::value;
     static constexpr bool kGat = KIND == KIND_GATV2;
     // bf16 graph-transformer rows: scores are bf16 dot2 on the raw Q and K
     // pairs, accumulated in fp32 (the products of bf16 pairs are exact).  P*V
@@ -363,117 +366,81 @@ struct RowState {
     static constexpr bool kDot2 = std::is_same<T, bf16_tag>::value && !kGat;
     static constexpr bool kPairPV = kDot2 && KIND == KIND_GT_BF16W;
     static_assert(!kPairPV || kU % 2 == 0, "dot2 pairs entries");
-    float q[Gm::kNV][Gm::kEPV];
-    float a[kGat ? Gm::kNV : 1][kGat ? Gm::kEPV : 1];
-    float a2[kGat ? Gm::kNV : 1][kGat ? Gm::kEPV : 1];
-    float acc[Gm::kNV][Gm::kEPV];
-    float m[Gm::kNV];  // running max of log2-scaled scores for this lane's head
-    float l[Gm::kNV];  // running sum of 2^(s - m)
-    uint4 qraw[kDot2 ? Gm::kNV : 1];  // the row vector as bf16 pairs (dot2 form)
+    float q[Gm::kEPV];
+    float acc[Gm::kEPV];
+    float m;     // running max of log2-scaled scores for this lane's head
+    float l;     // running sum of 2^(s - m)
+    uint4 qraw;  // the row vector as bf16 pairs (dot2 form)
 
-    __device__ __forceinline__ void begin(const char* __restrict__ Qb, int64_t row, int lig,
-                                          const float* __restrict__ att = nullptr, float slope = 0.0f) {
-        const char* qrow = Qb + row * (int64_t)Gm::kRowBytes + lig * 16;
+    __device__ __forceinline__ void reset() {
+        m = -INFINITY;
+        l = 0.0f;
 #pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            const uint4 r = load_once(qrow + k * Gm::kG * 16);
-            if constexpr (kDot2)
-                qraw[k] = r;
-            else
-                widen<T>(r, q[k]);
-            if constexpr (kGat) {
-                // the attention vector is [H][D] fp32 in the row's element order
-                const float* av = att + (lig + k * Gm::kG) * Gm::kEPV;
-                const float hs = 0.5f * slope;
-#pragma unroll
-                for (int e = 0; e < Gm::kEPV; e += 4) {
-                    const float4 x4 = *reinterpret_cast<const float4*>(av + e);
-                    const float x[4] = {x4.x, x4.y, x4.z, x4.w};
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        a[k][e + t] = fmaf(hs, x[t], 0.5f * x[t]);
-                        a2[k][e + t] = fmaf(-hs, x[t], 0.5f * x[t]);
-                    }
-                }
-            }
-            m[k] = -INFINITY;
-            l[k] = 0.0f;
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) acc[k][e] = 0.0f;
-        }
+        for (int e = 0; e < Gm::kEPV; ++e) acc[e] = 0.0f;
     }
 
-    // begin() with this lane's 16-byte pieces of the row vector already in
-    // registers (graph-transformer score only).
-    __device__ __forceinline__ void begin_loaded(const uint4 (&r)[Gm::kNV]) {
-        static_assert(!kGat, "the GATv2 state also needs its attention vector");
-#pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            if constexpr (kDot2)
-                qraw[k] = r[k];
-            else
-                widen<T>(r[k], q[k]);
-            m[k] = -INFINITY;
-            l[k] = 0.0f;
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) acc[k][e] = 0.0f;
-        }
+    __device__ __forceinline__ void begin(const Op& op, int32_t row, int lig) {
+        begin_loaded(load_once(op.Q + op.offset(row, lig)));
+    }
+
+    // begin() with this lane's 16 bytes of the row vector already in registers.
+    __device__ __forceinline__ void begin_loaded(const uint4& r) {
+        if constexpr (kDot2)
+            qraw = r;
+        else
+            widen<T>(r, q);
     }
 
     // Loads of one step: the K and V rows (GATv2: the R rows) of U entries,
     // 16 bytes per lane each.
     struct Batch {
-        uint4 k[kU][Gm::kNV];
-        uint4 v[kGat ? 1 : kU][Gm::kNV];
+        uint4 k[kU];
+        uint4 v[kGat ? 1 : kU];
     };
 
-    __device__ __forceinline__ void issue(const char* __restrict__ Kb, const char* __restrict__ Vb,
-                                          const int32_t (&j)[kU], int lig, Batch& bt) const {
+    __device__ __forceinline__ void issue(const Op& op, const int32_t (&j)[kU], int lig, Batch& bt) const {
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int64_t off = (int64_t)j[u] * Gm::kRowBytes + lig * 16;
-#pragma unroll
-            for (int k = 0; k < Gm::kNV; ++k) {
-                bt.k[u][k] = *reinterpret_cast<const uint4*>(Kb + off + k * Gm::kG * 16);
-                if constexpr (!kGat) bt.v[u][k] = *reinterpret_cast<const uint4*>(Vb + off + k * Gm::kG * 16);
-            }
+            const uint64_t off = op.offset(j[u], lig);
+            bt.k[u] = *reinterpret_cast<const uint4*>(op.K + off);
+            if constexpr (!kGat) bt.v[u] = *reinterpret_cast<const uint4*>(op.V + off);
         }
     }
 
-    // Value row of entry u in vector slot k (GATv2: the gathered R row).
-    __device__ __forceinline__ static const uint4& value(const Batch& bt, int u, int k) {
+    // Value row of entry u (GATv2: the gathered R row).
+    __device__ __forceinline__ static const uint4& value(const Batch& bt, int u) {
         if constexpr (kGat)
-            return bt.k[u][k];
+            return bt.k[u];
         else
-            return bt.v[u][k];
+            return bt.v[u];
     }
 
-    // Score of entry u in vector slot k (log2 units, before masking).
-    __device__ __forceinline__ float score(const Batch& bt, int u, int k, float c) const {
+    // Score of entry u (log2 units, before masking).
+    __device__ __forceinline__ float score(const Op& op, const Batch& bt, int u) const {
 #pragma clang fp contract(off)
         float d = 0.0f;
         if constexpr (kDot2) {
-            const uint4 kr = bt.k[u][k], qr = qraw[k];
-            d = dot2_bf16(qr.x, kr.x, d);
-            d = dot2_bf16(qr.y, kr.y, d);
-            d = dot2_bf16(qr.z, kr.z, d);
-            d = dot2_bf16(qr.w, kr.w, d);
+            const uint4 kr = bt.k[u];
+            d = dot2_bf16(qraw.x, kr.x, d);
+            d = dot2_bf16(qraw.y, kr.y, d);
+            d = dot2_bf16(qraw.z, kr.z, d);
+            d = dot2_bf16(qraw.w, kr.w, d);
         } else {
             float kf[Gm::kEPV];
-            widen<T>(bt.k[u][k], kf);
+            widen<T>(bt.k[u], kf);
             if constexpr (kGat) {
 #pragma unroll
                 for (int e = 0; e < Gm::kEPV; ++e) {
-                    const float x = q[k][e] + kf[e];
-                    d = fmaf(a[k][e], x, d);
-                    d = fmaf(a2[k][e], fabsf(x), d);
+                    const float x = q[e] + kf[e];
+                    d = fmaf(op.a[e], x, d);
+                    d = fmaf(op.a2[e], fabsf(x), d);
                 }
             } else {
 #pragma unroll
-                for (int e = 0; e < Gm::kEPV; ++e) d = fmaf(q[k][e], kf[e], d);
+                for (int e = 0; e < Gm::kEPV; ++e) d = fmaf(q[e], kf[e], d);
             }
         }
-        return head_sum<Gm::kHL>(d) * c;
+        return head_sum<Gm::kHL>(d) * op.c;
     }
 
     // Online-softmax update with the U entries of a batch; entries u >= nvalid
@@ -482,294 +449,222 @@ struct RowState {
     // weight 0 adds exactly 0, so a single-entry row returns its value exactly;
     // dot2 steps with an odd number of valid entries pair the last one with a
     // weight-0 copy.
-    __device__ __forceinline__ void consume(const Batch& bt, int nvalid, float c) {
+    __device__ __forceinline__ void consume(const Op& op, const Batch& bt, const int32_t (&)[kU], int nvalid) {
         // No implicit contraction: fusing the score product into the later
         // subtraction of the running max would give the maximal entry a weight
         // of 2^(rounding error) instead of exactly 1.
 #pragma clang fp contract(off)
         constexpr int U = kU;
-        float s[U][Gm::kNV];
+        float s[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            const float d = score(op, bt, u);  // unconditional: the head sum is cross-lane
+            s[u] = (u < nvalid) ? d : -INFINITY;
+        }
+        float mb = m;
 #pragma unroll
-            for (int k = 0; k < Gm::kNV; ++k) {
-                const float d = score(bt, u, k, c);  // unconditional: the head sum is cross-lane
-                s[u][k] = (u < nvalid) ? d : -INFINITY;
-            }
+        for (int u = 0; u < U; ++u) mb = fmaxf(mb, s[u]);
+        const float corr = fast_exp2(m - mb);  // 0 on the first step (m = -inf)
+        l *= corr;
 #pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            float mb = m[k];
+        for (int e = 0; e < Gm::kEPV; ++e) acc[e] *= corr;
+        if constexpr (kPairPV) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) mb = fmaxf(mb, s[u][k]);
-            const float corr = fast_exp2(m[k] - mb);  // 0 on the first step (m = -inf)
-            l[k] *= corr;
+            for (int u = 0; u < U; u += 2) {
+                const float p0 = fast_exp2(s[u] - mb), p1 = fast_exp2(s[u + 1] - mb);
+                l += p0;  // the normaliser (and so lse) from the fp32 weights
+                l += p1;
+                const uint32_t pp = pack_bf16(p0, p1);
+                const uint4 v0 = value(bt, u), v1 = value(bt, u + 1);
+                const uint32_t a0[4] = {v0.x, v0.y, v0.z, v0.w}, a1[4] = {v1.x, v1.y, v1.z, v1.w};
 #pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) acc[k][e] *= corr;
-            if constexpr (kPairPV) {
-#pragma unroll
-                for (int u = 0; u < U; u += 2) {
-                    const float p0 = fast_exp2(s[u][k] - mb), p1 = fast_exp2(s[u + 1][k] - mb);
-                    l[k] += p0;  // the normaliser (and so lse) from the fp32 weights
-                    l[k] += p1;
-                    const uint32_t pp = pack_bf16(p0, p1);
-                    const uint4 v0 = value(bt, u, k), v1 = value(bt, u + 1, k);
-                    const uint32_t a0[4] = {v0.x, v0.y, v0.z, v0.w}, a1[4] = {v1.x, v1.y, v1.z, v1.w};
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        acc[k][2 * x] = dot2_bf16(pp, pair_lo(a0[x], a1[x]), acc[k][2 * x]);
-                        acc[k][2 * x + 1] = dot2_bf16(pp, pair_hi(a0[x], a1[x]), acc[k][2 * x + 1]);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const float pu = fast_exp2(s[u][k] - mb);
-                    l[k] += pu;
-                    float vf[Gm::kEPV];
-                    widen<T>(value(bt, u, k), vf);
-#pragma unroll
-                    for (int e = 0; e < Gm::kEPV; ++e) acc[k][e] = fmaf(pu, vf[e], acc[k][e]);
+                for (int x = 0; x < 4; ++x) {
+                    acc[2 * x] = dot2_bf16(pp, pair_lo(a0[x], a1[x]), acc[2 * x]);
+                    acc[2 * x + 1] = dot2_bf16(pp, pair_hi(a0[x], a1[x]), acc[2 * x + 1]);
                 }
             }
-            m[k] = mb;
-        }
-    }
-
-    __device__ __forceinline__ void step(const char* __restrict__ Kb, const char* __restrict__ Vb,
-                                         const int32_t (&j)[kU], int nvalid, int lig, float c) {
-        Batch bt;
-        issue(Kb, Vb, j, lig, bt);
-        consume(bt, nvalid, c);
-    }
-
-    // Merge the state held by the lane `off` positions away (same vector
-    // slots in another group of the wave).
-    __device__ __forceinline__ void merge_xor(int off) {
-#pragma clang fp contract(off)
-#pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            const float mo = __shfl_xor(m[k], off);
-            const float lo = __shfl_xor(l[k], off);
-            const float mn = fmaxf(m[k], mo);
-            const float ca = (m[k] == mn) ? 1.0f : fast_exp2(m[k] - mn);
-            const float cb = (mo == mn) ? 1.0f : fast_exp2(mo - mn);
-            l[k] = l[k] * ca + lo * cb;
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) {
-                const float ao = __shfl_xor(acc[k][e], off);
-                acc[k][e] = acc[k][e] * ca + ao * cb;
-            }
-            m[k] = mn;
-        }
-    }
-
-    __device__ __forceinline__ void store_out(char* __restrict__ outb, float* __restrict__ lse, int64_t row,
-                                              int lig) const {
-        char* orow = outb + row * (int64_t)Gm::kRowBytes + lig * 16;
-#pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            const float inv = l[k] > 0.0f ? 1.0f / l[k] : 0.0f;
-            float o[Gm::kEPV];
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) o[e] = acc[k][e] * inv;
-            store_once(orow + k * Gm::kG * 16, narrow<T>(o));
-            const int v = lig + k * Gm::kG;
-            if (lse && v % Gm::kHL == 0) lse[row * H + v / Gm::kHL] = lse_of(m[k], l[k]);
-        }
-    }
-
-    __device__ __forceinline__ void store_partial(float* __restrict__ pacc, float2* __restrict__ pml,
-                                                  int32_t slot, int lig) const {
-#pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            const int v = lig + k * Gm::kG;  // vector index within the row
-            float* dst = pacc + (int64_t)slot * Gm::kHD + v * Gm::kEPV;
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; e += 4)
-                *reinterpret_cast<float4*>(dst + e) =
-                    make_float4(acc[k][e], acc[k][e + 1], acc[k][e + 2], acc[k][e + 3]);
-            if (v % Gm::kHL == 0) pml[(int64_t)slot * H + v / Gm::kHL] = make_float2(m[k], l[k]);
-        }
-    }
-};
-
-// One wavefront streams CSR entries [b, e) of `row`; slot < 0 writes the
-// normalised output, slot >= 0 writes the partial state of a chunk.
-template <typename T, int H, int D, int KIND>
-__device__ __forceinline__ void wave_segment(const AttnParams& p, int64_t row, int64_t b, int64_t e,
-                                             int32_t slot, int32_t* __restrict__ tile, int lane) {
-    using Gm = Geo<T, H, D>;
-    constexpr int U = RowState<T, H, D, KIND>::kU, P = Gm::kP, G = Gm::kG;
-    const int g = lane / G, lig = lane % G;
-    RowState<T, H, D, KIND> st;
-    st.begin(p.Q, row, lig, p.att, p.slope);
-    for (int64_t tb = b; tb < e; tb += kWave) {
-        const int64_t pos = (tb + lane < e) ? tb + lane : e - 1;
-        const int32_t idx = p.colidx[pos];
-        wave_lds_fence();
-        tile[lane] = idx;
-        wave_lds_fence();
-        const int nt = (int)((e - tb) < kWave ? (e - tb) : kWave);
-        for (int t = 0; t < nt; t += P * U) {
-            const int e0 = t + g * U;
-            const int nvalid = nt - e0 < U ? nt - e0 : U;
-            if (nvalid > 0) {
-                int32_t j[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) j[u] = tile[e0 + u];
-                st.step(p.K, p.V, j, nvalid, lig, p.c);
-            }
-        }
-    }
-#pragma unroll
-    for (int off = G; off < kWave; off <<= 1) st.merge_xor(off);
-    if (g == 0) {
-        if (slot < 0)
-            st.store_out(p.out, p.lse, row, lig);
-        else
-            st.store_partial(p.part_acc, p.part_ml, slot, lig);
-    }
-}
-
-// Light rows (degree <= light_max), one lane group per row.  Each group walks
-// its sequence of rows software-pipelined: the next row's rowptr entries are
-// loaded before the current row's work starts, and its first index tile is
-// loaded while the current row's first K/V batch is in flight, so a short row
-// costs about one memory latency instead of three (rowptr -> colidx -> K/V).
-// An index tile holds LightTile<G>::kR * G entries (kR loads per lane).
-// Light rows in the partition's step order pay where a wave holds four or more
-// rows (its groups then wait on their longest row), and for the GATv2 score,
-// whose steps are arithmetic-heavy, already at two.  For the graph-transformer
-// score with one or two rows per wave the extra index load and the longer
-// partition cost more than the balance gains.
-template <typename T, int H, int D, int KIND = KIND_GT>
-struct SortedLight {
-    static constexpr bool value = Geo<T, H, D>::kP >= 4 || (KIND == KIND_GATV2 && Geo<T, H, D>::kP >= 2);
-};
-
-template <int G> struct LightTile {
-    static constexpr int kR = G >= 64 ? 1 : 2;
-    static constexpr int kEntries = kR * G;
-};
-
-template <typename T, int H, int D, int KIND>
-__device__ __forceinline__ void light_rows(const AttnParams& p, int64_t it, int64_t it_end,
-                                           int64_t stride, int g, int lig,
-                                           int32_t* __restrict__ gtile) {
-    using Gm = Geo<T, H, D>;
-    constexpr int U = RowState<T, H, D, KIND>::kU, G = Gm::kG, P = Gm::kP;
-    constexpr int R = LightTile<G>::kR, TE = LightTile<G>::kEntries;
-    static_assert(TE % U == 0, "index tiles hold whole steps");
-    // entries [tb, tb + TE) of a row ending at ce (clamped to its last entry)
-    auto load_tile = [&](int64_t tb, int64_t ce, int32_t (&v)[R]) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t pos = tb + r * G + lig;
-            v[r] = p.colidx[pos < ce ? pos : ce - 1];
-        }
-    };
-    // Item `it` is the group's row at position it * P + g of the light-row
-    // order (-1: none); the entry two items ahead is requested one item early,
-    // so that it is in a register when its row pointers are needed.
-    auto row_at = [&](int64_t i) -> int64_t {
-        const int64_t pos = i * P + g;
-        if constexpr (SortedLight<T, H, D, KIND>::value)
-            return (i < it_end && pos < p.N) ? (int64_t)p.light_list[pos] : -1;
-        else
-            return (i < it_end && pos < p.N) ? pos : -1;
-    };
-    int64_t row = row_at(it);
-    int64_t row_next = row_at(it + stride);
-    bool ok = row >= 0;
-    int64_t b = ok ? p.rowptr[row] : 0, e = ok ? p.rowptr[row + 1] : 0;
-    bool mine = ok && (e - b) <= p.light_max;
-    int32_t idx[R] = {};
-    if (mine && e > b) load_tile(b, e, idx);
-    while (it < it_end) {
-        const int64_t crow = row, cb = b, ce = e;
-        const bool cmine = mine;
-        int32_t tv[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) tv[r] = idx[r];
-        it += stride;
-        row = row_next;
-        row_next = row_at(it + stride);
-        ok = row >= 0;
-        b = ok ? p.rowptr[row] : 0;
-        e = ok ? p.rowptr[row + 1] : 0;
-        mine = ok && (e - b) <= p.light_max;
-        bool fetched = false;
-        if (cmine) {
-            RowState<T, H, D, KIND> st;
-            st.begin(p.Q, crow, lig, p.att, p.slope);
-            for (int64_t tb = cb; tb < ce; tb += TE) {
-                if (tb != cb) load_tile(tb, ce, tv);
-                wave_lds_fence();
-#pragma unroll
-                for (int r = 0; r < R; ++r) gtile[r * G + lig] = tv[r];
-                wave_lds_fence();
-                const int nt = (int)((ce - tb) < TE ? (ce - tb) : TE);
-                for (int t = 0; t < nt; t += U) {
-                    const int nvalid = nt - t < U ? nt - t : U;
-                    int32_t j[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) j[u] = gtile[t + u];
-                    typename RowState<T, H, D, KIND>::Batch bt;
-                    st.issue(p.K, p.V, j, lig, bt);
-                    if (!fetched) {  // next row's first tile, overlapped with this batch
-                        if (mine && e > b) load_tile(b, e, idx);
-                        fetched = true;
-                    }
-                    st.consume(bt, nvalid, p.c);
-                }
-            }
-            st.store_out(p.out, p.lse, crow, lig);
-        }
-        if (!fetched && mine && e > b) load_tile(b, e, idx);
-    }
-}
-
-// Attention kernel: first the chunk items (pieces of heavy rows,
-// then whole medium rows), one wavefront each; then the light rows, P per
-// wavefront, in XCD-contiguous ranges.
-template <typename T, int H, int D, int KIND>
-__global__ void __launch_bounds__(kBlock) gt_attn_kernel(AttnParams p) {
-    using Gm = Geo<T, H, D>;
-    // per wave: one 64-entry tile (wave items) or P light-row tiles
-    constexpr int kTileWords = Gm::kP * LightTile<Gm::kG>::kEntries > kWave ? Gm::kP * LightTile<Gm::kG>::kEntries : kWave;
-    __shared__ int32_t tiles[kWavesPerBlock][kTileWords];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x / kWave;
-    int32_t* tile = tiles[wv];
-
-    // Counts come from the partition kernel; clamping keeps every list read
-    // inside the workspace even if the CSR precondition were violated.  The
-    // light-row flag is read with them, so that a workgroup with nothing to
-    // do ends after one round trip.
-    const int32_t n_chunks = min(CNT(p.counters, CNT_CHUNKS), p.cap_items);
-    const int32_t n_items = n_chunks + (int32_t)min((int64_t)CNT(p.counters, CNT_MED), p.N);
-    const bool any_light = !SortedLight<T, H, D, KIND>::value || CNT(p.counters, CNT_LIGHT) != 0;
-    const int nwaves = gridDim.x * kWavesPerBlock;
-    for (int it = blockIdx.x * kWavesPerBlock + wv; it < n_items; it += nwaves) {
-        if (it < n_chunks) {
-            const ChunkItem ci = p.chunks[it];
-            wave_segment<T, H, D, KIND>(p, ci.row, ci.begin, ci.end, ci.slot, tile, lane);
         } else {
-            const int64_t row = p.med_list[it - n_chunks];
-            wave_segment<T, H, D, KIND>(p, row, p.rowptr[row], p.rowptr[row + 1], -1, tile, lane);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float pu = fast_exp2(s[u] - mb);
+                l += pu;
+                float vf[Gm::kEPV];
+                widen<T>(value(bt, u), vf);
+#pragma unroll
+                for (int e = 0; e < Gm::kEPV; ++e) acc[e] = fmaf(pu, vf[e], acc[e]);
+            }
         }
+        m = mb;
     }
 
-    const int xcd = blockIdx.x % kXcds;
-    const int waves_per_xcd = (gridDim.x / kXcds) * kWavesPerBlock;
-    const int lw = (blockIdx.x / kXcds) * kWavesPerBlock + wv;
-    const int64_t n_light = (p.N + Gm::kP - 1) / Gm::kP;
-    const int64_t lo = n_light * xcd / kXcds, hi = n_light * (xcd + 1) / kXcds;
-    const int g = lane / Gm::kG, lig = lane % Gm::kG;
-    // (with a light-row order, it can be empty: every light row lies in a
-    // dense window of the tile kernel)
-    if (!any_light) return;
-    light_rows<T, H, D, KIND>(p, lo + lw, hi, waves_per_xcd, g, lig, tile + g * LightTile<Gm::kG>::kEntries);
+    __device__ __forceinline__ void step(const Op& op, const int32_t (&j)[kU], int nvalid, int lig) {
+        Batch bt;
+        issue(op, j, lig, bt);
+        consume(op, bt, j, nvalid);
+    }
+
+    // Merge a state (mo, lo, ao) of other entries of the same row.
+    __device__ __forceinline__ void merge(float mo, float lo, const float (&ao)[Gm::kEPV]) {
+#pragma clang fp contract(off)
+        const float mn = fmaxf(m, mo);
+        const float ca = (m == mn) ? 1.0f : fast_exp2(m - mn);
+        const float cb = (mo == mn) ? 1.0f : fast_exp2(mo - mn);
+        l = l * ca + lo * cb;
+#pragma unroll
+        for (int e = 0; e < Gm::kEPV; ++e) acc[e] = acc[e] * ca + ao[e] * cb;
+        m = mn;
+    }
+
+    // Merge the state held by the lane `off` positions away (the same vector in
+    // another group of the wave).
+    __device__ __forceinline__ void merge_xor(int off) {
+        const float mo = __shfl_xor(m, off);
+        const float lo = __shfl_xor(l, off);
+        float ao[Gm::kEPV];
+#pragma unroll
+        for (int e = 0; e < Gm::kEPV; ++e) ao[e] = __shfl_xor(acc[e], off);
+        merge(mo, lo, ao);
+    }
+
+    __device__ __forceinline__ void store_out(const Op& op, int32_t row, int lig) const {
+        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+        float o[Gm::kEPV];
+#pragma unroll
+        for (int e = 0; e < Gm::kEPV; ++e) o[e] = acc[e] * inv;
+        store_once(op.out + op.offset(row, lig), narrow<T>(o));
+        if (op.lse && lig % Gm::kHL == 0) op.lse[(int64_t)row * op.heads + lig / Gm::kHL] = lse_of(m, l);
+    }
+
+    __device__ __forceinline__ void store_partial(const Op& op, int32_t slot, int lig) const {
+        float* dst = op.part_acc + (int64_t)slot * Gm::kHD + lig * Gm::kEPV;
+#pragma unroll
+        for (int e = 0; e < Gm::kEPV; e += 4)
+            *reinterpret_cast<float4*>(dst + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+        if (lig % Gm::kHL == 0) op.part_ml[(int64_t)slot * HS + lig / Gm::kHL] = make_float2(m, l);
+    }
+
+    __device__ __forceinline__ void load_partial(const Op& op, int32_t slot, int lig, float& mo, float& lo,
+                                                 float (&ao)[Gm::kEPV]) const {
+        const float* src = op.part_acc + (int64_t)slot * Gm::kHD + lig * Gm::kEPV;
+#pragma unroll
+        for (int e = 0; e < Gm::kEPV; e += 4) {
+            const float4 x = *reinterpret_cast<const float4*>(src + e);
+            ao[e] = x.x;
+            ao[e + 1] = x.y;
+            ao[e + 2] = x.z;
+            ao[e + 3] = x.w;
+        }
+        const float2 ml = op.part_ml[(int64_t)slot * HS + lig / Gm::kHL];
+        mo = ml.x;
+        lo = ml.y;
+    }
+};
+
+struct AttnParams {
+    RowWork w;
+    const char* Q;
+    const char* K;
+    const char* V;
+    char* out;
+    float* lse;  // [N][H] natural-log logsumexp of the scaled scores, or nullptr
+    const float* att;  // GATv2 attention vector [H][D]
+    float slope;       // GATv2 LeakyReLU negative slope
+    float c;           // scale * log2(e); log2(e) for GATv2
+    int32_t row_shift;
+    int32_t heads;
+    int32_t slice0;    // slice of blockIdx.y == 0
+    float* part_acc;   // [slice of this launch][slot][HS * D]
+    float2* part_ml;   // [slice of this launch][slot][HS]
+};
+
+template <typename T, int HS, int D, int KIND>
+__device__ __forceinline__ AttnOp<T, HS, D, KIND> slice_op(const AttnParams& p) {
+    using Op = AttnOp<T, HS, D, KIND>;
+    Op op;
+    const int head = (p.slice0 + (int)blockIdx.y) * HS;
+    const int64_t at = (int64_t)head * D * Elt<T>::kBytes;
+    const int64_t slot = (int64_t)blockIdx.y * p.w.cap_slots;
+    op.Q = p.Q + at;
+    op.K = p.K + at;
+    op.V = p.V + at;
+    op.out = p.out + at;
+    op.lse = p.lse ? p.lse + head : nullptr;
+    op.part_acc = p.part_acc + slot * Op::kSlotFloats;
+    op.part_ml = p.part_ml + slot * HS;
+    op.row_shift = p.row_shift;
+    op.heads = p.heads;
+    op.c = p.c;
+    if constexpr (Op::kGat) {
+        // the attention vector is [H][D] fp32 in the row's element order
+        const float* av = p.att + head * D + (threadIdx.x % Op::kG) * Op::Gm::kEPV;
+        const float hs = 0.5f * p.slope;
+#pragma unroll
+        for (int e = 0; e < Op::Gm::kEPV; e += 4) {
+            const float4 x4 = *reinterpret_cast<const float4*>(av + e);
+            const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                op.a[e + t] = fmaf(hs, x[t], 0.5f * x[t]);
+                op.a2[e + t] = fmaf(-hs, x[t], 0.5f * x[t]);
+            }
+        }
+    }
+    return op;
+}
+
+// Attention kernel: blockIdx.y is the slice (launched one after another), the
+// blocks of a slice share its rows as row_loop says.
+template <typename T, int HS, int D, int KIND>
+__global__ void __launch_bounds__(kBlock) gt_attn_kernel(AttnParams p) {
+    using Op = AttnOp<T, HS, D, KIND>;
+    __shared__ __attribute__((aligned(16))) int32_t tiles[kWavesPerBlock][kWave / Op::kG * TileOf<Op::kG>::kEntries];
+    const Op op = slice_op<T, HS, D, KIND>(p);
+    row_loop(p.w, op, tiles[threadIdx.x / kWave]);
+}
+
+// Merge of the partial states of each cut row: one wavefront per row and slice.
+// Lane group g merges pieces g, g + P, ..., kMergePieces of them in flight at a
+// time, and the groups are merged across lanes: a fixed order, so the results
+// are bitwise reproducible.
+constexpr int kMergePieces = 4;
+
+template <typename T, int HS, int D>
+__global__ void __launch_bounds__(kBlock) gt_merge_kernel(AttnParams p) {
+    using Op = AttnOp<T, HS, D, KIND_GT>;
+    constexpr int G = Op::kG, P = kWave / G, EPV = Op::Gm::kEPV;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t g = lane / G;
+    const int lig = lane % G;
+    if (ROWS_CNT(p.w.counters, ROWS_PIECES) == 0) return;  // no long rows
+    const CutRows cut(p.w, lane);
+    const uint32_t n = cut.count(), waves = gridDim.x * kWavesPerBlock;
+    const Op op = slice_op<T, HS, D, KIND_GT>(p);
+    for (uint32_t i = blockIdx.x * kWavesPerBlock + wv; i < n; i += waves) {
+        uint32_t slot, nq;
+        const int32_t row = cut.row(p.w, i, lane, slot, nq);
+        typename Op::State st;
+        st.reset();
+        for (uint32_t q0 = 0; q0 < nq; q0 += P * kMergePieces) {
+            float mo[kMergePieces], lo[kMergePieces], ao[kMergePieces][EPV];
+            // (a group without a piece reads the row's last and leaves it out)
+#pragma unroll
+            for (int u = 0; u < kMergePieces; ++u) {
+                const uint32_t q = q0 + u * P + g;
+                st.load_partial(op, (int32_t)(slot + (q < nq ? q : nq - 1)), lig, mo[u], lo[u], ao[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kMergePieces; ++u) {
+                if (q0 + u * P + g >= nq) mo[u] = -INFINITY, lo[u] = 0.0f;
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) ao[u][e] = q0 + u * P + g < nq ? ao[u][e] : 0.0f;
+                st.merge(mo[u], lo[u], ao[u]);
+            }
+        }
+#pragma unroll
+        for (int off = G; off < kWave; off <<= 1) st.merge_xor(off);
+        if (g == 0) st.store_out(op, row, lig);
+    }
 }
 
 // ------------------------------------------------------- dense-tile path
@@ -828,7 +723,7 @@ struct TileParams {
     int32_t light_max;  // <= kWinMaxDeg
     int32_t min_entries;
     const uint8_t* win_flags;  // [ceil(N / 64)]: 1 for the dense windows the partition found
-    const int32_t* counters;   // CNT_WIN: any window dense (byte 0) / not dense (byte 1)
+    const int32_t* counters;   // ROWS_WIN: any window dense (byte 0) / not dense (byte 1)
 };
 
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
@@ -881,7 +776,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(Til
 gt_tile_kernel(TileParams p) {
     using Gm = Geo<bf16_tag, H, D>;
     using L = TileLds<H, D>;
-    using RS = RowState<bf16_tag, H, D, KIND>;
+    using RS = RowState<bf16_tag, H, D, KIND>;  // (all heads: these rows are at most 256 bytes)
     constexpr int HD = H * D;
     constexpr int G = Gm::kG, P = Gm::kP, U = RS::kU;
     // fp32 weights (KIND_GT): P = hi + lo as two bf16 terms, two P*V
@@ -902,7 +797,7 @@ gt_tile_kernel(TileParams p) {
     // spilled; a list also needs its entry before any other load.)
     const int64_t r0 = (int64_t)blockIdx.x * kWin;
     const int64_t wend = r0 + kWin;
-    const int32_t win_state = CNT(p.counters, CNT_WIN);
+    const int32_t win_state = ROWS_CNT(p.counters, ROWS_WIN);
     if ((win_state & 0xFF) == 0) return;
     const bool all_dense = (win_state & 0xFF00) == 0;
 
@@ -1137,6 +1032,15 @@ gt_tile_kernel(TileParams p) {
     // ---- 4. remaining entries of each light row, CSR online softmax, output.
     // Each lane group takes rows g, g + P, ... of the wave's strip; the entries
     // of a group's next row are requested before the current row's gathers.
+    AttnOp<bf16_tag, H, D, KIND> op;
+    op.Q = p.Q;
+    op.K = p.K;
+    op.V = p.V;
+    op.out = p.out;
+    op.lse = p.lse;
+    op.row_shift = __builtin_ctz(HD * 2);
+    op.heads = H;
+    op.c = p.c;
     const int g = lane / G, lig = lane % G;
     int32_t* gtile = lds.big.rest.ctile[wv] + g * kWinMaxDeg;
     constexpr int kRowPer = (kWinMaxDeg + G - 1) / G;  // a light row: at most kWinMaxDeg entries
@@ -1148,21 +1052,18 @@ gt_tile_kernel(TileParams p) {
     // move reads zero from an inactive lane), with selects rather than
     // branches.
     constexpr bool kQRegs = QFromOperands<H, D, KIND>::value;
-    auto row_vector = [&](int pass, uint4 (&qp)[Gm::kNV]) {
+    auto row_vector = [&](int pass) -> uint4 {
+        const int e0 = 8 * lig;  // first element of this lane's piece
+        const int src = 16 * ((e0 % 32) / 8) + pass * P + g, tsel = e0 / 32;
+        uint32_t v[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            const int e0 = 8 * (lig + k * G);  // first element of this lane's piece
-            const int src = 16 * ((e0 % 32) / 8) + pass * P + g, tsel = e0 / 32;
-            uint32_t v[4] = {0, 0, 0, 0};
+        for (int t = 0; t < HD / 32; ++t) {
+            const uint32_t x[4] = {(uint32_t)__shfl((int)qreg[t].x, src), (uint32_t)__shfl((int)qreg[t].y, src),
+                                   (uint32_t)__shfl((int)qreg[t].z, src), (uint32_t)__shfl((int)qreg[t].w, src)};
 #pragma unroll
-            for (int t = 0; t < HD / 32; ++t) {
-                const uint32_t x[4] = {(uint32_t)__shfl((int)qreg[t].x, src), (uint32_t)__shfl((int)qreg[t].y, src),
-                                       (uint32_t)__shfl((int)qreg[t].z, src), (uint32_t)__shfl((int)qreg[t].w, src)};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) v[c] = tsel == t ? x[c] : v[c];
-            }
-            qp[k] = make_uint4(v[0], v[1], v[2], v[3]);
+            for (int c = 0; c < 4; ++c) v[c] = tsel == t ? x[c] : v[c];
         }
+        return make_uint4(v[0], v[1], v[2], v[3]);
     };
     auto load_entries = [&](int pass, int32_t (&e)[kRowPer]) {
         const int sr = pass * P + g, wr = 16 * wv + sr;
@@ -1182,28 +1083,25 @@ gt_tile_kernel(TileParams p) {
 #pragma unroll
         for (int k = 0; k < kRowPer; ++k) re[k] = nxt[k];
         if (pass + 1 < kPasses) load_entries(pass + 1, nxt);
-        uint4 qp[Gm::kNV];
-        if constexpr (kQRegs) row_vector(pass, qp);
+        uint4 qp = make_uint4(0, 0, 0, 0);
+        if constexpr (kQRegs) qp = row_vector(pass);
         const int sr = pass * P + g;
         if (!((light_bits >> (4 * sr)) & 1ull)) continue;
         const bool use_tile = dense && ((ok_bits >> (4 * sr)) & 1ull);
         const int wr = 16 * wv + sr;
         const int64_t row = r0 + wr;
         RS st;
+        st.reset();
         if constexpr (kQRegs)
             st.begin_loaded(qp);
         else
-            st.begin(p.Q, row, lig);
+            st.begin(op, (int32_t)row, lig);
         if (use_tile) {
+            const float2 ml = lds.ml[wv][sr][lig / Gm::kHL];
+            st.m = ml.x;
+            st.l = ml.y;
 #pragma unroll
-            for (int k = 0; k < Gm::kNV; ++k) {
-                const int v = lig + k * G;
-                const float2 ml = lds.ml[wv][sr][v / Gm::kHL];
-                st.m[k] = ml.x;
-                st.l[k] = ml.y;
-#pragma unroll
-                for (int q = 0; q < Gm::kEPV; ++q) st.acc[k][q] = lds.big.rest.acc[wv][sr][v * Gm::kEPV + q];
-            }
+            for (int q = 0; q < Gm::kEPV; ++q) st.acc[q] = lds.big.rest.acc[wv][sr][lig * Gm::kEPV + q];
         }
         // the row's remaining entries (outside the tile) into gtile
         const int64_t eb = lds.rp[wr], ee = lds.rp[wr + 1];
@@ -1224,10 +1122,10 @@ gt_tile_kernel(TileParams p) {
             int32_t j[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) j[u] = gtile[(t + u < n_take) ? t + u : n_take - 1];
-            st.step(p.K, p.V, j, nvalid, lig, p.c);
+            st.step(op, j, nvalid, lig);
         }
         wave_lds_fence();
-        st.store_out(p.out, p.lse, row, lig);
+        st.store_out(op, (int32_t)row, lig);
     }
 }
 
@@ -1488,74 +1386,6 @@ hipError_t launch_partition(const PartParams& pp, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// Merge of the chunk partials of each heavy row, in chunk order (one
-// wavefront per row; each lane owns H*D/64 consecutive accumulator floats).
-// Partials are loaded kMergeBatch chunks at a time so their latencies
-// overlap; the merge itself stays sequential in chunk order.
-constexpr int kMergeBatch = 8;
-
-template <typename T, int H, int D>
-__global__ void __launch_bounds__(kBlock) gt_merge_kernel(MergeParams p) {
-#pragma clang fp contract(off)
-    constexpr int HD = H * D;
-    constexpr int F = HD >= kWave ? HD / kWave : 1;
-    constexpr int EB = Elt<T>::kBytes;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int f0 = lane * F;
-    const int head = f0 / D;
-    const int32_t n_heavy = min(CNT(p.counters, CNT_HEAVY), p.cap_heavy);
-    const int nwaves = gridDim.x * kWavesPerBlock;
-    for (int hr = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave; hr < n_heavy; hr += nwaves) {
-        if (f0 >= HD) continue;
-        const HeavyRow w = p.heavy[hr];
-        float m = -INFINITY, l = 0.0f, acc[F];
-#pragma unroll
-        for (int f = 0; f < F; ++f) acc[f] = 0.0f;
-        // a batch holds at most 64 accumulator floats per lane (wide rows take
-        // fewer chunks per batch)
-        constexpr int kB = 64 / F < kMergeBatch ? (64 / F > 1 ? 64 / F : 1) : kMergeBatch;
-        for (int c0 = 0; c0 < w.nch; c0 += kB) {
-            float2 ml[kB];
-            float a[kB][F];
-#pragma unroll
-            for (int u = 0; u < kB; ++u) {
-                const int64_t slot = w.base + (c0 + u < w.nch ? c0 + u : w.nch - 1);
-                ml[u] = p.part_ml[slot * H + head];
-#pragma unroll
-                for (int f = 0; f < F; ++f) a[u][f] = p.part_acc[slot * HD + f0 + f];
-            }
-            // chunks past the row's last are merged into nothing (selects, not
-            // a loop exit, so that the batch's loads stay ahead of their use)
-#pragma unroll
-            for (int u = 0; u < kB; ++u) {
-                const bool valid = c0 + u < w.nch;
-                const float mn = fmaxf(m, ml[u].x);
-                const float ca = (m == mn) ? 1.0f : fast_exp2(m - mn);
-                const float cb = (ml[u].x == mn) ? 1.0f : fast_exp2(ml[u].x - mn);
-                const float ln = l * ca + ml[u].y * cb;
-                l = valid ? ln : l;
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    const float an = acc[f] * ca + a[u][f] * cb;
-                    acc[f] = valid ? an : acc[f];
-                }
-                m = valid ? mn : m;
-            }
-        }
-        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-        if (p.lse && f0 % D == 0) p.lse[(int64_t)w.row * H + head] = lse_of(m, l);
-        char* orow = p.out + (int64_t)w.row * HD * EB;
-#pragma unroll
-        for (int f = 0; f < F; ++f) {
-            const float o = acc[f] * inv;
-            if constexpr (EB == 4)
-                reinterpret_cast<float*>(orow)[f0 + f] = o;
-            else
-                reinterpret_cast<uint16_t*>(orow)[f0 + f] = (uint16_t)bf16_rne(o);
-        }
-    }
-}
-
 // Clears n ints (the work-list counters at the start of a call).  A kernel
 // rather than hipMemsetAsync, so that a call recorded into a HIP graph holds
 // no memset node.
@@ -1655,7 +1485,9 @@ struct PhaseEvents {
 // queried.
 constexpr int kMaxDevices = 64;
 constexpr uint64_t kPoolKeepBytes = uint64_t(256) << 20;
-constexpr size_t kCacheBytes = size_t(256) << 20;  // free blocks kept per device
+// free blocks kept per device: a large call takes up to 256 MiB, and calls on
+// several streams hold a block each
+constexpr size_t kCacheBytes = size_t(1) << 30;
 constexpr size_t kBlockGranule = size_t(1) << 20;
 
 struct DevicePools {
@@ -1882,14 +1714,17 @@ hipError_t scratch_of(int dev, char** out) {
     return sa.err[dev];
 }
 
+gt_status scratch_exceeded(size_t bytes) {
+    return fail(GT_ERROR_INVALID_VALUE, "the call needs " + std::to_string(bytes) +
+                                            " bytes of workspace, more than the " + std::to_string(kScratchBytes) +
+                                            "-byte scratch array of gt_attn_fwd_noalloc");
+}
+
 // The workspace of one call: from the pool, or (allocation-free entry point)
 // the device's scratch array, whose size bounds the accepted problems.
 gt_status call_workspace(bool noalloc, int dev, size_t bytes, hipStream_t stream, CallWorkspace& ws) {
     if (!noalloc) return acquire_workspace(dev, bytes, stream, ws);
-    if (bytes > kScratchBytes)
-        return fail(GT_ERROR_INVALID_VALUE, "the call needs " + std::to_string(bytes) +
-                                                " bytes of workspace, more than the " + std::to_string(kScratchBytes) +
-                                                "-byte scratch array of gt_attn_fwd_noalloc");
+    if (bytes > kScratchBytes) return scratch_exceeded(bytes);
     char* p = nullptr;
     const hipError_t he = scratch_of(dev, &p);
     if (he != hipSuccess) return hip_fail(he, "hipGetSymbolAddress(scratch)");
@@ -2021,96 +1856,239 @@ int device_cus(int dev) {
     return cache[dev];
 }
 
-template <typename T, int H, int D, int KIND>
-int attn_blocks_per_cu(int dev) {
+// How the rows of a call are cut (see RowWork).
+struct RowRule {
+    int32_t light_max;
+    uint32_t split_min, chunk, nq_floor, nq_max, group_len;
+    int64_t max_slots;  // partial states at most, over all graphs of this size
+    bool forced;        // chunk length given by the caller
+};
+
+// Rows are cut into eight pieces from eight times the length at which a piece
+// saves what it costs.  It costs its partial state (slot_bytes, written and read
+// once) and about 256 bytes of row vector, list entry and index line; its
+// entries, of `gather_bytes` each, hit the L2 with a share `cover` more than in
+// row order, the part of an XCD's eighth of the sources that its L2 holds
+// (uniform sources; skewed ones gain more, hence the 3/4).  At least four entries
+// per piece, and 32 per wavefront of `groups` pieces.  Longer rows get pieces of
+// 32 to 64 entries, twice that where the call's gathers take more than about
+// 400 us.  Measured (us per call) with rows cut from 8*4 / 8*8 / 8*16 entries:
+// fp32 4x32 power law of 16 K nodes 41.6 / 45.4 / 58.3, of 169 K nodes 212 / 211
+// / 218, R-MAT scale 21 4932 / 4730 / 4764; fp32 4x128 power law of 169 K nodes
+// 985 / 880 / 870; bf16 8x64 lognormal 10411 / 10409 / 9910.
+RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int slot_bytes, int groups, const gt_tuning* tu) {
+    constexpr double kL2Bytes = 4.0 * 1024 * 1024, kGatherBytesPerSecond = 7.0e12;
+    double cover = kXcds * kL2Bytes / ((double)N * gather_bytes);
+    if (cover > 0.75) cover = 0.75;
+    const double pays = 0.75 * (2.0 * slot_bytes + 256.0) / (gather_bytes * cover);
+    uint32_t len = 32 / groups > 8 ? 32 / groups : (double)N * gather_bytes <= 2 * kL2Bytes ? 4 : 8;
+    while (len < 32 && 2 * len <= pays) len *= 2;
+    const bool large = (double)E * slices * gather_bytes / kGatherBytesPerSecond > 400e-6;
+    RowRule r;
+    r.light_max = (int32_t)(kXcds * len);
+    r.split_min = kXcds * len;
+    r.chunk = large ? 128 : 64;
+    r.nq_floor = kXcds;
+    r.nq_max = 256;
+    r.group_len = r.chunk;
+    r.forced = false;
+    r.max_slots = E / (2 * len) + 1;
+    if (tu && tu->light_max_deg > 0) r.light_max = tu->light_max_deg;
+    if (tu && tu->heavy_min_deg > 0) r.split_min = r.split_min > (uint32_t)tu->heavy_min_deg ? r.split_min : (uint32_t)tu->heavy_min_deg;
+    if (tu && tu->chunk_edges > 0) {
+        r.forced = true;
+        r.chunk = ((uint32_t)tu->chunk_edges + kWave - 1) / kWave * kWave;
+        r.split_min = r.chunk + 1;
+        if (tu->heavy_min_deg > 0 && (uint32_t)tu->heavy_min_deg > r.split_min) r.split_min = (uint32_t)tu->heavy_min_deg;
+        r.nq_floor = 1;
+        r.nq_max = 32;
+        r.max_slots = 2 * (E / r.chunk) + 1;
+    }
+    return r;
+}
+
+int floor_log2(uint64_t x) { return 63 - __builtin_clzll(x); }
+
+// Entries of the class lists together: class_capacity over the classes.
+uint64_t long_list_rows(int64_t N, int64_t E, int32_t light_max) {
+    uint64_t n = 0;
+    for (int c = floor_log2((uint64_t)light_max + 1); c < kClasses - 1; ++c) n += (uint64_t)((E >> c) < N ? (E >> c) : N);
+    return n;
+}
+
+void set_rule(RowWork& w, const RowRule& r) {
+    w.light_max = r.light_max;
+    w.min_class = floor_log2((uint64_t)r.light_max + 1);
+    w.split_min = r.split_min;
+    w.chunk = r.chunk;
+    w.nq_floor = r.nq_floor;
+    w.nq_max = r.nq_max;
+    w.group_len = r.group_len;
+}
+
+// Partial states and slices per launch.  Where the states of all slices fit
+// kSlicesTogether bytes, the slices share a launch (and a merge); larger calls
+// launch one slice at a time, which reuses the states' memory, up to the
+// workspace of the allocation-free entry point.
+struct SlotPlan {
+    uint32_t cap;
+    int slices;  // per launch
+};
+constexpr size_t kSlicesTogether = size_t(192) << 20;
+
+// `bounded`: the call's workspace has to fit the allocation-free entry point.
+SlotPlan slot_plan(const RowRule& r, int slices, size_t slot_bytes, size_t other_bytes, bool bounded) {
+    SlotPlan s;
+    s.slices = slices;
+    s.cap = (uint32_t)r.max_slots;
+    const size_t room = (other_bytes + 1024 < kScratchBytes ? kScratchBytes - other_bytes - 1024 : 0) / slot_bytes;
+    if (!r.forced && (size_t)r.max_slots * slices * slot_bytes > kSlicesTogether) s.slices = 1;
+    if ((!r.forced || bounded) && (size_t)r.max_slots > room / s.slices) s.cap = (uint32_t)(room / s.slices);
+    return s;
+}
+
+// Workgroups of the attention kernel that the device holds at once.
+template <typename T, int HS, int D, int KIND>
+int attn_resident(int dev) {
     static std::atomic<int> cache[64];
-    if (dev < 0 || dev >= 64) return 4;
+    if (dev < 0 || dev >= 64) return 4 * 256;
     if (cache[dev] == 0) {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gt_attn_kernel<T, H, D, KIND>, kBlock, 0) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gt_attn_kernel<T, HS, D, KIND>, kBlock, 0) != hipSuccess ||
             nb <= 0)
             nb = 4;
-        cache[dev] = nb;
+        cache[dev] = nb * device_cus(dev);
     }
     return cache[dev];
 }
 
+// Workgroups of a row kernel for one slice.  Light rows: two batches (a row per
+// lane group) per wave, four where the tile path may take them all; many more
+// waves than the device holds, so that the hardware scheduler evens out the
+// per-wave work (1, 2, 4 and 8 batches: R-MAT scale 21 fp32 4x32 5.08, 5.11, 5.33
+// and 5.77 ms).  Long rows: one batch per wave if three quarters of all entries lie
+// in pieces of 64, up to eight times the workgroups the device holds at once (a
+// wave without a batch still costs its prologue).
+struct RowGrid {
+    uint32_t blocks, long_blocks;
+};
+RowGrid row_grid(int64_t N, int64_t E, int groups, bool tiles, int resident, const gt_tuning* tu) {
+    auto blocks = [](int64_t batches, int64_t per_wave) {
+        const int64_t g = (batches + per_wave * kWavesPerBlock - 1) / (per_wave * kWavesPerBlock);
+        return (uint32_t)((g + kXcds - 1) / kXcds * kXcds);
+    };
+    RowGrid rg;
+    rg.long_blocks = blocks(3 * (E / 4) / ((int64_t)groups * 64) + 1, 1);
+    const uint32_t most = (uint32_t)(tiles ? 2 : 8) * (uint32_t)resident / kXcds * kXcds;
+    if (rg.long_blocks > most) rg.long_blocks = most;
+    rg.blocks = rg.long_blocks + blocks((N + groups - 1) / groups, tiles ? 4 : 2);
+    if (tu && tu->grid_blocks > 0) {
+        rg.long_blocks = blocks(((int64_t)tu->grid_blocks + 1) / 2 * kWavesPerBlock, 1);
+        rg.blocks = 2 * rg.long_blocks;
+    }
+    return rg;
+}
+
 constexpr int kDefaultTileMin = 256;
 
-template <typename T, int H, int D, int KIND>
+template <int H, int D, int KIND>
+hipError_t launch_tiles(const TileParams& tp, hipStream_t stream) {
+    const int64_t n_windows = (tp.N + kWin - 1) / kWin;
+    hipLaunchKernelGGL((gt_tile_kernel<H, D, KIND>), dim3((unsigned)n_windows), dim3(kBlock), 0, stream, tp);
+    return hipGetLastError();
+}
+
+// The tile kernel of H heads, for bf16 rows of at most 256 bytes.
+template <int D, int KIND>
+hipError_t pick_tiles(int H, const TileParams& tp, hipStream_t stream) {
+    if (H == 1) return launch_tiles<1, D, KIND>(tp, stream);
+    if constexpr (D <= 64)
+        if (H == 2) return launch_tiles<2, D, KIND>(tp, stream);
+    if constexpr (D <= 32)
+        if (H == 4) return launch_tiles<4, D, KIND>(tp, stream);
+    return hipErrorInvalidValue;
+}
+
+// Workspace that the allocation-free entry point asks for (its documented
+// limit): the row lists, and the partial states of rows cut into pieces of
+// `chunk` entries, for all heads at once.
+size_t noalloc_need(const Args& a, int elt_bytes, const gt_tuning* tu) {
+    const int row = a.H * a.D * elt_bytes, vecs = row / 16, lanes = vecs < kWave ? vecs : kWave;
+    const int rows = kWave / lanes, nv = vecs / lanes;
+    int u = 8 / nv > 2 ? 8 / nv : 2;
+    if (u > lanes) u = lanes;
+    const int light = tu && tu->light_max_deg > 0 ? tu->light_max_deg : 8 * u;
+    int chunk = default_chunk_long(a.E, 2 * row, rows * (rows >= 4 && u >= 8 ? u / 2 : u));
+    int heavy = default_front(chunk, rows);
+    if (tu && tu->heavy_min_deg > 0) heavy = tu->heavy_min_deg;
+    if (tu && tu->chunk_edges > 0) chunk = (tu->chunk_edges + kWave - 1) / kWave * kWave;
+    if (heavy <= light) heavy = light + 1;
+    const PartCaps caps = part_caps(a.E, heavy, chunk);
+    return (size_t)a.N * sizeof(int32_t) * (rows >= 4 ? 2 : 1) + (size_t)caps.heavy * sizeof(HeavyRow) +
+           (size_t)caps.items * sizeof(ChunkItem) + (size_t)caps.slots * a.H * (sizeof(float2) + a.D * sizeof(float));
+}
+
+template <typename T, int HS, int D, int KIND>
 gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
-    using Gm = Geo<T, H, D>;
-    // Defaults chosen by measurement on the five workload shapes (power law,
-    // R-MAT, SBM, lognormal hubs): a group handles rows of up to 8 steps;
-    // rows of degree >= 256 go first, split into chunks of up to 1024
-    // entries, shorter ones on small graphs (default_chunk); on large graphs
-    // longer chunks and, where a wave holds several rows, a higher front
-    // threshold (default_chunk_long, default_front).  GATv2
-    // counts its own single gather per entry but the graph-transformer step:
-    // that put its chunks at the measured optimum on the arxiv-shaped graph
-    // with 16K and 65K nodes (65K: 92.6 -> 77.5 us per call) and at 768
-    // entries on the 169K-node one (within 1 % of 1024).  Its own half step
-    // would give 384 entries there, 5.7 % slower.
-    int light_max = 8 * Gm::kU;
-    int chunk = KIND != KIND_GATV2
-                    ? default_chunk_long(a.E, 2 * Gm::kRowBytes, Gm::kP * StepOf<T, H, D, KIND_GT>::value)
-                    : default_chunk(a.E, Gm::kRowBytes, Gm::kP * StepOf<T, H, D, KIND_GT>::value);
-    int heavy_min = KIND != KIND_GATV2 ? default_front(chunk, Gm::kP) : 256;
-    int grid = 0;
-    // Dense-tile windows (tile shapes only): on by default, for windows
-    // estimated to hold at least 256 in-window entries, which a 64-row block
-    // at half density holds about eight times over (measured on the SBM
+    using Op = AttnOp<T, HS, D, KIND>;
+    constexpr int kRowSlice = HS * D * Elt<T>::kBytes;
+    constexpr int kSlotBytes = HS * (int)(D * sizeof(float) + sizeof(float2));
+    const int slices = a.H / HS;
+    RowRule rule = row_rule(a.N, a.E, slices, (KIND == KIND_GATV2 ? 1 : 2) * kRowSlice, kSlotBytes, Op::Gm::kP, tu);
+    // Dense-tile windows (bf16 rows of at most 256 bytes): on by default, for
+    // windows estimated to hold at least 256 in-window entries, which a 64-row
+    // block at half density holds about eight times over (measured on the SBM
     // workload; on the R-MAT one no window qualifies and the tile kernel
     // finds an empty list).
     int tile_min = kDefaultTileMin;
-    if (tu) {
-        if (tu->dense_tiles != 0) tile_min = tu->dense_tiles;  // < 0: off
-        if (tu->light_max_deg > 0) light_max = tu->light_max_deg;
-        if (tu->heavy_min_deg > 0) heavy_min = tu->heavy_min_deg;
-        if (tu->chunk_edges > 0) chunk = (tu->chunk_edges + kWave - 1) / kWave * kWave;
-        if (tu->grid_blocks > 0) grid = tu->grid_blocks;
-    }
-    if (heavy_min <= light_max) heavy_min = light_max + 1;
-    constexpr bool kTileShape =
-        KIND != KIND_GATV2 && std::is_same<T, bf16_tag>::value && H * D <= 128 && D % 32 == 0;
-    static_assert(!kTileShape || SortedLight<T, H, D, KIND>::value,
-                  "the tile path leaves its rows out of the light-row order");
-    const bool tiles = kTileShape && tile_min > 0;
-    if (tiles && light_max > kWinMaxDeg) light_max = kWinMaxDeg;
+    if (tu && tu->dense_tiles != 0) tile_min = tu->dense_tiles;  // < 0: off
+    constexpr bool kTileShape = KIND != KIND_GATV2 && std::is_same<T, bf16_tag>::value && D <= 128;
+    static_assert(!kTileShape || Op::kSorted, "the tile path leaves its rows out of the light-row order");
+    const bool tile_rows = kTileShape && a.H * D <= 128, tile_call = tile_rows && tile_min > 0;
+    // (the same light rows with the path off: a row that it streams has the same
+    // bits then)
+    if (tile_rows && !(tu && tu->light_max_deg > 0)) rule.light_max = kWinMaxDeg;
+    if (tile_call && rule.light_max > kWinMaxDeg) rule.light_max = kWinMaxDeg;
 
     int dev = 0;
     if (const gt_status ds = call_device(stream, &dev); ds != GT_SUCCESS) return ds;
     hipError_t he = hipSuccess;
-    if (grid <= 0) {
-        // About two light items (P rows each) per wave, between 4x and 64x the
-        // number of workgroups the device holds at once: finer than one
-        // resident wave of workgroups so the hardware scheduler evens out the
-        // per-wave work, coarse enough to keep dispatch cheap.
-        const int64_t resident = (int64_t)device_cus(dev) * attn_blocks_per_cu<T, H, D, KIND>(dev);
-        const int64_t light_items = (a.N + Gm::kP - 1) / Gm::kP;
-        int64_t g = light_items / (2 * kWavesPerBlock);
-        if (g < 4 * resident) g = 4 * resident;
-        if (g > 64 * resident) g = 64 * resident;
-        const int64_t need = (light_items + kWavesPerBlock - 1) / kWavesPerBlock;
-        if (g > need) g = need;
-        grid = (int)(g > 0 ? g : 1);
-    }
-    grid = (grid + kXcds - 1) / kXcds * kXcds;
+    const RowGrid rg = row_grid(a.N, a.E, Op::Gm::kP, tile_call, attn_resident<T, HS, D, KIND>(dev), tu);
+    // (calls that the allocation-free entry point takes keep their workspace
+    // within its array through either entry point, so that both give the same
+    // bits)
+    const size_t need = noalloc_need(a, Elt<T>::kBytes, tu);
+    const bool bounded = need <= kScratchBytes;
+    if (a.noalloc && !bounded) return scratch_exceeded(need);
 
-    // workspace: counters | medium rows | heavy rows | chunk items | partial (m,l) | partial acc
-    const PartCaps caps = part_caps(a.E, heavy_min, chunk);
-    size_t off = 0;
-    const size_t o_cnt = off;      off = align_up(off + 2 * kCntSetWords * sizeof(int32_t), 256);  // two sets
-    const size_t o_med = off;      off = align_up(off + (size_t)a.N * sizeof(int32_t), 256);
-    const size_t o_heavy = off;    off = align_up(off + (size_t)caps.heavy * sizeof(HeavyRow), 256);
-    const size_t o_chunks = off;   off = align_up(off + (size_t)caps.items * sizeof(ChunkItem), 256);
-    const size_t o_ml = off;       off = align_up(off + (size_t)caps.slots * H * sizeof(float2), 256);
-    const size_t o_acc = off;      off = align_up(off + (size_t)caps.slots * H * D * sizeof(float), 256);
-    const size_t o_light = off;
-    off = align_up(off + (!SortedLight<T, H, D, KIND>::value ? 0 : (size_t)a.N * sizeof(int32_t)), 256);
+    // workspace: counters | long rows | light rows | window flags | partial (m,l) | partial acc
+    RowWork w;
+    w.rowptr = a.rowptr;
+    w.colidx = a.colidx;
+    w.N = a.N;
+    w.E = (uint32_t)a.E;
     const int64_t n_windows = (a.N + kWin - 1) / kWin;
-    const size_t o_win = off;
-    off = align_up(off + (tiles ? (size_t)n_windows : 0), 256);
+    // The allocation-free entry point takes the light rows in id order where
+    // their step order would not fit its array (more than 26 million nodes; the
+    // order changes no result), and then without the tile path, which needs it.
+    const bool fits = (size_t)a.N * (sizeof(LightRow) + 1) <= kScratchBytes / 16 * 14;
+    const bool tiles = tile_call && (!bounded || fits);
+    const bool sorted = Op::kSorted && (!a.noalloc || fits);
+    size_t off = 0;
+    const size_t o_cnt = off;    off = align_up(off + 2 * kRowsSetWords * sizeof(int32_t), 256);  // two sets
+    const size_t o_light = off;  off = align_up(off + (sorted ? (size_t)a.N * sizeof(LightRow) : 0), 256);
+    const size_t o_deg = off;    off = align_up(off + (sorted ? (size_t)a.N : 0), 256);
+    const size_t o_win = off;    off = align_up(off + (tiles ? (size_t)n_windows : 0), 256);
+    const size_t o_long = off;
+    // (a larger light bound makes the class lists shorter: only near 2^31 entries)
+    while (bounded && off + long_list_rows(a.N, a.E, rule.light_max) * sizeof(LongRow) + 4096 > kScratchBytes)
+        rule.light_max = 2 * rule.light_max + 1;
+    set_rule(w, rule);
+    off = align_up(off + (size_t)long_list_rows(a.N, a.E, w.light_max) * sizeof(LongRow), 256);
+    const SlotPlan sp = slot_plan(rule, slices, kSlotBytes, off, bounded);
+    w.cap_slots = sp.cap;
+    const size_t o_ml = off;     off = align_up(off + (size_t)sp.cap * sp.slices * HS * sizeof(float2), 256);
+    const size_t o_acc = off;    off = align_up(off + (size_t)sp.cap * sp.slices * HS * D * sizeof(float), 256);
     const size_t ws_bytes = off;
 
     CallWorkspace cw;
@@ -2123,37 +2101,30 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     // scratch array and a captured stream clear the one set they use.
     int32_t* cnt_base = reinterpret_cast<int32_t*>(ws + o_cnt);
     const bool alternate = cw.kind == CallWorkspace::CACHED;
-    int32_t* counters = cnt_base + (alternate ? (cw.block.gen & 1u) * kCntSetWords : 0);
+    w.counters = cnt_base + (alternate ? (cw.block.gen & 1u) * kRowsSetWords : 0);
+    w.long_list = reinterpret_cast<LongRow*>(ws + o_long);
+    w.light_list = sorted ? reinterpret_cast<LightRow*>(ws + o_light) : nullptr;
+    w.light_deg = reinterpret_cast<uint8_t*>(ws + o_deg);
+    w.long_blocks = 0;
+    w.maybe_no_light = tiles;
 
     // (the allocation-free entry point records no profiling events: creating
     // them is a runtime allocation)
     PhaseEvents ph;
     if (!a.noalloc && (he = ph.start(stream)) != hipSuccess) return hip_fail(he, "profiling events");
-    if (!(alternate && cw.block.primed) && (he = clear_counters(counters, kCntSetWords, stream)) != hipSuccess)
+    if (!(alternate && cw.block.primed) && (he = clear_counters(w.counters, kRowsSetWords, stream)) != hipSuccess)
         return hip_fail(he, "counter clear");
 
-    PartParams pp;
-    pp.rowptr = a.rowptr;
-    pp.N = a.N;
-    pp.light_max = light_max;
-    pp.heavy_min = heavy_min;
-    pp.chunk = chunk;
-    pp.cap_heavy = (int32_t)caps.heavy;
-    pp.cap_items = (int32_t)caps.items;
-    pp.cap_slots = (int32_t)caps.slots;
-    pp.counters = counters;
-    pp.med_list = reinterpret_cast<int32_t*>(ws + o_med);
-    pp.heavy = reinterpret_cast<HeavyRow*>(ws + o_heavy);
-    pp.chunks = reinterpret_cast<ChunkItem*>(ws + o_chunks);
-    pp.light_list = !SortedLight<T, H, D, KIND>::value ? nullptr : reinterpret_cast<int32_t*>(ws + o_light);
-    pp.step = RowState<T, H, D, KIND>::kU;
+    SortParams pp;
+    pp.w = w;
+    pp.step = Op::kU;
+    pp.groups = Op::Gm::kP;
     if (tiles) {
-        pp.colidx = a.colidx;
         pp.win_flags = reinterpret_cast<uint8_t*>(ws + o_win);
         pp.tile_min = tile_min;
     }
-    if (alternate) pp.zero_next = cnt_base + ((cw.block.gen + 1u) & 1u) * kCntSetWords;
-    if ((he = launch_partition(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
+    if (alternate) pp.zero_next = cnt_base + ((cw.block.gen + 1u) & 1u) * kRowsSetWords;
+    if ((he = launch_sort_rows(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
     if (alternate) {
         ++cw.block.gen;
         cw.keep_primed = true;
@@ -2171,73 +2142,81 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
             tp.lse = a.lse;
             tp.N = a.N;
             tp.c = a.scale * 1.4426950408889634f;
-            tp.light_max = light_max;
+            tp.light_max = w.light_max;
             tp.min_entries = tile_min;
             tp.win_flags = pp.win_flags;
-            tp.counters = counters;
-            hipLaunchKernelGGL((gt_tile_kernel<H, D, KIND>), dim3((unsigned)n_windows), dim3(kBlock), 0, stream, tp);
-            if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "tile launch");
+            tp.counters = w.counters;
+            if ((he = pick_tiles<D, KIND>(a.H, tp, stream)) != hipSuccess) return hip_fail(he, "tile launch");
         }
     }
 
     AttnParams ap;
-    ap.rowptr = a.rowptr;
-    ap.colidx = a.colidx;
+    ap.w = w;
     ap.Q = static_cast<const char*>(a.Q);
     ap.K = static_cast<const char*>(a.K);
     ap.V = static_cast<const char*>(a.V);
     ap.out = static_cast<char*>(a.out);
     ap.lse = a.lse;
-    ap.N = a.N;
     ap.c = (KIND != KIND_GATV2 ? a.scale : 1.0f) * 1.4426950408889634f;
     ap.att = a.att;
     ap.slope = a.slope;
-    ap.light_max = light_max;
-    ap.cap_items = (int32_t)caps.items;
-    ap.counters = counters;
-    ap.med_list = pp.med_list;
-    ap.chunks = pp.chunks;
-    ap.part_acc = reinterpret_cast<float*>(ws + o_acc);
+    ap.row_shift = floor_log2((uint64_t)a.H * D * Elt<T>::kBytes);
+    ap.heads = a.H;
     ap.part_ml = reinterpret_cast<float2*>(ws + o_ml);
-    ap.light_list = pp.light_list;
-    hipLaunchKernelGGL((gt_attn_kernel<T, H, D, KIND>), dim3(grid), dim3(kBlock), 0, stream, ap);
-    if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "attention launch");
-    ph.mark(2, stream);
-
-    MergeParams mp;
-    mp.cap_heavy = (int32_t)caps.heavy;
-    mp.counters = counters;
-    mp.heavy = pp.heavy;
-    mp.part_acc = ap.part_acc;
-    mp.part_ml = ap.part_ml;
-    mp.out = ap.out;
-    mp.lse = a.lse;
-    int merge_grid = (int)((caps.heavy + kWavesPerBlock - 1) / kWavesPerBlock);
-    const int merge_cap = device_cus(dev) * 8;
-    if (merge_grid > merge_cap) merge_grid = merge_cap;
-    if (merge_grid < 1) merge_grid = 1;
-    hipLaunchKernelGGL((gt_merge_kernel<T, H, D>), dim3(merge_grid), dim3(kBlock), 0, stream, mp);
-    if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "merge launch");
+    ap.part_acc = reinterpret_cast<float*>(ws + o_acc);
+    const int cus = device_cus(dev);
+    ap.w.long_blocks = rg.long_blocks;
+    // at most as many cut rows as there are slots for eight pieces, or two
+    const int64_t cut_rows = (int64_t)sp.cap / (rule.forced ? 2 : kXcds) + 1;
+    int merge_grid = (int)((cut_rows + kWavesPerBlock - 1) / kWavesPerBlock);
+    if (merge_grid > cus * 8) merge_grid = cus * 8;
+    for (int s = 0; s < slices; s += sp.slices) {
+        ap.slice0 = s;
+        hipLaunchKernelGGL((gt_attn_kernel<T, HS, D, KIND>), dim3(rg.blocks, sp.slices), dim3(kBlock), 0, stream, ap);
+        if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "attention launch");
+        if (s + sp.slices >= slices) ph.mark(2, stream);
+        hipLaunchKernelGGL((gt_merge_kernel<T, HS, D>), dim3(merge_grid, sp.slices), dim3(kBlock), 0, stream, ap);
+        if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "merge launch");
+    }
     ph.commit(stream);
     return GT_SUCCESS;
 }
 
 using LaunchFn = gt_status (*)(const Args&, const gt_tuning*, hipStream_t);
 
+// The kernels of one slice of a row of H heads of D elements: the heads of 256
+// bytes, or one where a head has more.  (128-byte slices, the least that reads
+// whole cache lines, let an L2 cover twice the sources but visit every row twice
+// as often.  128 / 256 bytes, us per call: R-MAT scale 21 fp32 4x32 4666 / 4743,
+// bf16 4x32 2530 / 2573, bf16 8x64 lognormal 9889 / 9159, fp32 4x32 power law of
+// 169 K nodes 212 / 218, fp32 2x32 with 17 uniform sources for each of 1 M nodes
+// 1363 / 1266; GATv2, one row per entry: R-MAT scale 20 fp32 1492 / 1250.)
+constexpr int kSliceBytes = 256;
+
 template <typename T, int KIND>
 LaunchFn pick_hd(int32_t H, int32_t D) {
-#define GT_CASE(h, d) \
-    if (H == h && D == d) return &launch<T, h, d, KIND>;
-    GT_CASE(1, 32) GT_CASE(1, 64) GT_CASE(1, 128)
-    GT_CASE(2, 32) GT_CASE(2, 64) GT_CASE(2, 128)
-    GT_CASE(4, 32) GT_CASE(4, 64) GT_CASE(4, 128)
-    GT_CASE(8, 32) GT_CASE(8, 64) GT_CASE(8, 128)
-    GT_CASE(1, 256) GT_CASE(2, 256) GT_CASE(4, 256) GT_CASE(8, 256)
-    if constexpr (std::is_same<T, bf16_tag>::value) {  // a head must fit 64 lanes of 16 bytes
-        GT_CASE(1, 512) GT_CASE(2, 512) GT_CASE(4, 512)
+    constexpr bool kBf16 = std::is_same<T, bf16_tag>::value;
+    constexpr int kFit = kSliceBytes / Elt<T>::kBytes;  // elements
+    if (H != 1 && H != 2 && H != 4 && H != 8) return nullptr;
+    switch (D) {
+        case 32:
+            if constexpr (kFit >= 128)
+                if (H >= 4) return &launch<T, 4, 32, KIND>;
+            if constexpr (kFit >= 64)
+                if (H >= 2) return &launch<T, 2, 32, KIND>;
+            return &launch<T, 1, 32, KIND>;
+        case 64:
+            if constexpr (kFit >= 128)
+                if (H >= 2) return &launch<T, 2, 64, KIND>;
+            return &launch<T, 1, 64, KIND>;
+        case 128: return &launch<T, 1, 128, KIND>;
+        case 256: return &launch<T, 1, 256, KIND>;
+        case 512:  // a head must fit 64 lanes of 16 bytes
+            if constexpr (kBf16)
+                if (H <= 4) return &launch<T, 1, 512, KIND>;
+            return nullptr;
+        default: return nullptr;
     }
-#undef GT_CASE
-    return nullptr;
 }
 
 bool overlaps(const void* a, size_t an, const void* b, size_t bn) {

@@ -311,6 +311,9 @@ __global__ void __launch_bounds__(kBlock) gt_bwd_kernel(BwdParams p) {
     }
 }
 
+// Chunk partials in flight per lane
+constexpr int kMergeBatch = 8;
+
 // Ordered sum of the chunk partials of each split row, then scaling / storing.
 template <typename T, int H, int D, int MODE>
 __global__ void __launch_bounds__(kBlock) gt_bwd_merge_kernel(BwdParams p) {

@@ -1,0 +1,52 @@
+"""The row partition's edges, on small graphs against the oracle: degrees around
+the light bound and the degree octaves (rows whole, cut into pieces, spread over
+a wavefront), more long rows than there are partial states for (classes get
+fewer pieces), and rows in no order.  Every (lane group, heads per slice)
+combination of the slices."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from tests.helpers import TOL_BF16, TOL_F32, gate_error, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [("f32", 4, 32), ("f32", 8, 64), ("f32", 2, 128), ("f32", 1, 256), ("bf16", 1, 32), ("bf16", 4, 32),
+          ("bf16", 2, 64), ("bf16", 8, 128), ("bf16", 2, 256), ("bf16", 1, 512)]
+EDGES = [0, 1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 512, 513,
+         1023, 1024, 1025, 2047, 2048, 2600]
+
+
+def graph(kind):
+    """(rowptr, colidx) of N = 2700 nodes."""
+    N = 2700
+    rng = np.random.default_rng(5)
+    if kind == "edges":
+        deg = np.zeros(N, dtype=np.int64)
+        deg[rng.permutation(N)[:4 * len(EDGES)]] = EDGES * 4
+    elif kind == "many_short_pieces":  # rows just above the light bound: eight pieces each would not fit
+        deg = np.full(N, 33, dtype=np.int64)
+        deg[rng.permutation(N)[:40]] = 700
+    else:
+        deg = rng.integers(0, 90, N)
+        deg[[0, 77, N - 1]] = (2500, 1300, 600)
+    rowptr, colidx = synth.csr_from_degrees(9, N, deg, self_loops=False)
+    if kind == "unsorted":
+        for r in range(N):
+            rng.shuffle(colidx[rowptr[r]:rowptr[r + 1]])
+    return rowptr, colidx
+
+
+@pytest.mark.parametrize("kind", ["edges", "many_short_pieces", "unsorted"])
+@pytest.mark.parametrize("dtype,H,D", SHAPES)
+def test_forward_at_partition_edges(dtype, H, D, kind):
+    rowptr, colidx = graph(kind)
+    Q, K, V = synth.features(H * D, rowptr.size - 1, H, D, dtype)
+    scale = np.float32(1 / math.sqrt(D))
+    got = run_gpu(rowptr, colidx, Q, K, V, scale)
+    assert np.array_equal(got, run_gpu(rowptr, colidx, Q, K, V, scale))  # list orders differ from call to call
+    ref, absagg, _ = oracle.gt_attn_fwd(rowptr, colidx, Q, K, V, scale, want_lse=False)
+    assert gate_error(got, ref, absagg) <= (TOL_F32 if dtype == "f32" else TOL_BF16)
