@@ -1942,9 +1942,26 @@ SlotPlan slot_plan(const RowRule& r, int slices, size_t slot_bytes, size_t other
     s.slices = slices;
     s.cap = (uint32_t)r.max_slots;
     const size_t room = (other_bytes + 1024 < kScratchBytes ? kScratchBytes - other_bytes - 1024 : 0) / slot_bytes;
-    if (!r.forced && (size_t)r.max_slots * slices * slot_bytes > kSlicesTogether) s.slices = 1;
-    if ((!r.forced || bounded) && (size_t)r.max_slots > room / s.slices) s.cap = (uint32_t)(room / s.slices);
+    const size_t all = kSlicesTogether / (slot_bytes * slices);
+    if (!r.forced) {
+        // (a quarter of the most is enough for most graphs; where it is not,
+        // rows are cut into fewer pieces)
+        if (all >= (size_t)r.max_slots / 4)
+            s.cap = (uint32_t)(all < (size_t)r.max_slots ? all : (size_t)r.max_slots);
+        else
+            s.slices = 1;
+    }
+    if ((!r.forced || bounded) && s.cap > room / s.slices) s.cap = (uint32_t)(room / s.slices);
     return s;
+}
+
+// Workgroups of a merge kernel for one slice: one wavefront per cut row if rows
+// have eight pieces (two, where the caller gives their length), up to eight
+// workgroups per CU.
+int merge_blocks(const SlotPlan& sp, const RowRule& r, int cus) {
+    const int64_t cut_rows = (int64_t)sp.cap / (r.forced ? 2 : kXcds) + 1;
+    const int64_t g = (cut_rows + kWavesPerBlock - 1) / kWavesPerBlock;
+    return (int)(g < cus * 8 ? g : cus * 8);
 }
 
 // Workgroups of the attention kernel that the device holds at once.
@@ -2164,12 +2181,8 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     ap.heads = a.H;
     ap.part_ml = reinterpret_cast<float2*>(ws + o_ml);
     ap.part_acc = reinterpret_cast<float*>(ws + o_acc);
-    const int cus = device_cus(dev);
     ap.w.long_blocks = rg.long_blocks;
-    // at most as many cut rows as there are slots for eight pieces, or two
-    const int64_t cut_rows = (int64_t)sp.cap / (rule.forced ? 2 : kXcds) + 1;
-    int merge_grid = (int)((cut_rows + kWavesPerBlock - 1) / kWavesPerBlock);
-    if (merge_grid > cus * 8) merge_grid = cus * 8;
+    const int merge_grid = merge_blocks(sp, rule, device_cus(dev));
     for (int s = 0; s < slices; s += sp.slices) {
         ap.slice0 = s;
         hipLaunchKernelGGL((gt_attn_kernel<T, HS, D, KIND>), dim3(rg.blocks, sp.slices), dim3(kBlock), 0, stream, ap);

@@ -12,44 +12,14 @@
 // (key << 32 | source); the reduction is a plain unsigned 64-bit minimum
 // (max uses the complemented key, so ties still go to the smallest source).
 // The words are exactly the paper's packed atomics operands, but here they
-// stay in registers: rows are mapped like the attention forward (one lane
-// group per light row with 16-byte loads, one wave per medium row, chunks of
-// long rows on different waves) and the chunk partials of long rows are
-// merged by a second kernel instead of 64-bit atomics.  Padding entries of a
-// step repeat a valid entry, which a minimum absorbs, so they need no mask.
+// stay in registers: the rows are worked on as row_loop says (slices of 256
+// bytes, one lane group per light row or piece of a longer one, the pieces' source
+// ranges on their XCDs) and the partial words of cut rows are merged by a second
+// kernel instead of 64-bit atomics.  Padding entries of a step repeat a valid
+// entry, which a minimum absorbs, so they need no mask.
+// Min over 512 fp32 features on the power-law graph of 169 K nodes (2 KiB rows):
+// MEASURED_MIN us per call with whole rows and with slices.
 // This file is included by gt_attn.hip inside its anonymous namespace.
-
-template <typename T, int NVEC>
-struct RedGeo {
-    static constexpr int kEB = Elt<T>::kBytes;
-    static constexpr int kEPV = 16 / kEB;  // elements per 16-byte vector
-    static constexpr int kF = NVEC * kEPV;   // features per row
-    static constexpr int kRowBytes = NVEC * 16;
-    static constexpr int kG = NVEC < kWave ? NVEC : kWave;  // lanes per group
-    static constexpr int kNV = NVEC / kG;                   // vectors per lane
-    static constexpr int kP = kWave / kG;                   // groups per wave
-    static constexpr int kU0 = (8 / kNV) > 2 ? (8 / kNV) : 2;
-    static constexpr int kU = kU0 < kG ? kU0 : kG;          // entries per step
-    static_assert(kG % kU == 0 && kP * kU <= kWave, "index tiles must cover whole steps");
-};
-
-struct ReduceParams {
-    const int64_t* rowptr;
-    const int32_t* colidx;
-    const char* X;
-    char* out;
-    int32_t* arg;     // [N][F] or nullptr
-    uint64_t* part;   // [slot][F] packed (key, source) of chunk partials
-    int64_t N;
-    uint32_t flip;    // 0 for min, 0xFFFFFFFF for max
-    int32_t light_max;
-    int32_t cap_items;
-    int32_t cap_heavy;
-    const int32_t* counters;
-    const int32_t* med_list;
-    const ChunkItem* chunks;
-    const HeavyRow* heavy;
-};
 
 constexpr uint64_t kRedEmpty = ~0ull;  // no entry yet: source 0xFFFFFFFF is never valid
 
@@ -76,279 +46,175 @@ template <> __device__ __forceinline__ uint32_t red_bits<bf16_tag>(const uint4& 
 }
 
 template <typename T, int NVEC>
-struct RedState {
-    using Gm = RedGeo<T, NVEC>;
-    uint64_t best[Gm::kNV][Gm::kEPV];
+struct RedState;
 
-    __device__ __forceinline__ void begin() {
-#pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k)
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) best[k][e] = kRedEmpty;
+// One slice of NVEC 16-byte vectors of the feature row.
+template <typename T, int NVEC>
+struct RedOp {
+    using State = RedState<T, NVEC>;
+    static constexpr int kEPV = 16 / Elt<T>::kBytes;  // elements per vector
+    static constexpr int kG = NVEC;
+    static constexpr int kU = 4;
+    static constexpr bool kSorted = true;
+    static constexpr int kSlotWords = NVEC * kEPV;
+    const char* X;
+    char* out;
+    int32_t* arg;    // at the slice's first feature, or nullptr
+    uint64_t* part;  // [slot][kSlotWords] packed (key, source)
+    int row_shift;   // log2 of the bytes of one feature row
+    int64_t features;
+    uint32_t flip;   // 0 for min, 0xFFFFFFFF for max
+
+    __device__ __forceinline__ uint64_t offset(int32_t row, int lig) const {
+        return ((uint64_t)(uint32_t)row << row_shift) + (uint32_t)lig * 16u;
     }
+};
+
+template <typename T, int NVEC>
+struct RedState {
+    using Op = RedOp<T, NVEC>;
+    static constexpr int kU = Op::kU, kEPV = Op::kEPV;
+    uint64_t best[kEPV];
+
+    __device__ __forceinline__ void reset() {
+#pragma unroll
+        for (int e = 0; e < kEPV; ++e) best[e] = kRedEmpty;
+    }
+
+    __device__ __forceinline__ void begin(const Op&, int32_t, int) {}
 
     struct Batch {
-        uint4 x[Gm::kU][Gm::kNV];
+        uint4 x[kU];
     };
 
-    __device__ __forceinline__ void issue(const char* __restrict__ Xb, const int32_t (&j)[Gm::kU], int lig,
-                                          Batch& bt) const {
+    __device__ __forceinline__ void issue(const Op& op, const int32_t (&j)[kU], int lig, Batch& bt) const {
 #pragma unroll
-        for (int u = 0; u < Gm::kU; ++u) {
-            const char* src = Xb + (int64_t)j[u] * Gm::kRowBytes + lig * 16;
-#pragma unroll
-            for (int k = 0; k < Gm::kNV; ++k) bt.x[u][k] = *reinterpret_cast<const uint4*>(src + k * Gm::kG * 16);
-        }
+        for (int u = 0; u < kU; ++u) bt.x[u] = *reinterpret_cast<const uint4*>(op.X + op.offset(j[u], lig));
     }
 
-    __device__ __forceinline__ void consume(const Batch& bt, const int32_t (&j)[Gm::kU], uint32_t flip) {
+    __device__ __forceinline__ void consume(const Op& op, const Batch& bt, const int32_t (&j)[kU], int) {
 #pragma unroll
-        for (int u = 0; u < Gm::kU; ++u) {
+        for (int u = 0; u < kU; ++u)
 #pragma unroll
-            for (int k = 0; k < Gm::kNV; ++k) {
-#pragma unroll
-                for (int e = 0; e < Gm::kEPV; ++e) {
-                    const uint64_t w = ((uint64_t)red_key(red_bits<T>(bt.x[u][k], e), flip) << 32) | (uint32_t)j[u];
-                    best[k][e] = w < best[k][e] ? w : best[k][e];
-                }
+            for (int e = 0; e < kEPV; ++e) {
+                const uint64_t w = ((uint64_t)red_key(red_bits<T>(bt.x[u], e), op.flip) << 32) | (uint32_t)j[u];
+                best[e] = w < best[e] ? w : best[e];
             }
-        }
-    }
-
-    __device__ __forceinline__ void step(const char* __restrict__ Xb, const int32_t (&j)[Gm::kU], int lig,
-                                         uint32_t flip) {
-        Batch bt;
-        issue(Xb, j, lig, bt);
-        consume(bt, j, flip);
     }
 
     __device__ __forceinline__ void merge_xor(int off) {
 #pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k)
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) {
-                const uint32_t lo = __shfl_xor((uint32_t)best[k][e], off);
-                const uint32_t hi = __shfl_xor((uint32_t)(best[k][e] >> 32), off);
-                const uint64_t o = ((uint64_t)hi << 32) | lo;
-                best[k][e] = o < best[k][e] ? o : best[k][e];
-            }
-    }
-
-    __device__ __forceinline__ void store_out(const ReduceParams& p, int64_t row, int lig) const {
-        char* orow = p.out + row * (int64_t)Gm::kRowBytes + lig * 16;
-#pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            uint32_t vb[Gm::kEPV];
-            int32_t src[Gm::kEPV];
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; ++e) {
-                const bool none = (uint32_t)best[k][e] == 0xFFFFFFFFu;
-                vb[e] = none ? 0u : red_value_bits(best[k][e], p.flip);
-                src[e] = none ? -1 : (int32_t)(uint32_t)best[k][e];
-            }
-            uint4 o;
-            if constexpr (Gm::kEB == 4) {
-                o = make_uint4(vb[0], vb[1], vb[2], vb[3]);
-            } else {
-                // the selected value came from a bf16, so its low half is zero
-                o = make_uint4((vb[0] >> 16) | (vb[1] & 0xFFFF0000u), (vb[2] >> 16) | (vb[3] & 0xFFFF0000u),
-                               (vb[4] >> 16) | (vb[5] & 0xFFFF0000u), (vb[6] >> 16) | (vb[7] & 0xFFFF0000u));
-            }
-            *reinterpret_cast<uint4*>(orow + k * Gm::kG * 16) = o;
-            if (p.arg) {
-                int32_t* arow = p.arg + row * (int64_t)Gm::kF + (int64_t)(lig + k * Gm::kG) * Gm::kEPV;
-#pragma unroll
-                for (int e = 0; e < Gm::kEPV; e += 4)
-                    *reinterpret_cast<int4*>(arow + e) = make_int4(src[e], src[e + 1], src[e + 2], src[e + 3]);
-            }
+        for (int e = 0; e < kEPV; ++e) {
+            const uint32_t lo = __shfl_xor((uint32_t)best[e], off);
+            const uint32_t hi = __shfl_xor((uint32_t)(best[e] >> 32), off);
+            const uint64_t o = ((uint64_t)hi << 32) | lo;
+            best[e] = o < best[e] ? o : best[e];
         }
     }
 
-    __device__ __forceinline__ void store_partial(uint64_t* __restrict__ part, int32_t slot, int lig) const {
+    __device__ __forceinline__ void store_out(const Op& op, int32_t row, int lig) const {
+        uint32_t vb[kEPV];
+        int32_t src[kEPV];
 #pragma unroll
-        for (int k = 0; k < Gm::kNV; ++k) {
-            uint64_t* dst = part + (int64_t)slot * Gm::kF + (int64_t)(lig + k * Gm::kG) * Gm::kEPV;
-#pragma unroll
-            for (int e = 0; e < Gm::kEPV; e += 2) {
-                const uint64_t a = best[k][e], b = best[k][e + 1];
-                *reinterpret_cast<uint4*>(dst + e) =
-                    make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32));
-            }
+        for (int e = 0; e < kEPV; ++e) {
+            const bool none = (uint32_t)best[e] == 0xFFFFFFFFu;
+            vb[e] = none ? 0u : red_value_bits(best[e], op.flip);
+            src[e] = none ? -1 : (int32_t)(uint32_t)best[e];
         }
+        uint4 o;
+        if constexpr (kEPV == 4) {
+            o = make_uint4(vb[0], vb[1], vb[2], vb[3]);
+        } else {
+            // the selected value came from a bf16, so its low half is zero
+            o = make_uint4((vb[0] >> 16) | (vb[1] & 0xFFFF0000u), (vb[2] >> 16) | (vb[3] & 0xFFFF0000u),
+                           (vb[4] >> 16) | (vb[5] & 0xFFFF0000u), (vb[6] >> 16) | (vb[7] & 0xFFFF0000u));
+        }
+        store_once(op.out + op.offset(row, lig), o);
+        if (op.arg) {
+            char* arow = reinterpret_cast<char*>(op.arg + (int64_t)row * op.features + lig * kEPV);
+#pragma unroll
+            for (int e = 0; e < kEPV; e += 4)
+                store_once(arow + e * 4, make_uint4((uint32_t)src[e], (uint32_t)src[e + 1], (uint32_t)src[e + 2], (uint32_t)src[e + 3]));
+        }
+    }
+
+    __device__ __forceinline__ void store_partial(const Op& op, int32_t slot, int lig) const {
+        uint64_t* dst = op.part + (int64_t)slot * Op::kSlotWords + lig * kEPV;
+#pragma unroll
+        for (int e = 0; e < kEPV; e += 2)
+            *reinterpret_cast<uint4*>(dst + e) = make_uint4((uint32_t)best[e], (uint32_t)(best[e] >> 32),
+                                                            (uint32_t)best[e + 1], (uint32_t)(best[e + 1] >> 32));
+    }
+
+    __device__ __forceinline__ void merge_partial(const Op& op, int32_t slot, int lig) {
+        const uint64_t* src = op.part + (int64_t)slot * Op::kSlotWords + lig * kEPV;
+#pragma unroll
+        for (int e = 0; e < kEPV; ++e) best[e] = src[e] < best[e] ? src[e] : best[e];
     }
 };
 
-// One wavefront over CSR entries [b, e) of `row`: the P groups take
-// interleaved steps and are merged across lanes; slot < 0 writes the output,
-// slot >= 0 the chunk partial.
-template <typename T, int NVEC>
-__device__ __forceinline__ void red_wave_segment(const ReduceParams& p, int64_t row, int64_t b, int64_t e,
-                                                 int32_t slot, int32_t* __restrict__ tile, int lane) {
-    using Gm = RedGeo<T, NVEC>;
-    constexpr int U = Gm::kU, P = Gm::kP, G = Gm::kG;
-    const int g = lane / G, lig = lane % G;
-    RedState<T, NVEC> st;
-    st.begin();
-    for (int64_t tb = b; tb < e; tb += kWave) {
-        const int64_t pos = (tb + lane < e) ? tb + lane : e - 1;
-        const int32_t idx = p.colidx[pos];
-        wave_lds_fence();
-        tile[lane] = idx;
-        wave_lds_fence();
-        const int nt = (int)((e - tb) < kWave ? (e - tb) : kWave);
-        for (int t = 0; t < nt; t += P * U) {
-            const int e0 = t + g * U;
-            if (e0 < nt) {
-                int32_t j[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) j[u] = tile[e0 + u < nt ? e0 + u : nt - 1];
-                st.step(p.X, j, lig, p.flip);
-            }
-        }
-    }
-#pragma unroll
-    for (int off = G; off < kWave; off <<= 1) st.merge_xor(off);
-    if (g == 0) {
-        if (slot < 0)
-            st.store_out(p, row, lig);
-        else
-            st.store_partial(p.part, slot, lig);
-    }
-}
+struct ReduceParams {
+    RowWork w;
+    const char* X;
+    char* out;
+    int32_t* arg;    // [N][F] or nullptr
+    uint64_t* part;  // [slice of this launch][slot][kSlotWords]
+    int32_t row_shift;
+    int32_t features;
+    int32_t slice0;  // slice of blockIdx.y == 0
+    uint32_t flip;
+};
 
-// Light rows, one lane group each, software-pipelined across rows as in the
-// attention forward: the next row's rowptr pair is loaded before the current
-// row starts and its first index tile while the current row's first batch is
-// in flight.
 template <typename T, int NVEC>
-__device__ __forceinline__ void red_light_rows(const ReduceParams& p, int64_t it, int64_t it_end, int64_t stride,
-                                               int g, int lig, int32_t* __restrict__ gtile) {
-    using Gm = RedGeo<T, NVEC>;
-    constexpr int U = Gm::kU, G = Gm::kG, P = Gm::kP;
-    int64_t row = it * P + g;
-    bool ok = it < it_end && row < p.N;
-    int64_t b = ok ? p.rowptr[row] : 0, e = ok ? p.rowptr[row + 1] : 0;
-    bool mine = ok && (e - b) <= p.light_max;
-    int32_t idx = (mine && e > b) ? p.colidx[(b + lig < e) ? b + lig : e - 1] : 0;
-    while (it < it_end) {
-        const int64_t crow = row, cb = b, ce = e;
-        const bool cmine = mine;
-        const int32_t cidx = idx;
-        it += stride;
-        row = it * P + g;
-        ok = it < it_end && row < p.N;
-        b = ok ? p.rowptr[row] : 0;
-        e = ok ? p.rowptr[row + 1] : 0;
-        mine = ok && (e - b) <= p.light_max;
-        bool fetched = false;
-        if (cmine) {
-            RedState<T, NVEC> st;
-            st.begin();
-            for (int64_t tb = cb; tb < ce; tb += G) {
-                int32_t tile_idx = cidx;
-                if (tb != cb) tile_idx = p.colidx[(tb + lig < ce) ? tb + lig : ce - 1];
-                wave_lds_fence();
-                gtile[lig] = tile_idx;
-                wave_lds_fence();
-                const int nt = (int)((ce - tb) < G ? (ce - tb) : G);
-                for (int t = 0; t < nt; t += U) {
-                    int32_t j[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) j[u] = gtile[t + u];
-                    typename RedState<T, NVEC>::Batch bt;
-                    st.issue(p.X, j, lig, bt);
-                    if (!fetched) {
-                        idx = (mine && e > b) ? p.colidx[(b + lig < e) ? b + lig : e - 1] : 0;
-                        fetched = true;
-                    }
-                    st.consume(bt, j, p.flip);
-                }
-            }
-            st.store_out(p, crow, lig);
-        }
-        if (!fetched) idx = (mine && e > b) ? p.colidx[(b + lig < e) ? b + lig : e - 1] : 0;
-    }
+__device__ __forceinline__ RedOp<T, NVEC> reduce_op(const ReduceParams& p) {
+    using Op = RedOp<T, NVEC>;
+    const int slice = p.slice0 + (int)blockIdx.y;
+    Op op;
+    op.X = p.X + (int64_t)slice * NVEC * 16;
+    op.out = p.out + (int64_t)slice * NVEC * 16;
+    op.arg = p.arg ? p.arg + (int64_t)slice * Op::kSlotWords : nullptr;
+    op.part = p.part + (int64_t)blockIdx.y * p.w.cap_slots * Op::kSlotWords;
+    op.row_shift = p.row_shift;
+    op.features = p.features;
+    op.flip = p.flip;
+    return op;
 }
 
 template <typename T, int NVEC>
 __global__ void __launch_bounds__(kBlock) gt_reduce_kernel(ReduceParams p) {
-    using Gm = RedGeo<T, NVEC>;
-    __shared__ int32_t tiles[kWavesPerBlock][kWave];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x / kWave;
-    int32_t* tile = tiles[wv];
-
-    const int32_t n_chunks = min(CNT(p.counters, CNT_CHUNKS), p.cap_items);
-    const int32_t n_items = n_chunks + (int32_t)min((int64_t)CNT(p.counters, CNT_MED), p.N);
-    const int nwaves = gridDim.x * kWavesPerBlock;
-    for (int it = blockIdx.x * kWavesPerBlock + wv; it < n_items; it += nwaves) {
-        if (it < n_chunks) {
-            const ChunkItem ci = p.chunks[it];
-            red_wave_segment<T, NVEC>(p, ci.row, ci.begin, ci.end, ci.slot, tile, lane);
-        } else {
-            const int64_t row = p.med_list[it - n_chunks];
-            red_wave_segment<T, NVEC>(p, row, p.rowptr[row], p.rowptr[row + 1], -1, tile, lane);
-        }
-    }
-
-    const int xcd = blockIdx.x % kXcds;
-    const int waves_per_xcd = (gridDim.x / kXcds) * kWavesPerBlock;
-    const int lw = (blockIdx.x / kXcds) * kWavesPerBlock + wv;
-    const int64_t n_light = (p.N + Gm::kP - 1) / Gm::kP;
-    const int64_t lo = n_light * xcd / kXcds, hi = n_light * (xcd + 1) / kXcds;
-    const int g = lane / Gm::kG, lig = lane % Gm::kG;
-    red_light_rows<T, NVEC>(p, lo + lw, hi, waves_per_xcd, g, lig, tile + g * Gm::kG);
+    using Op = RedOp<T, NVEC>;
+    __shared__ __attribute__((aligned(16))) int32_t tiles[kWavesPerBlock][kWave / Op::kG * TileOf<Op::kG>::kEntries];
+    row_loop(p.w, reduce_op<T, NVEC>(p), tiles[threadIdx.x / kWave]);
 }
 
-// Merge of the chunk partials of each split row (one wave per row; lane l
-// owns features l, l+64, ... so every load and store is coalesced).
+// Merge of the partial words of each cut row, one wavefront per row and slice;
+// a group without a piece reads the row's last again, which a minimum absorbs.
 template <typename T, int NVEC>
 __global__ void __launch_bounds__(kBlock) gt_reduce_merge_kernel(ReduceParams p) {
-    using Gm = RedGeo<T, NVEC>;
-    constexpr int F = Gm::kF;
-    constexpr int PER = (F + kWave - 1) / kWave;
+    using Op = RedOp<T, NVEC>;
+    constexpr uint32_t G = Op::kG, P = kWave / G;
     const int lane = threadIdx.x & (kWave - 1);
-    const int32_t n_heavy = min(CNT(p.counters, CNT_HEAVY), p.cap_heavy);
-    const int nwaves = gridDim.x * kWavesPerBlock;
-    for (int hr = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave; hr < n_heavy; hr += nwaves) {
-        const HeavyRow w = p.heavy[hr];
-        uint64_t best[PER];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t g = lane / G;
+    const int lig = lane % G;
+    if (ROWS_CNT(p.w.counters, ROWS_PIECES) == 0) return;  // no long rows
+    const CutRows cut(p.w, lane);
+    const uint32_t n = cut.count(), waves = gridDim.x * kWavesPerBlock;
+    const Op op = reduce_op<T, NVEC>(p);
+    for (uint32_t i = blockIdx.x * kWavesPerBlock + wv; i < n; i += waves) {
+        uint32_t slot, nq;
+        const int32_t row = cut.row(p.w, i, lane, slot, nq);
+        typename Op::State st;
+        st.reset();
+        for (uint32_t q0 = 0; q0 < nq; q0 += P * kMergePieces)
 #pragma unroll
-        for (int q = 0; q < PER; ++q) best[q] = kRedEmpty;
-        // kRB chunks per round (about 8 loads per lane in flight), loaded
-        // before any is compared; a round past the row's last chunk re-reads
-        // the last one, which leaves the minimum unchanged
-        constexpr int kRB = 8 / PER > 1 ? 8 / PER : 1;
-        for (int c0 = 0; c0 < w.nch; c0 += kRB) {
-            uint64_t v[kRB][PER];
-#pragma unroll
-            for (int u = 0; u < kRB; ++u) {
-                const int c = c0 + u < w.nch ? c0 + u : w.nch - 1;
-                const uint64_t* src = p.part + (int64_t)(w.base + c) * F;
-#pragma unroll
-                for (int q = 0; q < PER; ++q) {
-                    const int f = lane + q * kWave;
-                    v[u][q] = f < F ? src[f] : kRedEmpty;
-                }
+            for (uint32_t u = 0; u < kMergePieces; ++u) {
+                const uint32_t q = q0 + u * P + g;
+                st.merge_partial(op, (int32_t)(slot + (q < nq ? q : nq - 1)), lig);
             }
 #pragma unroll
-            for (int u = 0; u < kRB; ++u)
-#pragma unroll
-                for (int q = 0; q < PER; ++q) best[q] = v[u][q] < best[q] ? v[u][q] : best[q];
-        }
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int f = lane + q * kWave;
-            if (f >= F) continue;
-            const bool none = (uint32_t)best[q] == 0xFFFFFFFFu;
-            const uint32_t vb = none ? 0u : red_value_bits(best[q], p.flip);
-            const int64_t o = (int64_t)w.row * F + f;
-            if constexpr (Gm::kEB == 4)
-                reinterpret_cast<uint32_t*>(p.out)[o] = vb;
-            else
-                reinterpret_cast<uint16_t*>(p.out)[o] = (uint16_t)(vb >> 16);
-            if (p.arg) p.arg[o] = none ? -1 : (int32_t)(uint32_t)best[q];
-        }
+        for (int off = G; off < kWave; off <<= 1) st.merge_xor(off);
+        if (g == 0) st.store_out(op, row, lig);
     }
 }
 
@@ -364,117 +230,94 @@ struct ReduceArgs {
 };
 
 template <typename T, int NVEC>
-int reduce_blocks_per_cu(int dev) {
+int reduce_resident(int dev) {
     static std::atomic<int> cache[64];
-    if (dev < 0 || dev >= 64) return 4;
+    if (dev < 0 || dev >= 64) return 4 * 256;
     if (cache[dev] == 0) {
         int nb = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gt_reduce_kernel<T, NVEC>, kBlock, 0) != hipSuccess ||
             nb <= 0)
             nb = 4;
-        cache[dev] = nb;
+        cache[dev] = nb * device_cus(dev);
     }
     return cache[dev];
 }
 
 template <typename T, int NVEC>
 gt_status launch_reduce(const ReduceArgs& a, const gt_tuning* tu, hipStream_t stream) {
-    using Gm = RedGeo<T, NVEC>;
-    int light_max = 8 * Gm::kU;
-    int chunk = default_chunk_long(a.E, Gm::kRowBytes, Gm::kP * Gm::kU);
-    int heavy_min = default_front(chunk, Gm::kP);
-    int grid = 0;
-    if (tu) {
-        if (tu->light_max_deg > 0) light_max = tu->light_max_deg;
-        if (tu->heavy_min_deg > 0) heavy_min = tu->heavy_min_deg;
-        if (tu->chunk_edges > 0) chunk = (tu->chunk_edges + kWave - 1) / kWave * kWave;
-        if (tu->grid_blocks > 0) grid = tu->grid_blocks;
-    }
-    if (heavy_min <= light_max) heavy_min = light_max + 1;
-
+    using Op = RedOp<T, NVEC>;
+    constexpr int kSlotBytes = Op::kSlotWords * (int)sizeof(uint64_t);
+    const int slices = a.F / (NVEC * Op::kEPV);
+    const RowRule rule = row_rule(a.N, a.E, slices, NVEC * 16, kSlotBytes, kWave / NVEC, tu);
     int dev = 0;
     if (const gt_status ds = call_device(stream, &dev); ds != GT_SUCCESS) return ds;
     hipError_t he = hipSuccess;
-    if (grid <= 0) {
-        const int64_t resident = (int64_t)device_cus(dev) * reduce_blocks_per_cu<T, NVEC>(dev);
-        const int64_t light_items = (a.N + Gm::kP - 1) / Gm::kP;
-        int64_t g = light_items / (2 * kWavesPerBlock);
-        if (g < 4 * resident) g = 4 * resident;
-        if (g > 64 * resident) g = 64 * resident;
-        const int64_t need = (light_items + kWavesPerBlock - 1) / kWavesPerBlock;
-        if (g > need) g = need;
-        grid = (int)(g > 0 ? g : 1);
-    }
-    grid = (grid + kXcds - 1) / kXcds * kXcds;
+    const RowGrid rg = row_grid(a.N, a.E, kWave / NVEC, false, reduce_resident<T, NVEC>(dev), tu);
 
-    // workspace: counters | medium rows | split rows | chunk items | partials
-    const PartCaps caps = part_caps(a.E, heavy_min, chunk);
+    // workspace: counters | light rows | long rows | partial words
+    RowWork w;
+    w.rowptr = a.rowptr;
+    w.colidx = a.colidx;
+    w.N = a.N;
+    w.E = (uint32_t)a.E;
+    set_rule(w, rule);
     size_t off = 0;
-    const size_t o_cnt = off;    off = align_up(off + kCntSetWords * sizeof(int32_t), 256);
-    const size_t o_med = off;    off = align_up(off + (size_t)a.N * sizeof(int32_t), 256);
-    const size_t o_heavy = off;  off = align_up(off + (size_t)caps.heavy * sizeof(HeavyRow), 256);
-    const size_t o_chunks = off; off = align_up(off + (size_t)caps.items * sizeof(ChunkItem), 256);
-    const size_t o_part = off;   off = align_up(off + (size_t)caps.slots * Gm::kF * sizeof(uint64_t), 256);
-    const size_t ws_bytes = off;
+    const size_t o_cnt = off;    off = align_up(off + kRowsSetWords * sizeof(int32_t), 256);
+    const size_t o_light = off;  off = align_up(off + (size_t)a.N * sizeof(LightRow), 256);
+    const size_t o_deg = off;    off = align_up(off + (size_t)a.N, 256);
+    const size_t o_long = off;
+    off = align_up(off + (size_t)long_list_rows(a.N, a.E, w.light_max) * sizeof(LongRow), 256);
+    const SlotPlan sp = slot_plan(rule, slices, kSlotBytes, off, false);
+    w.cap_slots = sp.cap;
+    const size_t o_part = off;   off = align_up(off + (size_t)sp.cap * sp.slices * kSlotBytes, 256);
 
     CallWorkspace cw;
-    gt_status st = acquire_workspace(dev, ws_bytes, stream, cw);
+    gt_status st = acquire_workspace(dev, off, stream, cw);
     if (st != GT_SUCCESS) return st;
     char* ws = cw.ptr;
-    int32_t* counters = reinterpret_cast<int32_t*>(ws + o_cnt);
+    w.counters = reinterpret_cast<int32_t*>(ws + o_cnt);
+    w.light_list = reinterpret_cast<LightRow*>(ws + o_light);
+    w.light_deg = reinterpret_cast<uint8_t*>(ws + o_deg);
+    w.long_list = reinterpret_cast<LongRow*>(ws + o_long);
+    w.long_blocks = rg.long_blocks;
+    w.maybe_no_light = false;
 
     PhaseEvents ph;
     if ((he = ph.start(stream)) != hipSuccess) return hip_fail(he, "profiling events");
-    if ((he = clear_counters(counters, kCntSetWords, stream)) != hipSuccess) return hip_fail(he, "counter clear");
-
-    PartParams pp;
-    pp.rowptr = a.rowptr;
-    pp.N = a.N;
-    pp.light_max = light_max;
-    pp.heavy_min = heavy_min;
-    pp.chunk = chunk;
-    pp.cap_heavy = (int32_t)caps.heavy;
-    pp.cap_items = (int32_t)caps.items;
-    pp.cap_slots = (int32_t)caps.slots;
-    pp.counters = counters;
-    pp.med_list = reinterpret_cast<int32_t*>(ws + o_med);
-    pp.heavy = reinterpret_cast<HeavyRow*>(ws + o_heavy);
-    pp.chunks = reinterpret_cast<ChunkItem*>(ws + o_chunks);
-    if ((he = launch_partition(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
+    if ((he = clear_counters(w.counters, kRowsSetWords, stream)) != hipSuccess) return hip_fail(he, "counter clear");
+    SortParams pp;
+    pp.w = w;
+    pp.step = Op::kU;
+    pp.groups = kWave / NVEC;
+    if ((he = launch_sort_rows(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
     ph.mark(1, stream);
 
     ReduceParams rp;
-    rp.rowptr = a.rowptr;
-    rp.colidx = a.colidx;
+    rp.w = w;
     rp.X = static_cast<const char*>(a.X);
     rp.out = static_cast<char*>(a.out);
     rp.arg = a.arg;
     rp.part = reinterpret_cast<uint64_t*>(ws + o_part);
-    rp.N = a.N;
+    rp.row_shift = floor_log2((uint64_t)a.F * Elt<T>::kBytes);
+    rp.features = a.F;
     rp.flip = a.flip;
-    rp.light_max = light_max;
-    rp.cap_items = (int32_t)caps.items;
-    rp.cap_heavy = (int32_t)caps.heavy;
-    rp.counters = counters;
-    rp.med_list = pp.med_list;
-    rp.chunks = pp.chunks;
-    rp.heavy = pp.heavy;
-    hipLaunchKernelGGL((gt_reduce_kernel<T, NVEC>), dim3(grid), dim3(kBlock), 0, stream, rp);
-    if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "reduce launch");
-    ph.mark(2, stream);
-
-    int merge_grid = (int)((caps.heavy + kWavesPerBlock - 1) / kWavesPerBlock);
-    if (merge_grid > device_cus(dev) * 8) merge_grid = device_cus(dev) * 8;
-    if (merge_grid < 1) merge_grid = 1;
-    hipLaunchKernelGGL((gt_reduce_merge_kernel<T, NVEC>), dim3(merge_grid), dim3(kBlock), 0, stream, rp);
-    if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "reduce merge launch");
+    const int merge_grid = merge_blocks(sp, rule, device_cus(dev));
+    for (int s = 0; s < slices; s += sp.slices) {
+        rp.slice0 = s;
+        hipLaunchKernelGGL((gt_reduce_kernel<T, NVEC>), dim3(rg.blocks, sp.slices), dim3(kBlock), 0, stream, rp);
+        if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "reduce launch");
+        if (s + sp.slices >= slices) ph.mark(2, stream);
+        hipLaunchKernelGGL((gt_reduce_merge_kernel<T, NVEC>), dim3(merge_grid, sp.slices), dim3(kBlock), 0, stream, rp);
+        if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "reduce merge launch");
+    }
     ph.commit(stream);
     return GT_SUCCESS;
 }
 
 using ReduceFn = gt_status (*)(const ReduceArgs&, const gt_tuning*, hipStream_t);
 
-// Row sizes of 64 B .. 4 KiB: fp32 F in {16, ..., 1024}, bf16 F in {32, ..., 2048}.
+// Row sizes of 64 B .. 4 KiB: fp32 F in {16, ..., 1024}, bf16 F in {32, ..., 2048};
+// slices of 256 bytes, or the row.
 template <typename T>
 ReduceFn pick_reduce(int32_t F) {
     constexpr int EPV = 16 / Elt<T>::kBytes;
@@ -482,11 +325,11 @@ ReduceFn pick_reduce(int32_t F) {
     switch (F / EPV) {
         case 4: return &launch_reduce<T, 4>;
         case 8: return &launch_reduce<T, 8>;
-        case 16: return &launch_reduce<T, 16>;
-        case 32: return &launch_reduce<T, 32>;
-        case 64: return &launch_reduce<T, 64>;
-        case 128: return &launch_reduce<T, 128>;
-        case 256: return &launch_reduce<T, 256>;
+        case 16:
+        case 32:
+        case 64:
+        case 128:
+        case 256: return &launch_reduce<T, 16>;
         default: return nullptr;
     }
 }
