@@ -134,8 +134,8 @@ gt_status gt_attn_fwd_bf16(const int64_t* rowptr, const int32_t* colidx, const u
  *                   so very long rows get longer ones, and rows of a degree
  *                   octave that starts at no more than this stay whole
  *                   (default: eight pieces, more from 512 entries on (1024
- *                   where the gathers of a call take more than about 400 us),
- *                   up to 256, of 32 to 64 (64 to 128) entries)
+ *                   where the gathers of a call take more than about 60 us),
+ *                   up to 32)
  *   grid_blocks   : workgroups of the attention kernel per slice, rounded up to
  *                   a multiple of 16 (default: a wavefront per two batches of
  *                   light rows, and up to eight times the resident workgroups

@@ -69,25 +69,6 @@ constexpr int kXcds = 8;
 // their value rows); an option for rows whose steps are arithmetic-bound.
 enum { KIND_GT = 0, KIND_GATV2 = 1, KIND_GT_BF16W = 2 };
 
-// Work-list counters in the workspace, cleared by a fill kernel at the start
-// of each call.  Each counter sits on its own 256-byte line so that atomics
-// on different counters do not serialise on one cache line.
-//   CNT_MED, CNT_HEAVY, CNT_CHUNKS, CNT_SLOTS: medium rows, split rows, work
-//     items, partial slots (list lengths, reserved with atomics);
-//   CNT_OVERFLOW: set if a list capacity was exceeded (the CSR precondition
-//     was violated; the excess entries are dropped);
-//   CNT_LIGHT: nonzero if the light-row order holds any row (shapes that build
-//     one); a flag written with plain stores;
-//   CNT_WIN: byte 0 nonzero if some window was found dense, byte 1 if some
-//     window was not (byte flags written with plain stores, read as one word).
-enum {
-    CNT_MED = 0, CNT_HEAVY = 1, CNT_CHUNKS = 2, CNT_OVERFLOW = 3, CNT_SLOTS = 4, CNT_LIGHT = 5, CNT_WIN = 6,
-    CNT_COUNT = 7
-};
-constexpr int kCntStride = 64;                          // ints between counters
-constexpr int kCntSetWords = CNT_COUNT * kCntStride;   // one counter set
-#define CNT(c, i) ((c)[(i) * kCntStride])
-
 struct bf16_tag {};
 
 template <typename T> struct Elt;
@@ -110,47 +91,6 @@ struct Geo {
     static_assert(kRowBytes % 16 == 0, "row must be a whole number of 16-B vectors");
     static_assert(kHL >= 1 && kG % kHL == 0, "heads must tile the lane group");
     static_assert(kG % kU == 0 && kP * kU <= kWave, "index tiles must cover whole steps");
-};
-
-struct ChunkItem {
-    int32_t row;
-    int32_t slot;
-    int64_t begin;
-    int64_t end;
-};
-
-struct HeavyRow {
-    int32_t row;
-    int32_t base;  // first partial slot
-    int32_t nch;   // number of chunks
-    int32_t pad;
-};
-
-struct PartParams {
-    const int64_t* rowptr;
-    int64_t N;
-    int32_t light_max;
-    int32_t heavy_min;
-    int32_t chunk;
-    int32_t cap_heavy;
-    int32_t cap_items;  // work items: unsplit front rows + chunks of split rows
-    int32_t cap_slots;  // partial-state slots: chunks of split rows only
-    int32_t* counters;
-    int32_t* med_list;
-    HeavyRow* heavy;
-    ChunkItem* chunks;
-    int32_t* light_list = nullptr;  // or the block-local order of the light rows
-    int32_t step = 1;               // entries per step of the light-row loop (its step classes)
-    // Dense-tile windows (win_flags != nullptr): aligned 64-row windows whose
-    // light rows are estimated to hold >= tile_min entries inside the window
-    // are flagged for the tile kernel, and their light rows left out of the
-    // light-row order.  The estimate reads one entry of every 8th light row.
-    const int32_t* colidx = nullptr;
-    uint8_t* win_flags = nullptr;  // [ceil(N / 64)]
-    int32_t tile_min = 0;
-    // the workspace's other counter set, zeroed by block 0 for the next call
-    // that takes this workspace (nullptr: none)
-    int32_t* zero_next = nullptr;
 };
 
 // ------------------------------------------------------------ element codecs
@@ -1129,263 +1069,6 @@ gt_tile_kernel(TileParams p) {
     }
 }
 
-// Degree binning.  A block owns RPT * 256 contiguous rows; thread t takes
-// rows t, t+256, ... of the block, so every rowptr load is coalesced.  Medium
-// rows are compacted with wave ballots; heavy-row and chunk counts with block
-// scans; each block then reserves its output ranges with one atomic per list.
-// A heavy row is cut into at most kMaxChunks chunks of (about) equal length,
-// at least `chunk` entries each, so the ordered merge of a hub stays a few
-// load rounds long.
-constexpr int kMaxChunks = 32;
-constexpr int kLightClasses = 16;  // step-count classes of the light-row order
-
-// Exclusive scans over the block of three per-thread counts at once (one
-// barrier); totals in tot[0..2].
-__device__ __forceinline__ int3 block_exclusive_scan3(int3 v, int3* lds_waves, int* tot) {
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    int3 x = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int a = __shfl_up(x.x, o), b = __shfl_up(x.y, o), c = __shfl_up(x.z, o);
-        if (lane >= o) {
-            x.x += a;
-            x.y += b;
-            x.z += c;
-        }
-    }
-    if (lane == kWave - 1) lds_waves[wv] = x;
-    __syncthreads();
-    int3 before = make_int3(0, 0, 0);
-    tot[0] = tot[1] = tot[2] = 0;
-#pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) {
-        const int3 t = lds_waves[w];
-        if (w < wv) {
-            before.x += t.x;
-            before.y += t.y;
-            before.z += t.z;
-        }
-        tot[0] += t.x;
-        tot[1] += t.y;
-        tot[2] += t.z;
-    }
-    return make_int3(before.x + x.x - v.x, before.y + x.y - v.y, before.z + x.z - v.z);
-}
-
-__device__ __forceinline__ int chunks_of(int64_t deg, int chunk) {
-    const int64_t n = (deg + chunk - 1) / chunk;
-    return (int)(n < kMaxChunks ? n : kMaxChunks);
-}
-
-template <int RPT>
-__global__ void __launch_bounds__(kBlock) gt_partition_kernel(PartParams p) {
-    constexpr int kPartRowsPerThread = RPT;
-    constexpr int kPartRowsPerBlock = kBlock * RPT;
-    __shared__ int wave_cnt[kPartRowsPerThread][kWavesPerBlock];
-    __shared__ int3 scan3[kWavesPerBlock];
-    __shared__ int base[4];
-    __shared__ int cls_cnt[kLightClasses], cls_pos[kLightClasses];
-    __shared__ int win_dense[kPartRowsPerThread][kWavesPerBlock];  // dense-tile window flags of this block
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    const int64_t r0 = (int64_t)blockIdx.x * kPartRowsPerBlock;
-    int64_t rb[kPartRowsPerThread], deg[kPartRowsPerThread];
-    bool med[kPartRowsPerThread];
-    uint64_t mask[kPartRowsPerThread];
-    int n_heavy = 0, n_chunk = 0, n_slot = 0;
-    if (p.zero_next && blockIdx.x == 0)
-        for (int i = threadIdx.x; i < kCntSetWords; i += kBlock) p.zero_next[i] = 0;
-    if (p.light_list && threadIdx.x < kLightClasses) cls_cnt[threadIdx.x] = 0;
-#pragma unroll
-    for (int k = 0; k < kPartRowsPerThread; ++k) {
-        const int64_t r = r0 + k * kBlock + threadIdx.x;
-        rb[k] = 0;
-        deg[k] = 0;
-        if (r < p.N) {
-            rb[k] = p.rowptr[r];
-            deg[k] = p.rowptr[r + 1] - rb[k];
-        }
-        med[k] = deg[k] > p.light_max && deg[k] < p.heavy_min;
-        mask[k] = __ballot(med[k]);
-        if (lane == 0) wave_cnt[k][wv] = __popcll(mask[k]);
-        if (deg[k] >= p.heavy_min) {
-            const int nch = chunks_of(deg[k], p.chunk);
-            n_heavy += nch > 1 ? 1 : 0;
-            n_chunk += nch;
-            n_slot += nch > 1 ? nch : 0;
-        }
-    }
-    // Dense-tile windows.  In iteration k, wave wv holds the 64 rows of one
-    // aligned window (r0 is a multiple of 1024).  The window's light rows hold
-    // ld entries; every 8th light row contributes its middle entry as a
-    // sample, and the in-window share of the sampled rows' entries (self-loops
-    // not counted) estimates the window's in-window entries (the tile kernel
-    // counts them exactly and still streams a window that falls short).  A dense window's light rows
-    // belong to the tile kernel (tiled), all others stay on this path.
-    bool tiled[kPartRowsPerThread];
-#pragma unroll
-    for (int k = 0; k < kPartRowsPerThread; ++k) tiled[k] = false;
-    if (p.win_flags) {
-        int32_t smp[kPartRowsPerThread];
-#pragma unroll
-        for (int k = 0; k < kPartRowsPerThread; ++k) {
-            const int64_t r = r0 + k * kBlock + threadIdx.x;
-            smp[k] = -1;
-            if (r < p.N && deg[k] > 0 && deg[k] <= p.light_max && (lane & 7) == 0)
-                smp[k] = p.colidx[rb[k] + deg[k] / 2];
-        }
-#pragma unroll
-        for (int k = 0; k < kPartRowsPerThread; ++k) {
-            const int64_t r = r0 + k * kBlock + threadIdx.x;
-            const bool lt = r < p.N && deg[k] <= p.light_max;
-            // light degrees are <= 64, so a window's sums fit: ld <= 4096 and
-            // the sampled sums (8 rows) <= 512, packed two to a word
-            const int ld = wave_sum_i32(lt ? (int)deg[k] : 0);
-            // a sampled self-loop does not count: every row has at most one,
-            // and rows holding only their self-loop would make sparse windows
-            // look dense
-            const int sd = smp[k] >= 0 ? (int)deg[k] : 0;
-            const int si = (smp[k] >= 0 && smp[k] != r && ((int64_t)smp[k] >> 6) == (r >> 6)) ? sd : 0;
-            const int ss = wave_sum_i32(sd | (si << 16));
-            const int sd_w = ss & 0xFFFF, si_w = ss >> 16;
-            const bool dense = p.tile_min <= 1 ? ld > 0
-                                               : (ld >= p.tile_min && si_w > 0 &&
-                                                  (int64_t)si_w * ld >= (int64_t)p.tile_min * sd_w);
-            tiled[k] = dense && lt;
-            const int64_t win = (r0 + k * kBlock + wv * kWave) >> 6;
-            if (lane == 0) {
-                const bool exists = win * kWave < p.N;
-                if (exists) p.win_flags[win] = dense ? 1 : 0;
-                win_dense[k][wv] = !exists ? 2 : dense ? 1 : 0;  // 2: past the last row
-            }
-        }
-    }
-    if (p.light_list) {
-        // Light rows of this block in descending step count (a counting sort in
-        // LDS), so the lane groups of a wave take rows of similar length and a
-        // wave does not wait on one long row among short ones: the degree
-        // bucketing of the degree-aware mapping (Appendix B.1), applied to the
-        // rows that share a wavefront.  The order within
-        // a step class is arbitrary; every row is computed on its own, so the
-        // results do not depend on it.  Positions after the block's light rows
-        // hold -1.
-        __syncthreads();  // cls_cnt zeroed
-        int cls[kPartRowsPerThread];
-#pragma unroll
-        for (int k = 0; k < kPartRowsPerThread; ++k) {
-            const int64_t r = r0 + k * kBlock + threadIdx.x;
-            cls[k] = -1;
-            if (r < p.N && deg[k] <= p.light_max && !tiled[k]) {
-                const int64_t st = (deg[k] + p.step - 1) / p.step;
-                cls[k] = (int)(st < kLightClasses - 1 ? st : kLightClasses - 1);
-                atomicAdd(&cls_cnt[cls[k]], 1);
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int acc = 0;
-            for (int c = kLightClasses - 1; c >= 0; --c) {
-                cls_pos[c] = acc;
-                acc += cls_cnt[c];
-            }
-            cls_cnt[0] = acc;  // the block's light-row count (class 0's count is no longer needed)
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kPartRowsPerThread; ++k)
-            if (cls[k] >= 0) {
-                const int at = atomicAdd(&cls_pos[cls[k]], 1);
-                p.light_list[r0 + at] = (int32_t)(r0 + k * kBlock + threadIdx.x);
-            }
-        const int n_light_rows = cls_cnt[0];
-        const int64_t rows_here = (p.N - r0 < kPartRowsPerBlock) ? p.N - r0 : kPartRowsPerBlock;
-        for (int64_t j = n_light_rows + threadIdx.x; j < rows_here; j += kBlock) p.light_list[r0 + j] = -1;
-    }
-    int tots[3];
-    const int3 offs = block_exclusive_scan3(make_int3(n_heavy, n_chunk, n_slot), scan3, tots);
-    const int off_h = offs.x, off_c = offs.y, off_s = offs.z;
-    // The block's reservations: lanes 0..3 of wave 0 each add to one list
-    // counter, so the atomics go out together rather than one after another;
-    // lanes 4..6 raise flags with plain stores.
-    if (threadIdx.x < 7) {
-        const int t = threadIdx.x;
-        if (t < 4) {
-            int amount = 0, which = CNT_MED;
-            if (t == 0) {
-                for (int k = 0; k < kPartRowsPerThread; ++k)
-                    for (int w = 0; w < kWavesPerBlock; ++w) amount += wave_cnt[k][w];
-            } else {
-                amount = tots[t - 1];
-                which = t == 1 ? CNT_HEAVY : t == 2 ? CNT_CHUNKS : CNT_SLOTS;
-            }
-            base[t] = amount ? atomicAdd(&CNT(p.counters, which), amount) : 0;
-        } else if (t == 4) {
-            // light rows left in the order: none lets the attention kernel
-            // skip its light-row loop (every light row in dense windows)
-            if (p.light_list && cls_cnt[0] > 0) CNT(p.counters, CNT_LIGHT) = 1;
-        } else if (p.win_flags) {
-            const int want = t == 5 ? 1 : 0;  // lane 5: a dense window; lane 6: a sparse one
-            bool seen = false;
-            for (int k = 0; k < kPartRowsPerThread; ++k)
-                for (int w = 0; w < kWavesPerBlock; ++w) seen |= win_dense[k][w] == want;
-            if (seen) reinterpret_cast<uint8_t*>(&CNT(p.counters, CNT_WIN))[t - 5] = 1;
-        }
-    }
-    __syncthreads();
-    int pos = base[0];
-    int hid = base[1] + off_h, item = base[2] + off_c, slot = base[3] + off_s;
-#pragma unroll
-    for (int k = 0; k < kPartRowsPerThread; ++k) {
-        const int64_t r = r0 + k * kBlock + threadIdx.x;
-        int before = 0;
-        for (int w = 0; w < wv; ++w) before += wave_cnt[k][w];
-        if (med[k]) p.med_list[pos + before + __popcll(mask[k] & ((1ull << lane) - 1))] = (int32_t)r;
-        for (int w = 0; w < kWavesPerBlock; ++w) pos += wave_cnt[k][w];
-        if (deg[k] >= p.heavy_min) {
-            // Rows of degree >= heavy_min are placed first in the work list (the
-            // longest items start first).  A row that fits in one chunk is a
-            // single item writing its output directly; a longer row is split,
-            // its chunks get partial-state slots, and it is recorded for the
-            // ordered merge.  Only split rows take slots, so the slots number
-            // at most 2E/chunk (a split row of degree d > chunk has fewer than
-            // 2d/chunk chunks).
-            const int nch = chunks_of(deg[k], p.chunk);
-            const int split = nch > 1 ? 1 : 0;
-            if (hid + split > p.cap_heavy || item + nch > p.cap_items || (split && slot + nch > p.cap_slots)) {
-                atomicOr(&CNT(p.counters, CNT_OVERFLOW), 1);
-            } else if (!split) {
-                p.chunks[item] = ChunkItem{(int32_t)r, -1, rb[k], rb[k] + deg[k]};
-            } else {
-                const int64_t len = (deg[k] + nch - 1) / nch;
-                const int64_t end = rb[k] + deg[k];
-                p.heavy[hid] = HeavyRow{(int32_t)r, slot, nch, 0};
-                for (int c = 0; c < nch; ++c) {
-                    const int64_t cb = rb[k] + c * len;
-                    p.chunks[item + c] = ChunkItem{(int32_t)r, slot + c, cb < end ? cb : end,
-                                                   cb + len < end ? cb + len : end};
-                }
-            }
-            hid += split;
-            item += nch;
-            slot += split ? nch : 0;
-        }
-    }
-}
-
-// Launches the degree binning over pp.N rows.  Large graphs take 2048 rows
-// per block, smaller ones 1024, giving more blocks in parallel.  Measured on
-// MI355X: 169K rows 12.8 -> 10.5 us with 1024; 2.1M rows 32 -> 44 us with
-// 1024.
-hipError_t launch_partition(const PartParams& pp, hipStream_t stream) {
-    if (pp.N <= (int64_t(1) << 19)) {
-        const int grid = (int)((pp.N + 4 * kBlock - 1) / (4 * kBlock));
-        hipLaunchKernelGGL(gt_partition_kernel<4>, dim3(grid), dim3(kBlock), 0, stream, pp);
-    } else {
-        const int grid = (int)((pp.N + 8 * kBlock - 1) / (8 * kBlock));
-        hipLaunchKernelGGL(gt_partition_kernel<8>, dim3(grid), dim3(kBlock), 0, stream, pp);
-    }
-    return hipGetLastError();
-}
-
 // Clears n ints (the work-list counters at the start of a call).  A kernel
 // rather than hipMemsetAsync, so that a call recorded into a HIP graph holds
 // no memset node.
@@ -1759,73 +1442,6 @@ struct Args {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Capacities of the partition's lists for E entries.  Split rows have degree
-// > chunk, so they number at most E/(chunk+1); front rows (degree >=
-// heavy_min) at most E/heavy_min.  A split row of degree d has fewer than
-// 2d/chunk chunks, so work items are at most E/heavy_min + 2E/chunk and
-// partial-state slots at most 2E/chunk.  The merge kernel's grid follows the
-// split-row bound.
-struct PartCaps {
-    int64_t heavy, items, slots;
-};
-
-PartCaps part_caps(int64_t E, int heavy_min, int chunk) {
-    PartCaps c;
-    c.heavy = E / ((int64_t)chunk + 1) + 1;
-    c.slots = 2 * (E / chunk) + 1;
-    c.items = E / heavy_min + c.slots;
-    return c;
-}
-
-// Default chunk length of split rows.  A chunk is one wavefront's chain of
-// dependent steps (P*U entries each, about one memory round trip, ~1 us), so
-// the longest chunk bounds the call from below.  On a small graph a 1024-entry
-// chunk outlasts everything else: on the arxiv-shaped power-law graph with
-// fp32 4x32 features, 16K nodes took 76 us per call at 1024 against 48 us at
-// 256, and 65K nodes 114 us against 95 us at 512.  The default keeps a chunk's
-// steps within half the time the call's gathers take at ~7 TB/s, in multiples
-// of 64, capped at 1024 (longer chunks on large graphs: default_chunk_long
-// below).  With the graph-transformer forward (two gathered rows per entry)
-// the arxiv-shaped 169K-node graph gets 1024; the GATv2 forward, one gathered
-// row per entry, gets 768 there and 1024 from about twice its size.
-double chunk_budget(int64_t E, int64_t bytes_per_entry, int entries_per_step) {
-    constexpr double kGatherBytesPerSecond = 7.0e12, kStepSeconds = 1.0e-6;
-    const double gather_seconds = (double)E * (double)bytes_per_entry / kGatherBytesPerSecond;
-    return 0.5 * gather_seconds / kStepSeconds * entries_per_step;
-}
-
-int default_chunk(int64_t E, int64_t bytes_per_entry, int entries_per_step) {
-    const double entries = chunk_budget(E, bytes_per_entry, entries_per_step);
-    if (entries >= 1024.0) return 1024;
-    const int64_t c = ((int64_t)entries + kWave - 1) / kWave * kWave;
-    return (int)(c < kWave ? kWave : c);
-}
-
-// Chunks and front rows on large graphs (the graph-transformer forward, its
-// backward and the segment reduction; the GATv2 forward keeps the rule
-// above).  Where a chunk of an eighth of the gather time holds more than
-// 1024 entries, chunks take that length, up to 8192; and where a wave holds
-// two or more rows, only rows of at least a quarter chunk go first as front
-// rows, the others being medium rows of one wavefront each.  Measured per call
-// against 1024-entry chunks and a front threshold of 256: R-MAT scale 21 fp32
-// 4x32 6.528 -> 6.260 ms and bf16 3.103 -> 2.936 ms, the backward on the bf16
-// one 8.30 -> 7.97 ms, the 512-feature min on the fp32 one 14.45 -> 14.27 ms;
-// the arxiv-shaped power-law graph at 2.1M nodes about 1 % faster; the
-// lognormal-hub and SBM graphs level; graphs up to the 169K-node one keep
-// their chunks.  With one row per wave (lognormal hubs, 8x64 bf16) a front
-// threshold of 2048 cost 0.3-0.6 %, so those shapes keep 256.  (For the GATv2
-// score the same lengths made R-MAT bf16 1.5 % slower.)
-int default_chunk_long(int64_t E, int64_t bytes_per_entry, int entries_per_step) {
-    const double quarter = 0.25 * chunk_budget(E, bytes_per_entry, entries_per_step);
-    if (quarter <= 1024.0) return default_chunk(E, bytes_per_entry, entries_per_step);
-    if (quarter >= 8192.0) return 8192;
-    return (int)(((int64_t)quarter + kWave - 1) / kWave * kWave);
-}
-
-int default_front(int chunk, int rows_per_wave) {
-    return rows_per_wave >= 2 && chunk / 4 > 256 ? chunk / 4 : 256;
-}
-
 // The device a call works on: the calling thread's current device.  The
 // workspace, its events and the kernels' memory all belong to it, so a stream
 // created on another device is refused rather than fed memory it may not be
@@ -1865,31 +1481,35 @@ struct RowRule {
 };
 
 // Rows are cut into eight pieces from eight times the length at which a piece
-// saves what it costs.  It costs its partial state (slot_bytes, written and read
-// once) and about 256 bytes of row vector, list entry and index line; its
-// entries, of `gather_bytes` each, hit the L2 with a share `cover` more than in
+// saves what it costs: `piece_bytes` of its partial state (written and read once),
+// row vectors, list entry and index line.  Its entries, of `gather_bytes` each, hit the L2 with a share `cover` more than in
 // row order, the part of an XCD's eighth of the sources that its L2 holds
-// (uniform sources; skewed ones gain more, hence the 3/4).  At least four entries
-// per piece, and 32 per wavefront of `groups` pieces.  Longer rows get pieces of
-// 32 to 64 entries, twice that where the call's gathers take more than about
-// 400 us.  Measured (us per call) with rows cut from 8*4 / 8*8 / 8*16 entries:
-// fp32 4x32 power law of 16 K nodes 41.6 / 45.4 / 58.3, of 169 K nodes 212 / 211
-// / 218, R-MAT scale 21 4932 / 4730 / 4764; fp32 4x128 power law of 169 K nodes
-// 985 / 880 / 870; bf16 8x64 lognormal 10411 / 10409 / 9910.
-RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int slot_bytes, int groups, const gt_tuning* tu) {
+// (uniform sources).  At least eight entries per piece (four where that pays and
+// the sources nearly fit an L2), and 32 per wavefront of `groups` pieces.  Longer
+// rows get pieces of 32 to 64 entries, twice that where the call's gathers take
+// more than about 60 us, and up to 32 of them: beyond that a wavefront reads a
+// piece, since every piece has to be merged.
+// Measured (us per call).  Rows cut from 32 / 64 / 128 entries, with 128-byte
+// slices: fp32 4x32 power law of 16 K nodes 41.6 / 45.4 / 58.3, of 169 K nodes 212
+// / 211 / 218, R-MAT scale 21 4932 / 4730 / 4764; fp32 4x128 power law of 169 K
+// nodes 985 / 880 / 870; bf16 8x64 lognormal 10411 / 10409 / 9910.  At most 16 /
+// 32 / 64 / 256 pieces: power law of 16 K nodes 41.1 / 37.9 / 39.4 / 41.7, R-MAT
+// scale 21 4716 / 4683 / 4693 / 4793, backward of R-MAT scale 20 bf16 4x32 2720 /
+// 2735 / 2736 / 3023.
+RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_bytes, int groups, const gt_tuning* tu) {
     constexpr double kL2Bytes = 4.0 * 1024 * 1024, kGatherBytesPerSecond = 7.0e12;
     double cover = kXcds * kL2Bytes / ((double)N * gather_bytes);
     if (cover > 0.75) cover = 0.75;
-    const double pays = 0.75 * (2.0 * slot_bytes + 256.0) / (gather_bytes * cover);
-    uint32_t len = 32 / groups > 8 ? 32 / groups : (double)N * gather_bytes <= 2 * kL2Bytes ? 4 : 8;
+    const double pays = piece_bytes / (gather_bytes * cover);
+    uint32_t len = 32 / groups > 8 ? 32 / groups : pays < 4 && (double)N * gather_bytes <= 2 * kL2Bytes ? 4 : 8;
     while (len < 32 && 2 * len <= pays) len *= 2;
-    const bool large = (double)E * slices * gather_bytes / kGatherBytesPerSecond > 400e-6;
+    const bool large = (double)E * slices * gather_bytes / kGatherBytesPerSecond > 60e-6;
     RowRule r;
     r.light_max = (int32_t)(kXcds * len);
     r.split_min = kXcds * len;
     r.chunk = large ? 128 : 64;
     r.nq_floor = kXcds;
-    r.nq_max = 256;
+    r.nq_max = 32;
     r.group_len = r.chunk;
     r.forced = false;
     r.max_slots = E / (2 * len) + 1;
@@ -2026,23 +1646,33 @@ hipError_t pick_tiles(int H, const TileParams& tp, hipStream_t stream) {
     return hipErrorInvalidValue;
 }
 
-// Workspace that the allocation-free entry point asks for (its documented
-// limit): the row lists, and the partial states of rows cut into pieces of
-// `chunk` entries, for all heads at once.
+// What the allocation-free entry point counts as a call's workspace, for its
+// documented limit: the row lists, and the partial states of rows cut into chunks
+// (of `chunk` entries, by default half the steps that the call's gathers take at
+// 7 TB/s and a microsecond per step, up to 1024 entries, or an eighth of them up
+// to 8192) for all heads at once.  Calls within the limit get a workspace within
+// it; the others are refused.
 size_t noalloc_need(const Args& a, int elt_bytes, const gt_tuning* tu) {
     const int row = a.H * a.D * elt_bytes, vecs = row / 16, lanes = vecs < kWave ? vecs : kWave;
     const int rows = kWave / lanes, nv = vecs / lanes;
     int u = 8 / nv > 2 ? 8 / nv : 2;
     if (u > lanes) u = lanes;
-    const int light = tu && tu->light_max_deg > 0 ? tu->light_max_deg : 8 * u;
-    int chunk = default_chunk_long(a.E, 2 * row, rows * (rows >= 4 && u >= 8 ? u / 2 : u));
-    int heavy = default_front(chunk, rows);
+    const int64_t light = tu && tu->light_max_deg > 0 ? tu->light_max_deg : 8 * u;
+    const double steps = (double)a.E * (2.0 * row) / 7.0e12 / 1.0e-6;
+    const double entries = 0.5 * steps * (rows * (rows >= 4 && u >= 8 ? u / 2 : u));
+    auto whole = [](double x) { return ((int64_t)x + kWave - 1) / kWave * kWave; };
+    int64_t chunk = 0.25 * entries > 8192.0   ? 8192
+                    : 0.25 * entries > 1024.0 ? whole(0.25 * entries)
+                    : entries >= 1024.0       ? 1024
+                                              : whole(entries);
+    if (chunk < kWave) chunk = kWave;
+    int64_t heavy = rows >= 2 && chunk / 4 > 256 ? chunk / 4 : 256;
     if (tu && tu->heavy_min_deg > 0) heavy = tu->heavy_min_deg;
-    if (tu && tu->chunk_edges > 0) chunk = (tu->chunk_edges + kWave - 1) / kWave * kWave;
+    if (tu && tu->chunk_edges > 0) chunk = whole(tu->chunk_edges);
     if (heavy <= light) heavy = light + 1;
-    const PartCaps caps = part_caps(a.E, heavy, chunk);
-    return (size_t)a.N * sizeof(int32_t) * (rows >= 4 ? 2 : 1) + (size_t)caps.heavy * sizeof(HeavyRow) +
-           (size_t)caps.items * sizeof(ChunkItem) + (size_t)caps.slots * a.H * (sizeof(float2) + a.D * sizeof(float));
+    const size_t slots = 2 * (size_t)(a.E / chunk) + 1;
+    return (size_t)a.N * sizeof(int32_t) * (rows >= 4 ? 2 : 1) + 16 * ((size_t)(a.E / (chunk + 1)) + 1) +
+           24 * ((size_t)(a.E / heavy) + slots) + slots * a.H * (sizeof(float2) + a.D * sizeof(float));
 }
 
 template <typename T, int HS, int D, int KIND>
@@ -2051,7 +1681,8 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     constexpr int kRowSlice = HS * D * Elt<T>::kBytes;
     constexpr int kSlotBytes = HS * (int)(D * sizeof(float) + sizeof(float2));
     const int slices = a.H / HS;
-    RowRule rule = row_rule(a.N, a.E, slices, (KIND == KIND_GATV2 ? 1 : 2) * kRowSlice, kSlotBytes, Op::Gm::kP, tu);
+    RowRule rule = row_rule(a.N, a.E, slices, (KIND == KIND_GATV2 ? 1 : 2) * kRowSlice,
+                            3 * (2 * kSlotBytes + 256) / 4, Op::Gm::kP, tu);
     // Dense-tile windows (bf16 rows of at most 256 bytes): on by default, for
     // windows estimated to hold at least 256 in-window entries, which a 64-row
     // block at half density holds about eight times over (measured on the SBM

@@ -1,6 +1,6 @@
 // Backward pass of the fused graph-transformer attention (included by
-// gt_attn.hip inside its anonymous namespace; uses its device helpers, the
-// degree partition kernel and the call workspace).
+// gt_attn.hip inside its anonymous namespace; uses its device helpers, the row
+// work order of gt_rows.hpp and the call workspace).
 //
 // Gradients for an upstream gradient dO (paper, Appendix D.2, backward pass of
 // the graph transformer: the weights are recomputed from the stored per-row
@@ -21,30 +21,31 @@
 //     pass 1: a = K_j, b = V_j, x = Q_i, y = dO_i, (L, Delta) gathered at i
 //     s = <a, x> scale, alpha = exp(s - L), ds = alpha (<b, y> - Delta)
 //     acc1 += ds x;  pass 1 also: acc2 += alpha y
+// Pass 0 leaves (L log2(e), Delta) of each row and head as one pair, so that an
+// entry of pass 1 reads one line for both.  Like the forward, the passes gather
+// two random rows per entry and are bound by the path from L2 to the fabric;
+// us per call with whole rows in row order, and with slices and source ranges:
+// R-MAT scale 20 bf16 4x32 3760 -> 2735, 300 K nodes fp32 4x32 1544 -> 1271;
+// lognormal 200 K nodes bf16 8x64 3753 -> 3683; power law fp32 4x32 of 169 K nodes
+// 478 -> 443, of 16 K nodes 74 -> 72.
 
 struct BwdParams {
-    const int64_t* rowptr;  // rows of this pass (CSR or transposed CSR)
-    const int32_t* colidx;
+    RowWork w;      // rows of this pass (CSR or transposed CSR)
     const char* A;  // row-own vectors a / b
     const char* B;
     const char* X;  // gathered vectors x / y
     const char* Y;
     const char* O;     // pass 0: forward output (for Delta)
     const float* lse;  // [N][H] natural log
-    float* delta;      // [N][H]: written by pass 0, read by pass 1
+    float2* stat;      // [N][H] (lse log2(e), Delta): written by pass 0, read by pass 1
     char* out1;        // dQ (pass 0) or dK (pass 1)
     char* out2;        // dV (pass 1)
-    int64_t N;
     float c;      // scale * log2(e)
     float scale;
-    int32_t light_max;
-    int32_t cap_items;
-    int32_t cap_heavy;
-    const int32_t* counters;
-    const int32_t* med_list;
-    const ChunkItem* chunks;
-    const HeavyRow* heavy;
-    float* part;  // [slot][NACC * H * D]
+    int32_t row_shift;
+    int32_t heads;
+    int32_t slice0;  // slice of blockIdx.y == 0
+    float* part;  // [slice of this launch][slot][NACC * HS * D]
 };
 
 // bf16 dot over the four pairs of two 16-byte vectors, accumulated in fp32
@@ -55,322 +56,273 @@ __device__ __forceinline__ float dot8_bf16(const uint4& a, const uint4& b) {
     return dot2_bf16(a.w, b.w, d);
 }
 
-template <typename T, int H, int D, int MODE>
-struct BwdState {
-    using Gm = Geo<T, H, D>;
-    static constexpr int NV = Gm::kNV, EPV = Gm::kEPV, U = Gm::kU;
+template <typename T, int HS, int D, int MODE>
+struct BwdState;
+
+template <typename T, int HS, int D, int MODE>
+struct BwdOp {
+    using Gm = Geo<T, HS, D>;
+    using State = BwdState<T, HS, D, MODE>;
+    static constexpr int kG = Gm::kG;
+    static constexpr int kU = Gm::kP >= 4 && Gm::kU >= 8 ? Gm::kU / 2 : Gm::kU;
+    static constexpr bool kSorted = Gm::kP >= 4;
     static constexpr int NACC = MODE ? 2 : 1;
+    static constexpr int kSlotFloats = NACC * HS * D;
+    const char* A;
+    const char* B;
+    const char* X;
+    const char* Y;
+    const char* O;
+    const float* lse;  // at the slice's first head
+    float2* stat;
+    char* out1;
+    char* out2;
+    float* part;
+    float c, scale;
+    int row_shift, heads;
+
+    __device__ __forceinline__ uint64_t offset(int32_t row, int lig) const {
+        return ((uint64_t)(uint32_t)row << row_shift) + (uint32_t)lig * 16u;
+    }
+};
+
+template <typename T, int HS, int D, int MODE>
+__device__ __forceinline__ BwdOp<T, HS, D, MODE> bwd_op(const BwdParams& p) {
+    using Op = BwdOp<T, HS, D, MODE>;
+    const int head = (p.slice0 + (int)blockIdx.y) * HS;
+    const int64_t at = (int64_t)head * D * Elt<T>::kBytes;
+    Op op;
+    op.A = p.A + at;
+    op.B = p.B + at;
+    op.X = p.X + at;
+    op.Y = p.Y + at;
+    op.O = p.O + at;
+    op.lse = p.lse + head;
+    op.stat = p.stat + head;
+    op.out1 = p.out1 + at;
+    op.out2 = p.out2 + at;
+    op.part = p.part + (int64_t)blockIdx.y * p.w.cap_slots * Op::kSlotFloats;
+    op.c = p.c;
+    op.scale = p.scale;
+    op.row_shift = p.row_shift;
+    op.heads = p.heads;
+    return op;
+}
+
+template <typename T, int HS, int D, int MODE>
+struct BwdState {
+    using Op = BwdOp<T, HS, D, MODE>;
+    using Gm = Geo<T, HS, D>;
+    static constexpr int EPV = Gm::kEPV, kU = Op::kU;
     // bf16 features: the two dots per entry are bf16 dot2 on raw pairs, and
     // the accumulations pair two entries: their coefficients (ds, alpha) are
     // rounded to one bf16 pair and dot2 multiplies it with the two entries'
     // elements, accumulating in fp32.
     static constexpr bool kDot2 = std::is_same<T, bf16_tag>::value;
-    static_assert(!kDot2 || U % 2 == 0, "dot2 pairs entries");
-    float a[kDot2 ? 1 : NV][EPV], b[kDot2 ? 1 : NV][EPV];
-    uint4 araw[kDot2 ? NV : 1], braw[kDot2 ? NV : 1];
-    float acc1[NV][EPV], acc2[NV][EPV];
-    float L2[NV], Dl[NV];  // pass 0: the row's statistics (per vector slot's head)
+    static_assert(!kDot2 || kU % 2 == 0, "dot2 pairs entries");
+    uint4 a, b;  // the row's own vectors
+    float acc1[EPV], acc2[EPV];
+    float L2, Dl;  // pass 0: the row's statistics (of this lane's head)
 
-    __device__ __forceinline__ void begin(const BwdParams& p, int64_t row, int lig) {
-        const int64_t off = row * (int64_t)Gm::kRowBytes + lig * 16;
+    __device__ __forceinline__ void reset() {
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const uint4 ar = *reinterpret_cast<const uint4*>(p.A + off + k * Gm::kG * 16);
-            const uint4 br = *reinterpret_cast<const uint4*>(p.B + off + k * Gm::kG * 16);
-            if constexpr (kDot2) {
-                araw[k] = ar;
-                braw[k] = br;
-            } else {
-                widen<T>(ar, a[k]);
-                widen<T>(br, b[k]);
-            }
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) acc1[k][e] = acc2[k][e] = 0.0f;
-        }
+        for (int e = 0; e < EPV; ++e) acc1[e] = acc2[e] = 0.0f;
+    }
+
+    __device__ __forceinline__ void begin(const Op& op, int32_t row, int lig) {
+        const uint64_t off = op.offset(row, lig);
+        a = load_once(op.A + off);
+        b = load_once(op.B + off);
         if constexpr (MODE == 0) {
+            const uint4 o = load_once(op.O + off);
+            const int64_t at = (int64_t)row * op.heads + lig / Gm::kHL;
+            L2 = op.lse[at] * 1.4426950408889634f;
+            float d = 0.0f;
+            if constexpr (kDot2) {
+                d = dot8_bf16(o, b);
+            } else {
+                float of[EPV], bf[EPV];
+                widen<T>(o, of);
+                widen<T>(b, bf);
 #pragma unroll
-            for (int k = 0; k < NV; ++k) {
-                const int v = lig + k * Gm::kG, h = v / Gm::kHL;
-                const uint4 orw = *reinterpret_cast<const uint4*>(p.O + off + k * Gm::kG * 16);
-                float d = 0.0f;
-                if constexpr (kDot2) {
-                    d = dot8_bf16(orw, braw[k]);
-                } else {
-                    float o[EPV];
-                    widen<T>(orw, o);
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) d = fmaf(o[e], b[k][e], d);
-                }
-                Dl[k] = head_sum<Gm::kHL>(d);
-                L2[k] = p.lse[row * H + h] * 1.4426950408889634f;
-                if (v % Gm::kHL == 0) p.delta[row * H + h] = Dl[k];
+                for (int e = 0; e < EPV; ++e) d = fmaf(of[e], bf[e], d);
             }
+            Dl = head_sum<Gm::kHL>(d);
+            // (the pieces of a cut row all write the same pair)
+            if (lig % Gm::kHL == 0) op.stat[at] = make_float2(L2, Dl);
         }
     }
 
-    __device__ __forceinline__ void step(const BwdParams& p, const int32_t (&j)[U], int nvalid, int lig) {
+    struct Batch {
+        uint4 x[kU], y[kU];
+        float2 st[MODE ? kU : 1];
+    };
+
+    __device__ __forceinline__ void issue(const Op& op, const int32_t (&j)[kU], int lig, Batch& bt) const {
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint64_t off = op.offset(j[u], lig);
+            bt.x[u] = *reinterpret_cast<const uint4*>(op.X + off);
+            bt.y[u] = *reinterpret_cast<const uint4*>(op.Y + off);
+            if constexpr (MODE == 1) bt.st[u] = op.stat[(int64_t)j[u] * op.heads + lig / Gm::kHL];
+        }
+    }
+
+    __device__ __forceinline__ void consume(const Op& op, const Batch& bt, const int32_t (&)[kU], int nvalid) {
 #pragma clang fp contract(off)
-        uint4 xr[U][NV], yr[U][NV];
-        float lg[U][NV], dg[U][NV];
+        float al[kU], ds[kU];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t off = (int64_t)j[u] * Gm::kRowBytes + lig * 16;
+        for (int u = 0; u < kU; ++u) {
+            float s = 0.0f, da = 0.0f;
+            if constexpr (kDot2) {
+                s = dot8_bf16(a, bt.x[u]);
+                da = dot8_bf16(b, bt.y[u]);
+            } else {
+                float af[EPV], bf[EPV], x[EPV], y[EPV];
+                widen<T>(a, af);
+                widen<T>(b, bf);
+                widen<T>(bt.x[u], x);
+                widen<T>(bt.y[u], y);
 #pragma unroll
-            for (int k = 0; k < NV; ++k) {
-                xr[u][k] = *reinterpret_cast<const uint4*>(p.X + off + k * Gm::kG * 16);
-                yr[u][k] = *reinterpret_cast<const uint4*>(p.Y + off + k * Gm::kG * 16);
-                if constexpr (MODE == 1) {
-                    const int h = (lig + k * Gm::kG) / Gm::kHL;
-                    lg[u][k] = p.lse[(int64_t)j[u] * H + h];
-                    dg[u][k] = p.delta[(int64_t)j[u] * H + h];
+                for (int e = 0; e < EPV; ++e) {
+                    s = fmaf(af[e], x[e], s);
+                    da = fmaf(bf[e], y[e], da);
                 }
             }
+            s = head_sum<Gm::kHL>(s) * op.c;
+            da = head_sum<Gm::kHL>(da);
+            const float l2 = MODE == 1 ? bt.st[MODE ? u : 0].x : L2;
+            const float dl = MODE == 1 ? bt.st[MODE ? u : 0].y : Dl;
+            al[u] = (u < nvalid) ? fast_exp2(s - l2) : 0.0f;
+            ds[u] = al[u] * (da - dl);
         }
         if constexpr (kDot2) {
 #pragma unroll
-            for (int u = 0; u < U; u += 2) {
+            for (int u = 0; u < kU; u += 2) {
+                const uint32_t pds = pack_bf16(ds[u], ds[u + 1]);
+                const uint32_t pal = pack_bf16(al[u], al[u + 1]);
+                const uint4 x0 = bt.x[u], x1 = bt.x[u + 1], y0 = bt.y[u], y1 = bt.y[u + 1];
+                const uint32_t xa[4] = {x0.x, x0.y, x0.z, x0.w}, xb[4] = {x1.x, x1.y, x1.z, x1.w};
+                const uint32_t ya[4] = {y0.x, y0.y, y0.z, y0.w}, yb[4] = {y1.x, y1.y, y1.z, y1.w};
 #pragma unroll
-                for (int k = 0; k < NV; ++k) {
-                    float al[2], ds[2];
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        const float sc = head_sum<Gm::kHL>(dot8_bf16(araw[k], xr[u + t][k])) * p.c;
-                        const float dd = head_sum<Gm::kHL>(dot8_bf16(braw[k], yr[u + t][k]));
-                        const float l2 = MODE == 1 ? lg[u + t][k] * 1.4426950408889634f : L2[k];
-                        const float dl = MODE == 1 ? dg[u + t][k] : Dl[k];
-                        al[t] = (u + t < nvalid) ? fast_exp2(sc - l2) : 0.0f;
-                        ds[t] = al[t] * (dd - dl);
-                    }
-                    const uint32_t pds = pack_bf16(ds[0], ds[1]);
-                    const uint32_t pal = pack_bf16(al[0], al[1]);
-                    const uint4 x0 = xr[u][k], x1 = xr[u + 1][k], y0 = yr[u][k], y1 = yr[u + 1][k];
-                    const uint32_t xa[4] = {x0.x, x0.y, x0.z, x0.w}, xb[4] = {x1.x, x1.y, x1.z, x1.w};
-                    const uint32_t ya[4] = {y0.x, y0.y, y0.z, y0.w}, yb[4] = {y1.x, y1.y, y1.z, y1.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        acc1[k][2 * q] = dot2_bf16(pds, pair_lo(xa[q], xb[q]), acc1[k][2 * q]);
-                        acc1[k][2 * q + 1] = dot2_bf16(pds, pair_hi(xa[q], xb[q]), acc1[k][2 * q + 1]);
-                        if constexpr (MODE == 1) {
-                            acc2[k][2 * q] = dot2_bf16(pal, pair_lo(ya[q], yb[q]), acc2[k][2 * q]);
-                            acc2[k][2 * q + 1] = dot2_bf16(pal, pair_hi(ya[q], yb[q]), acc2[k][2 * q + 1]);
-                        }
+                for (int q = 0; q < 4; ++q) {
+                    acc1[2 * q] = dot2_bf16(pds, pair_lo(xa[q], xb[q]), acc1[2 * q]);
+                    acc1[2 * q + 1] = dot2_bf16(pds, pair_hi(xa[q], xb[q]), acc1[2 * q + 1]);
+                    if constexpr (MODE == 1) {
+                        acc2[2 * q] = dot2_bf16(pal, pair_lo(ya[q], yb[q]), acc2[2 * q]);
+                        acc2[2 * q + 1] = dot2_bf16(pal, pair_hi(ya[q], yb[q]), acc2[2 * q + 1]);
                     }
                 }
             }
-            return;
-        }
+        } else {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int k = 0; k < NV; ++k) {
+            for (int u = 0; u < kU; ++u) {
                 float x[EPV], y[EPV];
-                widen<T>(xr[u][k], x);
-                widen<T>(yr[u][k], y);
-                float s = 0.0f, da = 0.0f;
+                widen<T>(bt.x[u], x);
+                widen<T>(bt.y[u], y);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) {
-                    s = fmaf(a[k][e], x[e], s);
-                    da = fmaf(b[k][e], y[e], da);
-                }
-                s = head_sum<Gm::kHL>(s) * p.c;
-                da = head_sum<Gm::kHL>(da);
-                const float l2 = MODE == 1 ? lg[u][k] * 1.4426950408889634f : L2[k];
-                const float dl = MODE == 1 ? dg[u][k] : Dl[k];
-                const float alpha = (u < nvalid) ? fast_exp2(s - l2) : 0.0f;
-                const float ds = alpha * (da - dl);
-#pragma unroll
-                for (int e = 0; e < EPV; ++e) {
-                    acc1[k][e] = fmaf(ds, x[e], acc1[k][e]);
-                    if constexpr (MODE == 1) acc2[k][e] = fmaf(alpha, y[e], acc2[k][e]);
+                    acc1[e] = fmaf(ds[u], x[e], acc1[e]);
+                    if constexpr (MODE == 1) acc2[e] = fmaf(al[u], y[e], acc2[e]);
                 }
             }
         }
     }
 
-    __device__ __forceinline__ void sum_xor(int off) {
+    __device__ __forceinline__ void merge_xor(int off) {
 #pragma unroll
-        for (int k = 0; k < NV; ++k)
-#pragma unroll
-            for (int e = 0; e < EPV; ++e) {
-                acc1[k][e] += __shfl_xor(acc1[k][e], off);
-                if constexpr (MODE == 1) acc2[k][e] += __shfl_xor(acc2[k][e], off);
-            }
+        for (int e = 0; e < EPV; ++e) {
+            acc1[e] += __shfl_xor(acc1[e], off);
+            if constexpr (MODE == 1) acc2[e] += __shfl_xor(acc2[e], off);
+        }
     }
 
-    __device__ __forceinline__ void store(const BwdParams& p, int64_t row, int lig) const {
-        const int64_t off = row * (int64_t)Gm::kRowBytes + lig * 16;
+    __device__ __forceinline__ void store_out(const Op& op, int32_t row, int lig) const {
+        const uint64_t off = op.offset(row, lig);
+        float o[EPV];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            float o[EPV];
+        for (int e = 0; e < EPV; ++e) o[e] = acc1[e] * op.scale;
+        store_once(op.out1 + off, narrow<T>(o));
+        if constexpr (MODE == 1) store_once(op.out2 + off, narrow<T>(acc2));
+    }
+
+    __device__ __forceinline__ void store_partial(const Op& op, int32_t slot, int lig) const {
+        float* dst = op.part + (int64_t)slot * Op::kSlotFloats + lig * EPV;
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) o[e] = acc1[k][e] * p.scale;
-            *reinterpret_cast<uint4*>(p.out1 + off + k * Gm::kG * 16) = narrow<T>(o);
+        for (int e = 0; e < EPV; e += 4) {
+            *reinterpret_cast<float4*>(dst + e) = make_float4(acc1[e], acc1[e + 1], acc1[e + 2], acc1[e + 3]);
             if constexpr (MODE == 1)
-                *reinterpret_cast<uint4*>(p.out2 + off + k * Gm::kG * 16) = narrow<T>(acc2[k]);
+                *reinterpret_cast<float4*>(dst + HS * D + e) = make_float4(acc2[e], acc2[e + 1], acc2[e + 2], acc2[e + 3]);
         }
     }
 
-    __device__ __forceinline__ void store_partial(const BwdParams& p, int32_t slot, int lig) const {
+    struct Partial {
+        float a1[EPV], a2[MODE ? EPV : 1];
+    };
+
+    __device__ __forceinline__ static void load_partial(const Op& op, int32_t slot, int lig, Partial& pt) {
+        const float* src = op.part + (int64_t)slot * Op::kSlotFloats + lig * EPV;
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const int v = lig + k * Gm::kG;
-            float* dst = p.part + (int64_t)slot * NACC * Gm::kHD + v * EPV;
+        for (int e = 0; e < EPV; ++e) {
+            pt.a1[e] = src[e];
+            if constexpr (MODE == 1) pt.a2[e] = src[HS * D + e];
+        }
+    }
+
+    __device__ __forceinline__ void add(const Partial& pt, bool valid) {
 #pragma unroll
-            for (int e = 0; e < EPV; e += 4) {
-                *reinterpret_cast<float4*>(dst + e) = make_float4(acc1[k][e], acc1[k][e + 1], acc1[k][e + 2], acc1[k][e + 3]);
-                if constexpr (MODE == 1)
-                    *reinterpret_cast<float4*>(dst + Gm::kHD + e) =
-                        make_float4(acc2[k][e], acc2[k][e + 1], acc2[k][e + 2], acc2[k][e + 3]);
+        for (int e = 0; e < EPV; ++e) {
+            const float t1 = acc1[e] + pt.a1[e];
+            acc1[e] = valid ? t1 : acc1[e];
+            if constexpr (MODE == 1) {
+                const float t2 = acc2[e] + pt.a2[e];
+                acc2[e] = valid ? t2 : acc2[e];
             }
         }
     }
 };
 
-template <typename T, int H, int D, int MODE>
-__device__ __forceinline__ void bwd_wave_segment(const BwdParams& p, int64_t row, int64_t b, int64_t e, int32_t slot,
-                                                 int32_t* __restrict__ tile, int lane) {
-    using Gm = Geo<T, H, D>;
-    constexpr int U = Gm::kU, P = Gm::kP, G = Gm::kG;
-    const int g = lane / G, lig = lane % G;
-    BwdState<T, H, D, MODE> st;
-    st.begin(p, row, lig);
-    for (int64_t tb = b; tb < e; tb += kWave) {
-        const int64_t pos = (tb + lane < e) ? tb + lane : e - 1;
-        const int32_t idx = p.colidx[pos];
-        wave_lds_fence();
-        tile[lane] = idx;
-        wave_lds_fence();
-        const int nt = (int)((e - tb) < kWave ? (e - tb) : kWave);
-        for (int t = 0; t < nt; t += P * U) {
-            const int e0 = t + g * U;
-            const int nvalid = nt - e0 < U ? nt - e0 : U;
-            if (nvalid > 0) {
-                int32_t j[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) j[u] = tile[e0 + u];
-                st.step(p, j, nvalid, lig);
-            }
-        }
-    }
-#pragma unroll
-    for (int off = G; off < kWave; off <<= 1) st.sum_xor(off);
-    if (g == 0) {
-        if (slot < 0)
-            st.store(p, row, lig);
-        else
-            st.store_partial(p, slot, lig);
-    }
-}
-
-template <typename T, int H, int D, int MODE>
+template <typename T, int HS, int D, int MODE>
 __global__ void __launch_bounds__(kBlock) gt_bwd_kernel(BwdParams p) {
-    using Gm = Geo<T, H, D>;
-    constexpr int U = Gm::kU, G = Gm::kG;
-    __shared__ int32_t tiles[kWavesPerBlock][kWave];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x / kWave;
-    int32_t* tile = tiles[wv];
-    const int32_t n_chunks = min(CNT(p.counters, CNT_CHUNKS), p.cap_items);
-    const int32_t n_items = n_chunks + (int32_t)min((int64_t)CNT(p.counters, CNT_MED), p.N);
-    const int nwaves = gridDim.x * kWavesPerBlock;
-    for (int it = blockIdx.x * kWavesPerBlock + wv; it < n_items; it += nwaves) {
-        if (it < n_chunks) {
-            const ChunkItem ci = p.chunks[it];
-            bwd_wave_segment<T, H, D, MODE>(p, ci.row, ci.begin, ci.end, ci.slot, tile, lane);
-        } else {
-            const int64_t row = p.med_list[it - n_chunks];
-            bwd_wave_segment<T, H, D, MODE>(p, row, p.rowptr[row], p.rowptr[row + 1], -1, tile, lane);
-        }
-    }
-    // light rows: one lane group each, P rows per wave
-    const int g = lane / G, lig = lane % G;
-    int32_t* gtile = tile + g * G;
-    const int64_t n_light = (p.N + Gm::kP - 1) / Gm::kP;
-    for (int64_t it = (int64_t)blockIdx.x * kWavesPerBlock + wv; it < n_light; it += nwaves) {
-        const int64_t row = it * Gm::kP + g;
-        if (row >= p.N) continue;
-        const int64_t b = p.rowptr[row], e = p.rowptr[row + 1];
-        if (e - b > p.light_max) continue;
-        BwdState<T, H, D, MODE> st;
-        st.begin(p, row, lig);
-        for (int64_t tb = b; tb < e; tb += G) {
-            const int32_t idx = p.colidx[(tb + lig < e) ? tb + lig : e - 1];
-            wave_lds_fence();
-            gtile[lig] = idx;
-            wave_lds_fence();
-            const int nt = (int)((e - tb) < G ? (e - tb) : G);
-            for (int t = 0; t < nt; t += U) {
-                const int nvalid = nt - t < U ? nt - t : U;
-                int32_t j[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) j[u] = gtile[t + u];
-                st.step(p, j, nvalid, lig);
-            }
-        }
-        st.store(p, row, lig);
-    }
+    using Op = BwdOp<T, HS, D, MODE>;
+    __shared__ __attribute__((aligned(16))) int32_t tiles[kWavesPerBlock][kWave / Op::kG * TileOf<Op::kG>::kEntries];
+    row_loop(p.w, bwd_op<T, HS, D, MODE>(p), tiles[threadIdx.x / kWave]);
 }
 
-// Chunk partials in flight per lane
-constexpr int kMergeBatch = 8;
-
-// Ordered sum of the chunk partials of each split row, then scaling / storing.
-template <typename T, int H, int D, int MODE>
+// Sum of the partial states of each cut row in a fixed order (lane group g adds
+// pieces g, g + P, ..., then the groups are summed across lanes), then scaling
+// and storing: one wavefront per row and slice.
+template <typename T, int HS, int D, int MODE>
 __global__ void __launch_bounds__(kBlock) gt_bwd_merge_kernel(BwdParams p) {
-    constexpr int HD = H * D;
-    constexpr int NACC = MODE ? 2 : 1;
-    constexpr int F = HD >= kWave ? HD / kWave : 1;
-    constexpr int EB = Elt<T>::kBytes;
+    using Op = BwdOp<T, HS, D, MODE>;
+    constexpr uint32_t G = Op::kG, P = kWave / G;
     const int lane = threadIdx.x & (kWave - 1);
-    const int f0 = lane * F;
-    const int32_t n_heavy = min(CNT(p.counters, CNT_HEAVY), p.cap_heavy);
-    const int nwaves = gridDim.x * kWavesPerBlock;
-    for (int hr = blockIdx.x * kWavesPerBlock + threadIdx.x / kWave; hr < n_heavy; hr += nwaves) {
-        if (f0 >= HD) continue;
-        const HeavyRow w = p.heavy[hr];
-        float s1[F], s2[F];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t g = lane / G;
+    const int lig = lane % G;
+    if (ROWS_CNT(p.w.counters, ROWS_PIECES) == 0) return;  // no long rows
+    const CutRows cut(p.w, lane);
+    const uint32_t n = cut.count(), waves = gridDim.x * kWavesPerBlock;
+    const Op op = bwd_op<T, HS, D, MODE>(p);
+    for (uint32_t i = blockIdx.x * kWavesPerBlock + wv; i < n; i += waves) {
+        uint32_t slot, nq;
+        const int32_t row = cut.row(p.w, i, lane, slot, nq);
+        typename Op::State st;
+        st.reset();
+        for (uint32_t q0 = 0; q0 < nq; q0 += P * kMergePieces) {
+            // (a group without a piece reads the row's last and leaves it out)
+            typename Op::State::Partial pt[kMergePieces];
 #pragma unroll
-        for (int f = 0; f < F; ++f) s1[f] = s2[f] = 0.0f;
-        // a batch holds at most 64 partial floats per lane
-        constexpr int kPer = (MODE ? 2 : 1) * F;
-        constexpr int kB = 64 / kPer < kMergeBatch ? (64 / kPer > 1 ? 64 / kPer : 1) : kMergeBatch;
-        for (int c0 = 0; c0 < w.nch; c0 += kB) {
-            float a1[kB][F], a2[kB][F];
-#pragma unroll
-            for (int u = 0; u < kB; ++u) {
-                const int64_t slot = w.base + (c0 + u < w.nch ? c0 + u : w.nch - 1);
-                const float* src = p.part + slot * NACC * HD + f0;
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    a1[u][f] = src[f];
-                    a2[u][f] = MODE ? src[HD + f] : 0.0f;
-                }
+            for (uint32_t u = 0; u < kMergePieces; ++u) {
+                const uint32_t q = q0 + u * P + g;
+                st.load_partial(op, (int32_t)(slot + (q < nq ? q : nq - 1)), lig, pt[u]);
             }
-            // chunks past the row's last add nothing (selects, not a loop exit,
-            // so that the batch's loads stay ahead of their use)
 #pragma unroll
-            for (int u = 0; u < kB; ++u) {
-                const bool valid = c0 + u < w.nch;
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    const float t1 = s1[f] + a1[u][f], t2 = s2[f] + a2[u][f];
-                    s1[f] = valid ? t1 : s1[f];
-                    s2[f] = valid ? t2 : s2[f];
-                }
-            }
+            for (uint32_t u = 0; u < kMergePieces; ++u) st.add(pt[u], q0 + u * P + g < nq);
         }
-        const int64_t base = (int64_t)w.row * HD + f0;
 #pragma unroll
-        for (int f = 0; f < F; ++f) {
-            const float o1 = s1[f] * p.scale;
-            if constexpr (EB == 4) {
-                reinterpret_cast<float*>(p.out1)[base + f] = o1;
-                if (MODE) reinterpret_cast<float*>(p.out2)[base + f] = s2[f];
-            } else {
-                reinterpret_cast<uint16_t*>(p.out1)[base + f] = (uint16_t)bf16_rne(o1);
-                if (MODE) reinterpret_cast<uint16_t*>(p.out2)[base + f] = (uint16_t)bf16_rne(s2[f]);
-            }
-        }
+        for (int off = G; off < kWave; off <<= 1) st.merge_xor(off);
+        if (g == 0) st.store_out(op, row, lig);
     }
 }
 
@@ -393,115 +345,133 @@ struct BwdArgs {
     float scale;
 };
 
-template <typename T, int H, int D>
+template <typename T, int HS, int D, int MODE>
+int bwd_resident(int dev) {
+    static std::atomic<int> cache[64];
+    if (dev < 0 || dev >= 64) return 4 * 256;
+    if (cache[dev] == 0) {
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gt_bwd_kernel<T, HS, D, MODE>, kBlock, 0) != hipSuccess ||
+            nb <= 0)
+            nb = 4;
+        cache[dev] = nb * device_cus(dev);
+    }
+    return cache[dev];
+}
+
+// One pass: the partition of its structure, then slice by slice its row kernel
+// and the merge of the cut rows.
+template <typename T, int HS, int D, int MODE>
+gt_status launch_bwd_pass(BwdParams bp, const RowRule& rule, const SlotPlan& sp, int dev, hipStream_t stream) {
+    using Op = BwdOp<T, HS, D, MODE>;
+    hipError_t he = hipSuccess;
+    const RowGrid rg = row_grid(bp.w.N, bp.w.E, Op::Gm::kP, false, bwd_resident<T, HS, D, MODE>(dev), nullptr);
+    bp.w.long_blocks = rg.long_blocks;
+    SortParams pp;
+    pp.w = bp.w;
+    pp.step = Op::kU;
+    pp.groups = Op::Gm::kP;
+    if ((he = launch_sort_rows(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
+    const int merge_grid = merge_blocks(sp, rule, device_cus(dev));
+    for (int s = 0; s < bp.heads / HS; s += sp.slices) {
+        bp.slice0 = s;
+        hipLaunchKernelGGL((gt_bwd_kernel<T, HS, D, MODE>), dim3(rg.blocks, sp.slices), dim3(kBlock), 0, stream, bp);
+        if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "backward launch");
+        hipLaunchKernelGGL((gt_bwd_merge_kernel<T, HS, D, MODE>), dim3(merge_grid, sp.slices), dim3(kBlock), 0, stream, bp);
+        if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "backward merge launch");
+    }
+    return GT_SUCCESS;
+}
+
+template <typename T, int HS, int D>
 gt_status launch_bwd(const BwdArgs& a, hipStream_t stream) {
-    using Gm = Geo<T, H, D>;
-    const int light_max = 8 * Gm::kU;
-    const int chunk = default_chunk_long(a.E, 2 * Gm::kRowBytes, Gm::kP * Gm::kU);  // both passes gather two rows
-    const int heavy_min = default_front(chunk, Gm::kP);
+    using Op = BwdOp<T, HS, D, 1>;
+    constexpr int kSlotBytes = Op::kSlotFloats * (int)sizeof(float);  // (pass 0: half of it)
+    const int slices = a.H / HS;
+    const RowRule rule = row_rule(a.N, a.E, slices, 2 * HS * D * Elt<T>::kBytes, 2 * kSlotBytes + 1024, Op::Gm::kP,
+                                  nullptr);
     int dev = 0;
     if (const gt_status ds = call_device(stream, &dev); ds != GT_SUCCESS) return ds;
     hipError_t he = hipSuccess;
-    const int64_t resident = (int64_t)device_cus(dev) * 4;
-    const int64_t light_items = (a.N + Gm::kP - 1) / Gm::kP;
-    int64_t g = light_items / (2 * kWavesPerBlock);
-    if (g < 4 * resident) g = 4 * resident;
-    if (g > 64 * resident) g = 64 * resident;
-    const int64_t need = (light_items + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (g > need) g = need;
-    const int grid = (int)(g > 0 ? g : 1);
 
-    const PartCaps caps = part_caps(a.E, heavy_min, chunk);
+    // workspace: a counter set per pass | statistics | light rows | long rows | partial states
+    RowWork w;
+    w.N = a.N;
+    w.E = (uint32_t)a.E;
+    set_rule(w, rule);
     size_t off = 0;
-    const size_t o_cnt = off;    off = align_up(off + 2 * kCntSetWords * sizeof(int32_t), 256);
-    const size_t o_med = off;    off = align_up(off + (size_t)a.N * sizeof(int32_t), 256);
-    const size_t o_heavy = off;  off = align_up(off + (size_t)caps.heavy * sizeof(HeavyRow), 256);
-    const size_t o_chunks = off; off = align_up(off + (size_t)caps.items * sizeof(ChunkItem), 256);
-    const size_t o_part = off;   off = align_up(off + (size_t)caps.slots * 2 * H * D * sizeof(float), 256);
-    const size_t o_delta = off;  off = align_up(off + (size_t)a.N * H * sizeof(float), 256);
-    const size_t ws_bytes = off;
+    const size_t o_cnt = off;    off = align_up(off + 2 * kRowsSetWords * sizeof(int32_t), 256);
+    const size_t o_stat = off;   off = align_up(off + (size_t)a.N * a.H * sizeof(float2), 256);
+    const size_t o_light = off;  off = align_up(off + (Op::kSorted ? (size_t)a.N * sizeof(LightRow) : 0), 256);
+    const size_t o_deg = off;    off = align_up(off + (Op::kSorted ? (size_t)a.N : 0), 256);
+    const size_t o_long = off;
+    off = align_up(off + (size_t)long_list_rows(a.N, a.E, w.light_max) * sizeof(LongRow), 256);
+    const SlotPlan sp = slot_plan(rule, slices, kSlotBytes, off, false);
+    w.cap_slots = sp.cap;
+    const size_t o_part = off;   off = align_up(off + (size_t)sp.cap * sp.slices * kSlotBytes, 256);
 
     CallWorkspace cw;
-    gt_status st = acquire_workspace(dev, ws_bytes, stream, cw);
+    gt_status st = acquire_workspace(dev, off, stream, cw);
     if (st != GT_SUCCESS) return st;
     char* ws = cw.ptr;
-    int32_t* cnt_sets = reinterpret_cast<int32_t*>(ws + o_cnt);  // one counter set per pass
-    if ((he = clear_counters(cnt_sets, 2 * kCntSetWords, stream)) != hipSuccess) return hip_fail(he, "counter clear");
+    int32_t* cnt_sets = reinterpret_cast<int32_t*>(ws + o_cnt);
+    if ((he = clear_counters(cnt_sets, 2 * kRowsSetWords, stream)) != hipSuccess) return hip_fail(he, "counter clear");
+    w.light_list = Op::kSorted ? reinterpret_cast<LightRow*>(ws + o_light) : nullptr;
+    w.light_deg = reinterpret_cast<uint8_t*>(ws + o_deg);
+    w.long_list = reinterpret_cast<LongRow*>(ws + o_long);
+    w.long_blocks = 0;
+    w.maybe_no_light = false;
 
     for (int mode = 0; mode < 2; ++mode) {
-        int32_t* counters = cnt_sets + mode * kCntSetWords;
-        const int64_t* rp = mode == 0 ? a.rowptr : a.rowptr_t;
-        const int32_t* ci = mode == 0 ? a.colidx : a.colidx_t;
-
-        PartParams pp;
-        pp.rowptr = rp;
-        pp.N = a.N;
-        pp.light_max = light_max;
-        pp.heavy_min = heavy_min;
-        pp.chunk = chunk;
-        pp.cap_heavy = (int32_t)caps.heavy;
-        pp.cap_items = (int32_t)caps.items;
-        pp.cap_slots = (int32_t)caps.slots;
-        pp.counters = counters;
-        pp.med_list = reinterpret_cast<int32_t*>(ws + o_med);
-        pp.heavy = reinterpret_cast<HeavyRow*>(ws + o_heavy);
-        pp.chunks = reinterpret_cast<ChunkItem*>(ws + o_chunks);
-        if ((he = launch_partition(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
-
+        w.rowptr = mode == 0 ? a.rowptr : a.rowptr_t;
+        w.colidx = mode == 0 ? a.colidx : a.colidx_t;
+        w.counters = cnt_sets + mode * kRowsSetWords;
         BwdParams bp;
-        bp.rowptr = rp;
-        bp.colidx = ci;
+        bp.w = w;
         bp.A = static_cast<const char*>(mode == 0 ? a.Q : a.K);
         bp.B = static_cast<const char*>(mode == 0 ? a.dO : a.V);
         bp.X = static_cast<const char*>(mode == 0 ? a.K : a.Q);
         bp.Y = static_cast<const char*>(mode == 0 ? a.V : a.dO);
         bp.O = static_cast<const char*>(a.O);
         bp.lse = a.lse;
-        bp.delta = reinterpret_cast<float*>(ws + o_delta);
+        bp.stat = reinterpret_cast<float2*>(ws + o_stat);
         bp.out1 = static_cast<char*>(mode == 0 ? a.dQ : a.dK);
         bp.out2 = static_cast<char*>(a.dV);
-        bp.N = a.N;
         bp.c = a.scale * 1.4426950408889634f;
         bp.scale = a.scale;
-        bp.light_max = light_max;
-        bp.cap_items = (int32_t)caps.items;
-        bp.cap_heavy = (int32_t)caps.heavy;
-        bp.counters = counters;
-        bp.med_list = pp.med_list;
-        bp.chunks = pp.chunks;
-        bp.heavy = pp.heavy;
+        bp.row_shift = floor_log2((uint64_t)a.H * D * Elt<T>::kBytes);
+        bp.heads = a.H;
         bp.part = reinterpret_cast<float*>(ws + o_part);
-        int merge_grid = (int)((caps.heavy + kWavesPerBlock - 1) / kWavesPerBlock);
-        if (merge_grid > device_cus(dev) * 8) merge_grid = device_cus(dev) * 8;
-        if (merge_grid < 1) merge_grid = 1;
-        if (mode == 0) {
-            hipLaunchKernelGGL((gt_bwd_kernel<T, H, D, 0>), dim3(grid), dim3(kBlock), 0, stream, bp);
-            if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "backward launch");
-            hipLaunchKernelGGL((gt_bwd_merge_kernel<T, H, D, 0>), dim3(merge_grid), dim3(kBlock), 0, stream, bp);
-        } else {
-            hipLaunchKernelGGL((gt_bwd_kernel<T, H, D, 1>), dim3(grid), dim3(kBlock), 0, stream, bp);
-            if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "backward launch");
-            hipLaunchKernelGGL((gt_bwd_merge_kernel<T, H, D, 1>), dim3(merge_grid), dim3(kBlock), 0, stream, bp);
-        }
-        if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "backward merge launch");
+        st = mode == 0 ? launch_bwd_pass<T, HS, D, 0>(bp, rule, sp, dev, stream)
+                       : launch_bwd_pass<T, HS, D, 1>(bp, rule, sp, dev, stream);
+        if (st != GT_SUCCESS) return st;
     }
     return GT_SUCCESS;
 }
 
 using BwdFn = gt_status (*)(const BwdArgs&, hipStream_t);
 
+// Slices as in the forward: the heads of 256 bytes, or one.
 template <typename T>
 BwdFn pick_bwd(int32_t H, int32_t D) {
-#define GT_CASE(h, d) \
-    if (H == h && D == d) return &launch_bwd<T, h, d>;
-    GT_CASE(1, 32) GT_CASE(1, 64) GT_CASE(1, 128)
-    GT_CASE(2, 32) GT_CASE(2, 64) GT_CASE(2, 128)
-    GT_CASE(4, 32) GT_CASE(4, 64) GT_CASE(4, 128)
-    GT_CASE(8, 32) GT_CASE(8, 64) GT_CASE(8, 128)
-    GT_CASE(1, 256) GT_CASE(2, 256) GT_CASE(4, 256) GT_CASE(8, 256)
-    if constexpr (std::is_same<T, bf16_tag>::value) {  // a head must fit 64 lanes of 16 bytes
-        GT_CASE(1, 512) GT_CASE(2, 512) GT_CASE(4, 512)
+    constexpr bool kBf16 = std::is_same<T, bf16_tag>::value;
+    if (H != 1 && H != 2 && H != 4 && H != 8) return nullptr;
+    switch (D) {
+        case 32:
+            if constexpr (kBf16)
+                if (H >= 4) return &launch_bwd<T, 4, 32>;
+            if (H >= 2) return &launch_bwd<T, 2, 32>;
+            return &launch_bwd<T, 1, 32>;
+        case 64:
+            if constexpr (kBf16)
+                if (H >= 2) return &launch_bwd<T, 2, 64>;
+            return &launch_bwd<T, 1, 64>;
+        case 128: return &launch_bwd<T, 1, 128>;
+        case 256: return &launch_bwd<T, 1, 256>;
+        case 512:  // a head must fit 64 lanes of 16 bytes
+            if constexpr (kBf16)
+                if (H <= 4) return &launch_bwd<T, 1, 512>;
+            return nullptr;
+        default: return nullptr;
     }
-#undef GT_CASE
-    return nullptr;
 }

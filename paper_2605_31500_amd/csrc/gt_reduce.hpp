@@ -17,8 +17,11 @@
 // ranges on their XCDs) and the partial words of cut rows are merged by a second
 // kernel instead of 64-bit atomics.  Padding entries of a step repeat a valid
 // entry, which a minimum absorbs, so they need no mask.
-// Min over 512 fp32 features on the power-law graph of 169 K nodes (2 KiB rows):
-// MEASURED_MIN us per call with whole rows and with slices.
+// Min with sources, whole rows in row order -> slices and source ranges (us per
+// call): R-MAT scale 20, 128 fp32 features 1702 -> 1412; lognormal 500 K nodes, 512
+// fp32 5339 -> 4763; power law 20 K nodes, 1024 bf16 130 -> 86, 169 K nodes, 512 fp32
+// 510 -> 492.  Slices of 128 / 256 / 512 bytes: 1518 / 1412 / 1376, 5095 / 4763 /
+// 4705, 93 / 86 / 94 and 506 / 492 / 505.
 // This file is included by gt_attn.hip inside its anonymous namespace.
 
 constexpr uint64_t kRedEmpty = ~0ull;  // no entry yet: source 0xFFFFFFFF is never valid
@@ -248,7 +251,7 @@ gt_status launch_reduce(const ReduceArgs& a, const gt_tuning* tu, hipStream_t st
     using Op = RedOp<T, NVEC>;
     constexpr int kSlotBytes = Op::kSlotWords * (int)sizeof(uint64_t);
     const int slices = a.F / (NVEC * Op::kEPV);
-    const RowRule rule = row_rule(a.N, a.E, slices, NVEC * 16, kSlotBytes, kWave / NVEC, tu);
+    const RowRule rule = row_rule(a.N, a.E, slices, NVEC * 16, 3 * (2 * kSlotBytes + 256) / 4, kWave / NVEC, tu);
     int dev = 0;
     if (const gt_status ds = call_device(stream, &dev); ds != GT_SUCCESS) return ds;
     hipError_t he = hipSuccess;

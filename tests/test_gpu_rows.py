@@ -50,3 +50,26 @@ def test_forward_at_partition_edges(dtype, H, D, kind):
     assert np.array_equal(got, run_gpu(rowptr, colidx, Q, K, V, scale))  # list orders differ from call to call
     ref, absagg, _ = oracle.gt_attn_fwd(rowptr, colidx, Q, K, V, scale, want_lse=False)
     assert gate_error(got, ref, absagg) <= (TOL_F32 if dtype == "f32" else TOL_BF16)
+
+
+@pytest.mark.parametrize("kind", ["edges", "many_short_pieces", "unsorted"])
+@pytest.mark.parametrize("dtype,F", [("f32", 16), ("f32", 64), ("f32", 512), ("bf16", 32), ("bf16", 256)])
+def test_reduce_at_partition_edges(dtype, F, kind):
+    """Values and sources, bit for bit."""
+    from tests.test_gpu_reduce import check, features
+    rowptr, colidx = graph(kind)
+    check(rowptr, colidx, features(F, rowptr.size - 1, F, dtype), dtype, "max")
+
+
+@pytest.mark.parametrize("kind", ["edges", "many_short_pieces", "unsorted"])
+@pytest.mark.parametrize("dtype,H,D", [("f32", 4, 32), ("f32", 1, 128), ("bf16", 8, 64)])
+def test_backward_at_partition_edges(dtype, H, D, kind):
+    from tests.test_gpu_bwd import check_grads
+    from tests.helpers import run_gpu_fwd_bwd
+    rowptr, colidx = graph(kind)
+    N, seed = rowptr.size - 1, 3 * H * D
+    Q, K, V = synth.features(seed, N, H, D, dtype)
+    dO, _, _ = synth.features(seed + 1, N, H, D, dtype)
+    scale = np.float32(1 / math.sqrt(D))
+    got = run_gpu_fwd_bwd(rowptr, colidx, Q, K, V, dO, scale)
+    check_grads(rowptr, colidx, Q, K, V, dO, scale, got, dtype)
