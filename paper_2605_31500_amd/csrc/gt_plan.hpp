@@ -1,0 +1,225 @@
+// How a call's rows are cut and how much of the device and of memory its row
+// kernels take: arithmetic only, the same on the host and on the device (included
+// by gt_attn.hip inside its anonymous namespace; a test compiles it for the CPU).
+// gt_rows.hpp says why rows are cut.
+
+constexpr int kWave = 64;
+constexpr int kWavesPerBlock = 4;
+constexpr int kXcds = 8;
+constexpr size_t kScratchBytes = size_t(256) << 20;  // array of the allocation-free entry point
+
+constexpr int kClasses = 32;  // degree octaves
+
+// How the rows of a call are cut.  A row of degree d <= light_max is one segment;
+// longer rows are listed by degree octave (class c: 2^c <= d < 2^(c+1)), and all
+// rows of a class are cut into the same number of pieces.
+struct RowCut {
+    int64_t N;
+    uint32_t E;
+    int32_t light_max;
+    int32_t min_class;   // class of light_max + 1
+    uint32_t split_min;  // classes whose shortest row has this many entries are cut
+    uint32_t chunk;      // entries of a piece at most (unless nq_max or nq_floor says otherwise)
+    uint32_t nq_floor, nq_max;
+    uint32_t group_len;  // longest piece that one lane group reads
+    uint32_t cap_slots;  // partial states there is room for
+};
+
+// Rows that class c can hold: their degrees are at least 2^c.
+__host__ __device__ inline uint32_t class_capacity(const RowCut& w, int c) {
+    if (c < w.min_class || c >= kClasses - 1) return 0;
+    return (int64_t)(w.E >> c) < w.N ? w.E >> c : (uint32_t)w.N;
+}
+
+// Pieces of a row of class c, where there is room for their partial states.
+__host__ __device__ inline uint32_t class_pieces(const RowCut& w, int c) {
+    if ((1u << c) < w.split_min) return 1;
+    const uint32_t nq = (2u << c) / w.chunk > w.nq_floor ? (2u << c) / w.chunk : w.nq_floor;
+    return nq < w.nq_max ? nq : w.nq_max;
+}
+
+// Whether pieces of class c are too long for one lane group.
+__host__ __device__ inline bool class_spread(const RowCut& w, int c, uint32_t nq) {
+    return (uint32_t)((uint64_t(2) << c) / nq) > w.group_len;
+}
+
+// Pieces of each of n rows, nq of them or half as many until their partial states
+// fit the `left` ones.
+__host__ __device__ inline uint32_t fit_pieces(uint32_t n, uint32_t nq, uint32_t left) {
+    while (nq > 1 && (uint64_t)n * nq > left) nq >>= 1;
+    return nq;
+}
+
+// Pieces [lo, hi) of a class's n * nq that XCD xcd takes (piece number major).
+__host__ __device__ inline uint32_t piece_share(uint64_t pieces, uint32_t xcd) {
+    return (uint32_t)(pieces * xcd / kXcds);
+}
+
+// A wavefront's batches of `pieces` pieces: one each if they are spread over its P
+// lane groups, else P at a time.
+__host__ __device__ inline uint32_t piece_batches(uint32_t pieces, bool spread, uint32_t P) {
+    return spread ? pieces : (pieces + P - 1) / P;
+}
+
+// Lane groups that n rows of class c ask for, P per wavefront, at most: fit_pieces
+// may halve the pieces, and then they may get too long for one lane group.
+__host__ __device__ inline uint32_t class_groups(const RowCut& w, int c, uint32_t n, uint32_t P) {
+    const uint32_t nq = class_pieces(w, c);
+    uint32_t q = nq;
+    while (q > 1 && !class_spread(w, c, q)) q >>= 1;
+    const uint32_t most = class_spread(w, c, q) ? q * P : q;
+    return n * (most > nq ? most : nq);
+}
+
+// Batches of an XCD at most, if all classes together ask for `groups` lane groups
+// (each class rounds up to a batch).
+__host__ __device__ inline uint32_t batch_bound(uint32_t groups, uint32_t P) {
+    return groups / (kXcds * P) + kClasses;
+}
+
+// A long row in its class list (entry positions fit 32 bits: E < 2^31).
+struct LongRow {
+    int32_t row;
+    uint32_t begin;
+    uint32_t deg;
+    uint32_t pad;
+};
+
+// RowCut, before the room for partial states is known.
+struct RowRule {
+    int32_t light_max;
+    uint32_t split_min, chunk, nq_floor, nq_max, group_len;
+    int64_t max_slots;  // partial states at most, over all graphs of this size
+    bool forced;        // chunk length given by the caller
+};
+
+// Rows are cut into eight pieces from eight times the length at which a piece
+// saves what it costs: `piece_bytes` of its partial state (written and read once),
+// row vectors, list entry and index line.  Its entries, of `gather_bytes` each, hit the L2 with a share `cover` more than in
+// row order, the part of an XCD's eighth of the sources that its L2 holds
+// (uniform sources).  At least eight entries per piece (four where that pays and
+// the sources nearly fit an L2), and 32 per wavefront of `groups` pieces.  Longer
+// rows get pieces of 32 to 64 entries, twice that where the call's gathers take
+// more than about 60 us, and up to 32 of them: beyond that a wavefront reads a
+// piece, since every piece has to be merged.
+// Measured (us per call).  Rows cut from 32 / 64 / 128 entries, with 128-byte
+// slices: fp32 4x32 power law of 16 K nodes 41.6 / 45.4 / 58.3, of 169 K nodes 212
+// / 211 / 218, R-MAT scale 21 4932 / 4730 / 4764; fp32 4x128 power law of 169 K
+// nodes 985 / 880 / 870; bf16 8x64 lognormal 10411 / 10409 / 9910.  At most 16 /
+// 32 / 64 / 256 pieces: power law of 16 K nodes 41.1 / 37.9 / 39.4 / 41.7, R-MAT
+// scale 21 4716 / 4683 / 4693 / 4793, backward of R-MAT scale 20 bf16 4x32 2720 /
+// 2735 / 2736 / 3023.
+RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_bytes, int groups, const gt_tuning* tu) {
+    constexpr double kL2Bytes = 4.0 * 1024 * 1024, kGatherBytesPerSecond = 7.0e12;
+    double cover = kXcds * kL2Bytes / ((double)N * gather_bytes);
+    if (cover > 0.75) cover = 0.75;
+    const double pays = piece_bytes / (gather_bytes * cover);
+    uint32_t len = 32 / groups > 8 ? 32 / groups : pays < 4 && (double)N * gather_bytes <= 2 * kL2Bytes ? 4 : 8;
+    while (len < 32 && 2 * len <= pays) len *= 2;
+    const bool large = (double)E * slices * gather_bytes / kGatherBytesPerSecond > 60e-6;
+    RowRule r;
+    r.light_max = (int32_t)(kXcds * len);
+    r.split_min = kXcds * len;
+    r.chunk = large ? 128 : 64;
+    r.nq_floor = kXcds;
+    r.nq_max = 32;
+    r.group_len = r.chunk;
+    r.forced = false;
+    r.max_slots = E / (2 * len) + 1;
+    if (tu && tu->light_max_deg > 0) r.light_max = tu->light_max_deg;
+    if (tu && tu->heavy_min_deg > 0) r.split_min = r.split_min > (uint32_t)tu->heavy_min_deg ? r.split_min : (uint32_t)tu->heavy_min_deg;
+    if (tu && tu->chunk_edges > 0) {
+        r.forced = true;
+        r.chunk = ((uint32_t)tu->chunk_edges + kWave - 1) / kWave * kWave;
+        r.split_min = r.chunk + 1;
+        if (tu->heavy_min_deg > 0 && (uint32_t)tu->heavy_min_deg > r.split_min) r.split_min = (uint32_t)tu->heavy_min_deg;
+        r.nq_floor = 1;
+        r.nq_max = 32;
+        r.max_slots = 2 * (E / r.chunk) + 1;
+    }
+    return r;
+}
+
+int floor_log2(uint64_t x) { return 63 - __builtin_clzll(x); }
+
+// Entries of the class lists together: class_capacity over the classes.
+uint64_t long_list_rows(int64_t N, int64_t E, int32_t light_max) {
+    uint64_t n = 0;
+    for (int c = floor_log2((uint64_t)light_max + 1); c < kClasses - 1; ++c) n += (uint64_t)((E >> c) < N ? (E >> c) : N);
+    return n;
+}
+
+void set_rule(RowCut& w, const RowRule& r) {
+    w.light_max = r.light_max;
+    w.min_class = floor_log2((uint64_t)r.light_max + 1);
+    w.split_min = r.split_min;
+    w.chunk = r.chunk;
+    w.nq_floor = r.nq_floor;
+    w.nq_max = r.nq_max;
+    w.group_len = r.group_len;
+}
+
+// Partial states and slices per launch.  Where the states of all slices fit
+// kSlicesTogether bytes, the slices share a launch (and a merge); larger calls
+// launch one slice at a time, which reuses the states' memory, up to the
+// workspace of the allocation-free entry point.
+struct SlotPlan {
+    uint32_t cap;
+    int slices;  // per launch
+};
+constexpr size_t kSlicesTogether = size_t(192) << 20;
+
+// `bounded`: the call's workspace has to fit the allocation-free entry point.
+SlotPlan slot_plan(const RowRule& r, int slices, size_t slot_bytes, size_t other_bytes, bool bounded) {
+    SlotPlan s;
+    s.slices = slices;
+    s.cap = (uint32_t)r.max_slots;
+    const size_t room = (other_bytes + 1024 < kScratchBytes ? kScratchBytes - other_bytes - 1024 : 0) / slot_bytes;
+    const size_t all = kSlicesTogether / (slot_bytes * slices);
+    if (!r.forced) {
+        // (a quarter of the most is enough for most graphs; where it is not,
+        // rows are cut into fewer pieces)
+        if (all >= (size_t)r.max_slots / 4)
+            s.cap = (uint32_t)(all < (size_t)r.max_slots ? all : (size_t)r.max_slots);
+        else
+            s.slices = 1;
+    }
+    if ((!r.forced || bounded) && s.cap > room / s.slices) s.cap = (uint32_t)(room / s.slices);
+    return s;
+}
+
+// Workgroups of a merge kernel for one slice: one wavefront per cut row if rows
+// have eight pieces (two, where the caller gives their length), up to eight
+// workgroups per CU.
+int merge_blocks(const SlotPlan& sp, const RowRule& r, int cus) {
+    const int64_t cut_rows = (int64_t)sp.cap / (r.forced ? 2 : kXcds) + 1;
+    const int64_t g = (cut_rows + kWavesPerBlock - 1) / kWavesPerBlock;
+    return (int)(g < cus * 8 ? g : cus * 8);
+}
+
+// Workgroups of a row kernel for one slice.  Light rows: two batches (a row per
+// lane group) per wave, four where the tile path may take them all; many more
+// waves than the device holds, so that the hardware scheduler evens out the
+// per-wave work (1, 2, 4 and 8 batches: R-MAT scale 21 fp32 4x32 5.08, 5.11, 5.33
+// and 5.77 ms).  Long rows: one batch per wave if three quarters of all entries lie
+// in pieces of 64, up to eight times the workgroups the device holds at once (a
+// wave without a batch still costs its prologue).
+struct RowGrid {
+    uint32_t blocks, long_blocks;
+};
+RowGrid row_grid(int64_t N, int64_t E, int groups, bool tiles, int resident, const gt_tuning* tu) {
+    auto blocks = [](int64_t batches, int64_t per_wave) {
+        const int64_t g = (batches + per_wave * kWavesPerBlock - 1) / (per_wave * kWavesPerBlock);
+        return (uint32_t)((g + kXcds - 1) / kXcds * kXcds);
+    };
+    RowGrid rg;
+    rg.long_blocks = blocks(3 * (E / 4) / ((int64_t)groups * 64) + 1, 1);
+    const uint32_t most = (uint32_t)(tiles ? 2 : 8) * (uint32_t)resident / kXcds * kXcds;
+    if (rg.long_blocks > most) rg.long_blocks = most;
+    rg.blocks = rg.long_blocks + blocks((N + groups - 1) / groups, tiles ? 4 : 2);
+    if (tu && tu->grid_blocks > 0) {
+        rg.long_blocks = blocks(((int64_t)tu->grid_blocks + 1) / 2 * kWavesPerBlock, 1);
+        rg.blocks = 2 * rg.long_blocks;
+    }
+    return rg;
+}

@@ -28,8 +28,6 @@
 // (a light row, a piece) is read by one lane group; pieces longer than
 // group_len are spread over the P groups of a wavefront and merged there.
 
-constexpr int kClasses = 32;  // degree octaves; lane i of a wavefront keeps class 31 - i
-
 // Work-list counters, cleared by a fill kernel or by an earlier call's
 // partition.  Each sits on its own 128-byte line so that atomics on different
 // counters do not serialise on one cache line.
@@ -46,32 +44,15 @@ constexpr int kRowsStride = 32;                         // ints between counters
 constexpr int kRowsSetWords = ROWS_COUNT * kRowsStride;  // one counter set
 #define ROWS_CNT(c, i) ((c)[(i) * kRowsStride])
 
-// A long row in its class list (entry positions fit 32 bits: E < 2^31).
-struct LongRow {
-    int32_t row;
-    uint32_t begin;
-    uint32_t deg;
-    uint32_t pad;
-};
-
 struct LightRow {
     int32_t row;
     uint32_t begin;
 };
 constexpr uint32_t kDegMany = 255;
 
-struct RowWork {
+struct RowWork : RowCut {
     const int64_t* rowptr;
     const int32_t* colidx;
-    int64_t N;
-    uint32_t E;
-    int32_t light_max;
-    int32_t min_class;   // class of light_max + 1
-    uint32_t split_min;  // classes whose shortest row has this many entries are cut
-    uint32_t chunk;      // entries of a piece at most (unless nq_max or nq_floor says otherwise)
-    uint32_t nq_floor, nq_max;
-    uint32_t group_len;  // longest piece that one lane group reads
-    uint32_t cap_slots;  // partial states there is room for
     bool maybe_no_light;  // the tile path may have taken every light row
     uint32_t long_blocks;  // workgroups of a slice that take the long rows (the first ones)
     int32_t* counters;
@@ -97,22 +78,6 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t x, int lane) {
     return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
 }
 
-// Rows that class c can hold: their degrees are at least 2^c.
-__device__ __forceinline__ uint32_t class_capacity(const RowWork& w, int c) {
-    const uint32_t most = (uint32_t)w.N;
-    return c >= w.min_class && c < kClasses - 1 ? min(w.E >> c, most) : 0u;
-}
-
-// Pieces of a row of class c, where there is room for their partial states.
-__device__ __forceinline__ uint32_t class_pieces(const RowWork& w, int c) {
-    return (1u << c) >= w.split_min ? min(max((2u << c) / w.chunk, w.nq_floor), w.nq_max) : 1u;
-}
-
-// Whether pieces of class c are too long for one lane group.
-__device__ __forceinline__ bool class_spread(const RowWork& w, int c, uint32_t nq) {
-    return (uint32_t)((uint64_t(2) << c) / nq) > w.group_len;
-}
-
 // The classes' rows, pieces and places, one class per lane.
 struct ClassPlan {
     uint32_t n;      // rows
@@ -136,8 +101,7 @@ __device__ __forceinline__ ClassPlan class_plan(const RowWork& w, int lane) {
         uint32_t left = w.cap_slots;
         for (int i = 1; i < kClasses; ++i) {
             const uint32_t n = lane_value(pl.n, i);
-            uint32_t nq = lane_value(pl.nq, i);
-            while (nq > 1 && (uint64_t)n * nq > left) nq >>= 1;
+            const uint32_t nq = fit_pieces(n, lane_value(pl.nq, i), left);
             if (nq > 1) left -= n * nq;
             if (lane == i) pl.nq = nq;
         }
@@ -194,14 +158,13 @@ __device__ __forceinline__ void row_loop(const RowWork& w, const Op& op, int32_t
     uint32_t lo = 0, hi = 0, nb = 0, cum = 0;
     bool spread = false;
     if (long_rows) {
-        // (each class rounds up to a batch)
-        if (it > (uint32_t)ROWS_CNT(w.counters, ROWS_PIECES) / (kXcds * P) + kClasses) return;
+        if (it >= batch_bound((uint32_t)ROWS_CNT(w.counters, ROWS_PIECES), P)) return;
         pl = class_plan(w, lane);
         const uint64_t flat = (uint64_t)pl.n * pl.nq;  // pieces, piece number major
-        lo = (uint32_t)(flat * xcd / kXcds);
-        hi = (uint32_t)(flat * (xcd + 1) / kXcds);
+        lo = piece_share(flat, xcd);
+        hi = piece_share(flat, xcd + 1);
         spread = lane < kClasses && class_spread(w, kClasses - 1 - lane, pl.nq);
-        nb = spread ? hi - lo : (hi - lo + P - 1) / P;
+        nb = piece_batches(hi - lo, spread, P);
         cum = scan32(nb);
         total = lane_value(cum, kClasses - 1);
     } else {
@@ -489,13 +452,7 @@ __global__ void __launch_bounds__(kBlock) gt_sort_rows_kernel(SortParams p) {
             if (!fits) atomicOr(&ROWS_CNT(w.counters, ROWS_OVERFLOW), 1);
             long_base[c] = fits ? off + base : ~0u;
         }
-        uint32_t groups = 0;
-        if (n) {
-            // (a class that has no room for its pieces asks for whole wavefronts)
-            const uint32_t nq = class_pieces(w, c);
-            groups = n * (class_spread(w, c, nq) ? nq * p.groups : max(nq, p.groups));
-        }
-        groups = scan32(groups);
+        const uint32_t groups = scan32(n ? class_groups(w, c, n, p.groups) : 0u);
         if (lane == kClasses - 1 && groups) atomicAdd(&ROWS_CNT(w.counters, ROWS_PIECES), (int32_t)groups);
     } else if (wv == 1) {
         const int c = kClasses - 1 - lane;

@@ -1,0 +1,123 @@
+"""The row kernels' plan on the CPU: the library's own arithmetic (csrc/gt_plan.hpp,
+compiled by tests/plan_probe.cpp) over random graphs' degree classes."""
+import ctypes
+import functools
+import hashlib
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2605_31500_amd", "csrc")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not installed")
+
+
+class Tuning(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in ("light_max_deg", "heavy_min_deg", "chunk_edges", "grid_blocks",
+                                              "dense_tiles", "bf16_weights")]
+
+
+class RowCut(ctypes.Structure):
+    _fields_ = [("N", ctypes.c_int64), ("E", ctypes.c_uint32), ("light_max", ctypes.c_int32),
+                ("min_class", ctypes.c_int32), ("split_min", ctypes.c_uint32), ("chunk", ctypes.c_uint32),
+                ("nq_floor", ctypes.c_uint32), ("nq_max", ctypes.c_uint32), ("group_len", ctypes.c_uint32),
+                ("cap_slots", ctypes.c_uint32)]
+
+
+class RowRule(ctypes.Structure):
+    _fields_ = [("light_max", ctypes.c_int32), ("split_min", ctypes.c_uint32), ("chunk", ctypes.c_uint32),
+                ("nq_floor", ctypes.c_uint32), ("nq_max", ctypes.c_uint32), ("group_len", ctypes.c_uint32),
+                ("max_slots", ctypes.c_int64), ("forced", ctypes.c_bool)]
+
+
+@functools.lru_cache(maxsize=None)
+def probe():
+    srcs = [os.path.join(ROOT, "tests", "plan_probe.cpp"), os.path.join(CSRC, "gt_plan.hpp"),
+            os.path.join(ROOT, "include", "gt_attn.h")]
+    h = hashlib.sha256(b"".join(open(s, "rb").read() for s in srcs)).hexdigest()[:12]
+    out = os.path.join(ROOT, "_build", "plan_probe-%s.so" % h)
+    if not os.path.exists(out):
+        os.makedirs(os.path.dirname(out), exist_ok=True)
+        tmp = out + ".tmp%d" % os.getpid()
+        r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-fPIC", "-shared", "-fsanitize=undefined",
+                            "-fno-sanitize-recover=all", "-static-libubsan", "-D__HIP_PLATFORM_AMD__", "-D__host__=",
+                            "-D__device__=", "-isystem", os.path.join(ROCM, "include"), "-I",
+                            os.path.join(ROOT, "include"), "-I", CSRC, srcs[0], "-o", tmp],
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-3000:]
+        os.replace(tmp, out)
+    L = ctypes.CDLL(out)
+    L.probe_batches.restype = ctypes.c_int64
+    return L
+
+
+# Row kernels: bytes gathered per entry, `piece_bytes` of the rule, lane groups per wavefront.
+KERNELS = [(512, 600, 4), (512, 600, 2), (256, 400, 8), (128, 300, 16), (64, 300, 16), (256, 600, 4), (1024, 2000, 1)]
+
+
+def batches(cut, rows, P):
+    rows = np.ascontiguousarray(rows, dtype=np.uint32)
+    nq, total = np.zeros(32, np.uint32), np.zeros(8, np.uint64)
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    bound = probe().probe_batches(ctypes.byref(cut), p(rows), ctypes.c_uint32(P), p(nq), p(total))
+    assert bound >= 0
+    return bound, nq, total
+
+
+def rule(N, E, slices, gather, piece, P, tuning=None):
+    cut, r = RowCut(), RowRule()
+    probe().probe_rule(ctypes.c_int64(N), ctypes.c_int64(E), slices, gather, piece, P,
+                       ctypes.byref(tuning) if tuning else None, ctypes.byref(cut), ctypes.byref(r))
+    return cut, r
+
+
+def random_rows(rng, cut):
+    """Rows per class of a graph with the cut's N and E."""
+    rows, left_e, left_n = np.zeros(32, np.int64), int(cut.E), int(cut.N)
+    for c in rng.permutation(np.arange(cut.min_class, 31)):
+        most = min(left_e >> int(c), left_n)
+        n = int(most * rng.choice([0, 0, 1e-3, 0.1, 0.5, 1.0]) * rng.random())
+        if c == cut.min_class:  # (its shortest rows are longer than light_max)
+            n = min(n, left_e // (cut.light_max + 1))
+        rows[c], left_e, left_n = n, left_e - (n << int(c)), left_n - n
+    return rows
+
+
+@pytest.mark.parametrize("gather,piece,P", KERNELS)
+def test_no_wave_with_batches_ends_early(gather, piece, P):
+    """A wave ends where its number reaches the bound that the partition counts: every
+    batch has to lie below it, also where classes lose pieces for want of partial states
+    and what is left of them takes whole wavefronts."""
+    rng = np.random.default_rng(gather + P)
+    shrunk_and_spread = 0
+    for _ in range(3000):
+        N = int(np.exp(rng.uniform(np.log(100), np.log(1 << 24))))
+        E = min(int(N * np.exp(rng.uniform(0, np.log(500)))), (1 << 31) - 1)
+        tuning = None
+        if rng.random() < 0.3:
+            tuning = Tuning(light_max_deg=int(rng.choice([0, 1, 8, 100])), chunk_edges=int(rng.choice([0, 64, 200, 5000])),
+                            heavy_min_deg=int(rng.choice([0, 64, 1000])))
+        cut, r = rule(N, E, int(rng.choice([1, 2, 8])), gather, piece, P, tuning)
+        cut.cap_slots = int(min(r.max_slots, 2**31) * rng.choice([1.0, 1.0, 0.3, 0.05, 0.001, 0.0]))
+        rows = random_rows(rng, cut)
+        bound, nq, total = batches(cut, rows, P)
+        assert int(total.max()) <= bound, (N, E, cut.cap_slots, list(rows))
+        for c in np.flatnonzero(rows):
+            full = 1 if (1 << int(c)) < cut.split_min else min(max((2 << int(c)) // cut.chunk, cut.nq_floor), cut.nq_max)
+            shrunk_and_spread += nq[c] < full and (2 << int(c)) // int(nq[c]) > cut.group_len
+    assert shrunk_and_spread > 100
+
+
+def test_halved_classes_take_whole_wavefronts():
+    """Backward of fp32 8x64 features: 6200 rows of 600 entries among 600 K, with room for half of their pieces."""
+    cut, _ = rule(600_000, 6200 * 600 + 3 * 600_000, 8, 512, 600, 4)
+    cut.split_min, cut.chunk, cut.nq_floor, cut.group_len, cut.cap_slots = 64, 128, 8, 128, 6200 * 4
+    rows = np.zeros(32)
+    rows[9] = 6200
+    bound, nq, total = batches(cut, rows, 4)
+    assert nq[9] == 4 and total.max() == 6200 * 4 // 8 and total.max() <= bound
