@@ -62,13 +62,15 @@ __host__ __device__ inline uint32_t piece_batches(uint32_t pieces, bool spread, 
 }
 
 // Lane groups that n rows of class c ask for, P per wavefront, at most: fit_pieces
-// may halve the pieces, and then they may get too long for one lane group.
-__host__ __device__ inline uint32_t class_groups(const RowCut& w, int c, uint32_t n, uint32_t P) {
+// may halve the pieces, and then they may get too long for one lane group.  (Over a
+// graph fewer than 2^31: a lane group more than a row's first reads two entries or
+// more.)
+__host__ __device__ inline uint64_t class_groups(const RowCut& w, int c, uint32_t n, uint32_t P) {
     const uint32_t nq = class_pieces(w, c);
     uint32_t q = nq;
     while (q > 1 && !class_spread(w, c, q)) q >>= 1;
     const uint32_t most = class_spread(w, c, q) ? q * P : q;
-    return n * (most > nq ? most : nq);
+    return (uint64_t)n * (most > nq ? most : nq);
 }
 
 // Batches of an XCD at most, if all classes together ask for `groups` lane groups

@@ -452,7 +452,7 @@ __global__ void __launch_bounds__(kBlock) gt_sort_rows_kernel(SortParams p) {
             if (!fits) atomicOr(&ROWS_CNT(w.counters, ROWS_OVERFLOW), 1);
             long_base[c] = fits ? off + base : ~0u;
         }
-        const uint32_t groups = scan32(n ? class_groups(w, c, n, p.groups) : 0u);
+        const uint32_t groups = scan32(n ? (uint32_t)class_groups(w, c, n, p.groups) : 0u);
         if (lane == kClasses - 1 && groups) atomicAdd(&ROWS_CNT(w.counters, ROWS_PIECES), (int32_t)groups);
     } else if (wv == 1) {
         const int c = kClasses - 1 - lane;

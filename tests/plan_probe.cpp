@@ -15,7 +15,8 @@ extern "C" {
 // Batches of each XCD for rows[c] rows of each class c, P lane groups per
 // wavefront, and the pieces of each class, as class_plan and row_loop have them;
 // returns batch_bound of what the partition counts.
-int64_t probe_batches(const RowCut* w, const uint32_t* rows, uint32_t P, uint32_t* nq, uint64_t* total) {
+int64_t probe_batches(const RowCut* w, const uint32_t* rows, uint32_t P, uint32_t* nq, uint64_t* total,
+                      uint64_t* asked) {
     uint64_t slots = 0;
     for (int c = 0; c < kClasses; ++c) {
         const uint32_t cap = class_capacity(*w, c);
@@ -38,6 +39,7 @@ int64_t probe_batches(const RowCut* w, const uint32_t* rows, uint32_t P, uint32_
             total[x] += piece_batches(piece_share(flat, x + 1) - piece_share(flat, x), class_spread(*w, c, nq[c]), P);
         groups += rows[c] ? class_groups(*w, c, rows[c], P) : 0;
     }
+    *asked = groups;  // (a 32-bit counter on the device)
     return batch_bound((uint32_t)groups, P);
 }
 

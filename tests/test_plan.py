@@ -64,8 +64,9 @@ def batches(cut, rows, P):
     rows = np.ascontiguousarray(rows, dtype=np.uint32)
     nq, total = np.zeros(32, np.uint32), np.zeros(8, np.uint64)
     p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
-    bound = probe().probe_batches(ctypes.byref(cut), p(rows), ctypes.c_uint32(P), p(nq), p(total))
-    assert bound >= 0
+    asked = ctypes.c_uint64()
+    bound = probe().probe_batches(ctypes.byref(cut), p(rows), ctypes.c_uint32(P), p(nq), p(total), ctypes.byref(asked))
+    assert bound >= 0 and asked.value < 1 << 32
     return bound, nq, total
 
 
@@ -121,3 +122,18 @@ def test_halved_classes_take_whole_wavefronts():
     rows[9] = 6200
     bound, nq, total = batches(cut, rows, 4)
     assert nq[9] == 4 and total.max() == 6200 * 4 // 8 and total.max() <= bound
+
+
+@pytest.mark.parametrize("P", [1, 4, 16])
+@pytest.mark.parametrize("light_max_deg", [1, 2, 40, 0])
+def test_largest_graphs_count_in_32_bits(P, light_max_deg):
+    """2^31 - 1 entries in rows of one class, as many as there can be: the lane groups that the partition counts do not
+    wrap, and no wave with batches ends early."""
+    cut, r = rule((1 << 31) - 1, (1 << 31) - 1, 1, 1024 // P, 300, P, Tuning(light_max_deg=light_max_deg))
+    for cap in (r.max_slots, 1 << 20, 1 << 10, 0):
+        cut.cap_slots = cap
+        for c in range(cut.min_class, 31):
+            rows = np.zeros(32)
+            rows[c] = (cut.E >> c) if c > cut.min_class else cut.E // (cut.light_max + 1)
+            bound, _, total = batches(cut, rows, P)
+            assert int(total.max()) <= bound
