@@ -641,7 +641,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWin = 64;          // window rows = tile columns
-constexpr int kWinMaxDeg = 64;    // light rows handled here have at most this degree
 constexpr int kNoTile = -(1 << 28);  // a wave's window count that rules the tile out
 // Padded row of the transposed V tile, in bf16 elements: 34 dwords, so that
 // the 16 rows one P*V operand load reads (8 bytes per lane) start 2 banks
@@ -1439,8 +1438,6 @@ struct Args {
     bool noalloc = false;        // workspace from the scratch array, no allocation
 };
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
 // The device a call works on: the calling thread's current device.  The
 // workspace, its events and the kernels' memory all belong to it, so a stream
 // created on another device is refused rather than fed memory it may not be
@@ -1486,8 +1483,6 @@ int attn_resident(int dev) {
     return cache[dev];
 }
 
-constexpr int kDefaultTileMin = 256;
-
 template <int H, int D, int KIND>
 hipError_t launch_tiles(const TileParams& tp, hipStream_t stream) {
     const int64_t n_windows = (tp.N + kWin - 1) / kWin;
@@ -1506,115 +1501,44 @@ hipError_t pick_tiles(int H, const TileParams& tp, hipStream_t stream) {
     return hipErrorInvalidValue;
 }
 
-// What the allocation-free entry point counts as a call's workspace, for its
-// documented limit: the row lists, and the partial states of rows cut into chunks
-// (of `chunk` entries, by default half the steps that the call's gathers take at
-// 7 TB/s and a microsecond per step, up to 1024 entries, or an eighth of them up
-// to 8192) for all heads at once.  Calls within the limit get a workspace within
-// it; the others are refused.
-size_t noalloc_need(const Args& a, int elt_bytes, const gt_tuning* tu) {
-    const int row = a.H * a.D * elt_bytes, vecs = row / 16, lanes = vecs < kWave ? vecs : kWave;
-    const int rows = kWave / lanes, nv = vecs / lanes;
-    int u = 8 / nv > 2 ? 8 / nv : 2;
-    if (u > lanes) u = lanes;
-    const int64_t light = tu && tu->light_max_deg > 0 ? tu->light_max_deg : 8 * u;
-    const double steps = (double)a.E * (2.0 * row) / 7.0e12 / 1.0e-6;
-    const double entries = 0.5 * steps * (rows * (rows >= 4 && u >= 8 ? u / 2 : u));
-    auto whole = [](double x) { return ((int64_t)x + kWave - 1) / kWave * kWave; };
-    int64_t chunk = 0.25 * entries > 8192.0   ? 8192
-                    : 0.25 * entries > 1024.0 ? whole(0.25 * entries)
-                    : entries >= 1024.0       ? 1024
-                                              : whole(entries);
-    if (chunk < kWave) chunk = kWave;
-    int64_t heavy = rows >= 2 && chunk / 4 > 256 ? chunk / 4 : 256;
-    if (tu && tu->heavy_min_deg > 0) heavy = tu->heavy_min_deg;
-    if (tu && tu->chunk_edges > 0) chunk = whole(tu->chunk_edges);
-    if (heavy <= light) heavy = light + 1;
-    const size_t slots = 2 * (size_t)(a.E / chunk) + 1;
-    return (size_t)a.N * sizeof(int32_t) * (rows >= 4 ? 2 : 1) + 16 * ((size_t)(a.E / (chunk + 1)) + 1) +
-           24 * ((size_t)(a.E / heavy) + slots) + slots * a.H * (sizeof(float2) + a.D * sizeof(float));
-}
-
 template <typename T, int HS, int D, int KIND>
 gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     using Op = AttnOp<T, HS, D, KIND>;
-    constexpr int kRowSlice = HS * D * Elt<T>::kBytes;
-    constexpr int kSlotBytes = HS * (int)(D * sizeof(float) + sizeof(float2));
-    const int slices = a.H / HS;
-    RowRule rule = row_rule(a.N, a.E, slices, (KIND == KIND_GATV2 ? 1 : 2) * kRowSlice,
-                            3 * (2 * kSlotBytes + 256) / 4, Op::Gm::kP, tu);
-    // Dense-tile windows (bf16 rows of at most 256 bytes): on by default, for
-    // windows estimated to hold at least 256 in-window entries, which a 64-row
-    // block at half density holds about eight times over (measured on the SBM
-    // workload; on the R-MAT one no window qualifies and the tile kernel
-    // finds an empty list).
-    int tile_min = kDefaultTileMin;
-    if (tu && tu->dense_tiles != 0) tile_min = tu->dense_tiles;  // < 0: off
     constexpr bool kTileShape = KIND != KIND_GATV2 && std::is_same<T, bf16_tag>::value && D <= 128;
     static_assert(!kTileShape || Op::kSorted, "the tile path leaves its rows out of the light-row order");
-    const bool tile_rows = kTileShape && a.H * D <= 128, tile_call = tile_rows && tile_min > 0;
-    // (the same light rows with the path off: a row that it streams has the same
-    // bits then)
-    if (tile_rows && !(tu && tu->light_max_deg > 0)) rule.light_max = kWinMaxDeg;
-    if (tile_call && rule.light_max > kWinMaxDeg) rule.light_max = kWinMaxDeg;
-
+    const int slices = a.H / HS;
+    const AttnPlan plan = plan_attn(AttnShape{a.N, a.E, a.H, a.D, Elt<T>::kBytes, HS, Op::Gm::kP, KIND == KIND_GATV2, Op::kSorted},
+                                    tu, a.noalloc);
+    if (a.noalloc && plan.need > kScratchBytes) return scratch_exceeded(plan.need);
     int dev = 0;
     if (const gt_status ds = call_device(stream, &dev); ds != GT_SUCCESS) return ds;
     hipError_t he = hipSuccess;
-    const RowGrid rg = row_grid(a.N, a.E, Op::Gm::kP, tile_call, attn_resident<T, HS, D, KIND>(dev), tu);
-    // (calls that the allocation-free entry point takes keep their workspace
-    // within its array through either entry point, so that both give the same
-    // bits)
-    const size_t need = noalloc_need(a, Elt<T>::kBytes, tu);
-    const bool bounded = need <= kScratchBytes;
-    if (a.noalloc && !bounded) return scratch_exceeded(need);
+    const RowGrid rg = row_grid(a.N, a.E, Op::Gm::kP, plan.tiles, attn_resident<T, HS, D, KIND>(dev), tu);
 
-    // workspace: counters | long rows | light rows | window flags | partial (m,l) | partial acc
     RowWork w;
     w.rowptr = a.rowptr;
     w.colidx = a.colidx;
     w.N = a.N;
     w.E = (uint32_t)a.E;
-    const int64_t n_windows = (a.N + kWin - 1) / kWin;
-    // The allocation-free entry point takes the light rows in id order where
-    // their step order would not fit its array (more than 26 million nodes; the
-    // order changes no result), and then without the tile path, which needs it.
-    const bool fits = (size_t)a.N * (sizeof(LightRow) + 1) <= kScratchBytes / 16 * 14;
-    const bool tiles = tile_call && (!bounded || fits);
-    const bool sorted = Op::kSorted && (!a.noalloc || fits);
-    size_t off = 0;
-    const size_t o_cnt = off;    off = align_up(off + 2 * kRowsSetWords * sizeof(int32_t), 256);  // two sets
-    const size_t o_light = off;  off = align_up(off + (sorted ? (size_t)a.N * sizeof(LightRow) : 0), 256);
-    const size_t o_deg = off;    off = align_up(off + (sorted ? (size_t)a.N : 0), 256);
-    const size_t o_win = off;    off = align_up(off + (tiles ? (size_t)n_windows : 0), 256);
-    const size_t o_long = off;
-    // (a larger light bound makes the class lists shorter: only near 2^31 entries)
-    while (bounded && off + long_list_rows(a.N, a.E, rule.light_max) * sizeof(LongRow) + 4096 > kScratchBytes)
-        rule.light_max = 2 * rule.light_max + 1;
-    set_rule(w, rule);
-    off = align_up(off + (size_t)long_list_rows(a.N, a.E, w.light_max) * sizeof(LongRow), 256);
-    const SlotPlan sp = slot_plan(rule, slices, kSlotBytes, off, bounded);
-    w.cap_slots = sp.cap;
-    const size_t o_ml = off;     off = align_up(off + (size_t)sp.cap * sp.slices * HS * sizeof(float2), 256);
-    const size_t o_acc = off;    off = align_up(off + (size_t)sp.cap * sp.slices * HS * D * sizeof(float), 256);
-    const size_t ws_bytes = off;
+    set_rule(w, plan.rule);
+    w.cap_slots = plan.slots.cap;
 
     CallWorkspace cw;
-    gt_status st = call_workspace(a.noalloc, dev, ws_bytes, stream, cw);
+    gt_status st = call_workspace(a.noalloc, dev, plan.bytes, stream, cw);
     if (st != GT_SUCCESS) return st;
     char* ws = cw.ptr;
     // Counter sets: a cached block alternates between its two (the partition
     // zeroes the other one for the block's next call), so a block whose last
     // user was a forward call needs no clear kernel; a new block, the
     // scratch array and a captured stream clear the one set they use.
-    int32_t* cnt_base = reinterpret_cast<int32_t*>(ws + o_cnt);
+    int32_t* cnt_base = reinterpret_cast<int32_t*>(ws);
     const bool alternate = cw.kind == CallWorkspace::CACHED;
     w.counters = cnt_base + (alternate ? (cw.block.gen & 1u) * kRowsSetWords : 0);
-    w.long_list = reinterpret_cast<LongRow*>(ws + o_long);
-    w.light_list = sorted ? reinterpret_cast<LightRow*>(ws + o_light) : nullptr;
-    w.light_deg = reinterpret_cast<uint8_t*>(ws + o_deg);
+    w.long_list = reinterpret_cast<LongRow*>(ws + plan.o_long);
+    w.light_list = plan.sorted ? reinterpret_cast<LightRow*>(ws + plan.o_light) : nullptr;
+    w.light_deg = reinterpret_cast<uint8_t*>(ws + plan.o_deg);
     w.long_blocks = 0;
-    w.maybe_no_light = tiles;
+    w.maybe_no_light = plan.tiles;
 
     // (the allocation-free entry point records no profiling events: creating
     // them is a runtime allocation)
@@ -1627,9 +1551,9 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     pp.w = w;
     pp.step = Op::kU;
     pp.groups = Op::Gm::kP;
-    if (tiles) {
-        pp.win_flags = reinterpret_cast<uint8_t*>(ws + o_win);
-        pp.tile_min = tile_min;
+    if (plan.tiles) {
+        pp.win_flags = reinterpret_cast<uint8_t*>(ws + plan.o_win);
+        pp.tile_min = plan.tile_min;
     }
     if (alternate) pp.zero_next = cnt_base + ((cw.block.gen + 1u) & 1u) * kRowsSetWords;
     if ((he = launch_sort_rows(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
@@ -1639,7 +1563,7 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     }
     ph.mark(1, stream);  // the attention phase includes the tile kernel
     if constexpr (kTileShape) {
-        if (tiles) {
+        if (plan.tiles) {
             TileParams tp;
             tp.rowptr = a.rowptr;
             tp.colidx = a.colidx;
@@ -1651,7 +1575,7 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
             tp.N = a.N;
             tp.c = a.scale * 1.4426950408889634f;
             tp.light_max = w.light_max;
-            tp.min_entries = tile_min;
+            tp.min_entries = plan.tile_min;
             tp.win_flags = pp.win_flags;
             tp.counters = w.counters;
             if ((he = pick_tiles<D, KIND>(a.H, tp, stream)) != hipSuccess) return hip_fail(he, "tile launch");
@@ -1670,16 +1594,16 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     ap.slope = a.slope;
     ap.row_shift = floor_log2((uint64_t)a.H * D * Elt<T>::kBytes);
     ap.heads = a.H;
-    ap.part_ml = reinterpret_cast<float2*>(ws + o_ml);
-    ap.part_acc = reinterpret_cast<float*>(ws + o_acc);
+    ap.part_ml = reinterpret_cast<float2*>(ws + plan.o_ml);
+    ap.part_acc = reinterpret_cast<float*>(ws + plan.o_acc);
     ap.w.long_blocks = rg.long_blocks;
-    const int merge_grid = merge_blocks(sp, rule, device_cus(dev));
-    for (int s = 0; s < slices; s += sp.slices) {
+    const int merge_grid = merge_blocks(plan.slots, plan.rule, device_cus(dev));
+    for (int s = 0; s < slices; s += plan.slots.slices) {
         ap.slice0 = s;
-        hipLaunchKernelGGL((gt_attn_kernel<T, HS, D, KIND>), dim3(rg.blocks, sp.slices), dim3(kBlock), 0, stream, ap);
+        hipLaunchKernelGGL((gt_attn_kernel<T, HS, D, KIND>), dim3(rg.blocks, plan.slots.slices), dim3(kBlock), 0, stream, ap);
         if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "attention launch");
-        if (s + sp.slices >= slices) ph.mark(2, stream);
-        hipLaunchKernelGGL((gt_merge_kernel<T, HS, D>), dim3(merge_grid, sp.slices), dim3(kBlock), 0, stream, ap);
+        if (s + plan.slots.slices >= slices) ph.mark(2, stream);
+        hipLaunchKernelGGL((gt_merge_kernel<T, HS, D>), dim3(merge_grid, plan.slots.slices), dim3(kBlock), 0, stream, ap);
         if ((he = hipGetLastError()) != hipSuccess) return hip_fail(he, "merge launch");
     }
     ph.commit(stream);

@@ -6,6 +6,8 @@
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;
 constexpr int kXcds = 8;
+constexpr int kWinMaxDeg = 64;  // the tile path's rows have at most this degree
+constexpr int kDefaultTileMin = 256;
 constexpr size_t kScratchBytes = size_t(256) << 20;  // array of the allocation-free entry point
 
 constexpr int kClasses = 32;  // degree octaves
@@ -87,6 +89,26 @@ struct LongRow {
     uint32_t pad;
 };
 
+struct LightRow {
+    int32_t row;
+    uint32_t begin;
+};
+
+// Work-list counters, cleared by a fill kernel or by an earlier call's
+// partition.  Each sits on its own 128-byte line so that atomics on different
+// counters do not serialise on one cache line.
+//   0 .. 31: rows of each class;
+//   ROWS_OVERFLOW: set if a list capacity was exceeded (the CSR precondition was
+//     violated; the excess rows are dropped);
+//   ROWS_LIGHT: nonzero if the light-row order holds any row;
+//   ROWS_PIECES: lane groups that the long rows ask for, or more (a bound, by
+//     which a wave without long work ends after one load);
+//   ROWS_WIN: byte 0 nonzero if some window was found dense, byte 1 if some
+//     window was not (byte flags written with plain stores, read as one word).
+enum { ROWS_OVERFLOW = kClasses, ROWS_LIGHT, ROWS_WIN, ROWS_PIECES, ROWS_COUNT };
+constexpr int kRowsStride = 32;                         // ints between counters
+constexpr int kRowsSetWords = ROWS_COUNT * kRowsStride;  // one counter set
+
 // RowCut, before the room for partial states is known.
 struct RowRule {
     int32_t light_max;
@@ -141,6 +163,8 @@ RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_b
     }
     return r;
 }
+
+size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 int floor_log2(uint64_t x) { return 63 - __builtin_clzll(x); }
 
@@ -224,4 +248,112 @@ RowGrid row_grid(int64_t N, int64_t E, int groups, bool tiles, int resident, con
         rg.blocks = 2 * rg.long_blocks;
     }
     return rg;
+}
+
+// One call of the attention forward: its sizes and its row kernel.
+struct AttnShape {
+    int64_t N, E;
+    int32_t H, D;
+    int32_t elt_bytes;
+    int32_t slice_heads;  // heads of a slice
+    int32_t groups;       // lane groups per wavefront
+    bool gat;             // GATv2: one gathered row per entry, no tile path
+    bool sorted;          // the row kernel takes light rows in step order
+};
+
+// What the allocation-free entry point counts as a call's workspace, for its
+// documented limit: the row lists, and the partial states of rows cut into chunks
+// (of `chunk` entries, by default half the steps that the call's gathers take at
+// 7 TB/s and a microsecond per step, up to 1024 entries, or an eighth of them up
+// to 8192) for all heads at once.  Calls within the limit get a workspace within
+// it; the others are refused.
+size_t noalloc_need(const AttnShape& a, const gt_tuning* tu) {
+    const int row = a.H * a.D * a.elt_bytes, vecs = row / 16, lanes = vecs < kWave ? vecs : kWave;
+    const int rows = kWave / lanes, nv = vecs / lanes;
+    int u = 8 / nv > 2 ? 8 / nv : 2;
+    if (u > lanes) u = lanes;
+    const int64_t light = tu && tu->light_max_deg > 0 ? tu->light_max_deg : 8 * u;
+    const double steps = (double)a.E * (2.0 * row) / 7.0e12 / 1.0e-6;
+    const double entries = 0.5 * steps * (rows * (rows >= 4 && u >= 8 ? u / 2 : u));
+    auto whole = [](double x) { return ((int64_t)x + kWave - 1) / kWave * kWave; };
+    int64_t chunk = 0.25 * entries > 8192.0   ? 8192
+                    : 0.25 * entries > 1024.0 ? whole(0.25 * entries)
+                    : entries >= 1024.0       ? 1024
+                                              : whole(entries);
+    if (chunk < kWave) chunk = kWave;
+    int64_t heavy = rows >= 2 && chunk / 4 > 256 ? chunk / 4 : 256;
+    if (tu && tu->heavy_min_deg > 0) heavy = tu->heavy_min_deg;
+    if (tu && tu->chunk_edges > 0) chunk = whole(tu->chunk_edges);
+    if (heavy <= light) heavy = light + 1;
+    const size_t slots = 2 * (size_t)(a.E / chunk) + 1;
+    return (size_t)a.N * sizeof(int32_t) * (rows >= 4 ? 2 : 1) + 16 * ((size_t)(a.E / (chunk + 1)) + 1) +
+           24 * ((size_t)(a.E / heavy) + slots) + slots * a.H * (8 + a.D * 4);
+}
+
+// Rows, partial states and workspace of a call of the attention forward:
+// counters | light rows | window flags | long rows | partial (m,l) | partial acc.
+// The allocation-free entry point and the others get the same rows in the same
+// pieces, and so the same bits, wherever the former takes the call.
+struct AttnPlan {
+    size_t need;  // noalloc_need
+    RowRule rule;
+    SlotPlan slots;
+    bool tiles;   // the tile path takes light rows of dense windows
+    bool sorted;  // light rows in step order
+    int tile_min;
+    size_t o_light, o_deg, o_win, o_long, o_ml, o_acc, bytes;
+};
+
+AttnPlan plan_attn(const AttnShape& a, const gt_tuning* tu, bool noalloc) {
+    const int slice_bytes = a.slice_heads * a.D * a.elt_bytes, slices = a.H / a.slice_heads;
+    const int slot_bytes = a.slice_heads * (a.D * 4 + 8);
+    AttnPlan p;
+    p.rule = row_rule(a.N, a.E, slices, (a.gat ? 1 : 2) * slice_bytes, 3 * (2 * slot_bytes + 256) / 4, a.groups, tu);
+    // Dense-tile windows (bf16 rows of at most 256 bytes): on by default, for
+    // windows estimated to hold at least 256 in-window entries, which a 64-row
+    // block at half density holds about eight times over (measured on the SBM
+    // workload; on the R-MAT one no window qualifies and the tile kernel
+    // finds an empty list).
+    p.tile_min = tu && tu->dense_tiles != 0 ? tu->dense_tiles : kDefaultTileMin;  // < 0: off
+    const bool tile_rows = !a.gat && a.elt_bytes == 2 && a.H * a.D <= 128, tile_call = tile_rows && p.tile_min > 0;
+    // (the same light rows with the path off: a row that it streams has the same
+    // bits then)
+    if (tile_rows && !(tu && tu->light_max_deg > 0)) p.rule.light_max = kWinMaxDeg;
+    if (tile_call && p.rule.light_max > kWinMaxDeg) p.rule.light_max = kWinMaxDeg;
+
+    p.need = noalloc_need(a, tu);
+    const bool bounded = p.need <= kScratchBytes;
+    // Where the light rows' order would not fit the allocation-free entry point's
+    // array (more than 26 million nodes), that entry point takes them in id order
+    // (which changes no result) and neither has the tile path, which needs it.
+    const bool fits = !bounded || (size_t)a.N * (sizeof(LightRow) + 1) <= kScratchBytes / 16 * 14;
+    p.tiles = tile_call && fits;
+    p.sorted = a.sorted && (!noalloc || fits);
+    size_t off = align_up(2 * kRowsSetWords * sizeof(int32_t), 256);  // two counter sets
+    auto place = [&off](size_t bytes) {
+        const size_t at = off;
+        off = align_up(off + bytes, 256);
+        return at;
+    };
+    if (p.sorted && fits) {
+        p.o_light = place((size_t)a.N * sizeof(LightRow));
+        p.o_deg = place((size_t)a.N);
+    }
+    p.o_win = place(p.tiles ? (size_t)(a.N + kWave - 1) / kWave : 0);
+    // (a larger light bound makes the class lists shorter; the order above leaves
+    // room for none at the least)
+    while (bounded && p.rule.light_max < INT32_MAX &&
+           off + long_list_rows(a.N, a.E, p.rule.light_max) * sizeof(LongRow) + 4096 > kScratchBytes)
+        p.rule.light_max = p.rule.light_max < INT32_MAX / 2 ? 2 * p.rule.light_max + 1 : INT32_MAX;
+    p.o_long = place((size_t)long_list_rows(a.N, a.E, p.rule.light_max) * sizeof(LongRow));
+    p.slots = slot_plan(p.rule, slices, slot_bytes, off, bounded);
+    const size_t slots = (size_t)p.slots.cap * p.slots.slices;
+    p.o_ml = place(slots * a.slice_heads * 8);
+    p.o_acc = place(slots * a.slice_heads * a.D * 4);
+    if (!(p.sorted && fits)) {
+        p.o_light = place(p.sorted ? (size_t)a.N * sizeof(LightRow) : 0);
+        p.o_deg = place(p.sorted ? (size_t)a.N : 0);
+    }
+    p.bytes = off;
+    return p;
 }

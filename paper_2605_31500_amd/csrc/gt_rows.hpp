@@ -28,26 +28,8 @@
 // (a light row, a piece) is read by one lane group; pieces longer than
 // group_len are spread over the P groups of a wavefront and merged there.
 
-// Work-list counters, cleared by a fill kernel or by an earlier call's
-// partition.  Each sits on its own 128-byte line so that atomics on different
-// counters do not serialise on one cache line.
-//   0 .. 31: rows of each class;
-//   ROWS_OVERFLOW: set if a list capacity was exceeded (the CSR precondition was
-//     violated; the excess rows are dropped);
-//   ROWS_LIGHT: nonzero if the light-row order holds any row;
-//   ROWS_PIECES: lane groups that the long rows ask for, or more (a bound, by
-//     which a wave without long work ends after one load);
-//   ROWS_WIN: byte 0 nonzero if some window was found dense, byte 1 if some
-//     window was not (byte flags written with plain stores, read as one word).
-enum { ROWS_OVERFLOW = kClasses, ROWS_LIGHT, ROWS_WIN, ROWS_PIECES, ROWS_COUNT };
-constexpr int kRowsStride = 32;                         // ints between counters
-constexpr int kRowsSetWords = ROWS_COUNT * kRowsStride;  // one counter set
 #define ROWS_CNT(c, i) ((c)[(i) * kRowsStride])
 
-struct LightRow {
-    int32_t row;
-    uint32_t begin;
-};
 constexpr uint32_t kDegMany = 255;
 
 struct RowWork : RowCut {

@@ -51,4 +51,6 @@ void probe_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_by
     set_rule(*w, *r);
 }
 
+void probe_attn(const AttnShape* a, const gt_tuning* tu, int noalloc, AttnPlan* p) { *p = plan_attn(*a, tu, noalloc != 0); }
+
 }  // extern "C"

@@ -35,6 +35,22 @@ class RowRule(ctypes.Structure):
                 ("max_slots", ctypes.c_int64), ("forced", ctypes.c_bool)]
 
 
+class SlotPlan(ctypes.Structure):
+    _fields_ = [("cap", ctypes.c_uint32), ("slices", ctypes.c_int)]
+
+
+class AttnShape(ctypes.Structure):
+    _fields_ = [("N", ctypes.c_int64), ("E", ctypes.c_int64), ("H", ctypes.c_int32), ("D", ctypes.c_int32),
+                ("elt_bytes", ctypes.c_int32), ("slice_heads", ctypes.c_int32), ("groups", ctypes.c_int32),
+                ("gat", ctypes.c_bool), ("sorted", ctypes.c_bool)]
+
+
+class AttnPlan(ctypes.Structure):
+    _fields_ = [("need", ctypes.c_size_t), ("rule", RowRule), ("slots", SlotPlan), ("tiles", ctypes.c_bool),
+                ("sorted", ctypes.c_bool), ("tile_min", ctypes.c_int)] + [
+                    (f, ctypes.c_size_t) for f in ("o_light", "o_deg", "o_win", "o_long", "o_ml", "o_acc", "bytes")]
+
+
 @functools.lru_cache(maxsize=None)
 def probe():
     srcs = [os.path.join(ROOT, "tests", "plan_probe.cpp"), os.path.join(CSRC, "gt_plan.hpp"),
@@ -137,3 +153,77 @@ def test_largest_graphs_count_in_32_bits(P, light_max_deg):
             rows[c] = (cut.E >> c) if c > cut.min_class else cut.E // (cut.light_max + 1)
             bound, _, total = batches(cut, rows, P)
             assert int(total.max()) <= bound
+
+
+# ------------------------------------------------------------------------- the forward's plan
+
+SCRATCH = 256 << 20
+SHAPES = [(eb, H, D) for eb in (2, 4) for H in (1, 2, 4, 8) for D in (32, 64, 128, 256)] + [(2, H, 512) for H in (1, 2, 4)]
+
+
+def shape(N, E, eb, H, D, gat=False):
+    """The call's slices and row kernel: the heads of 256 bytes, or one; four lane groups or more per wavefront
+    (two for GATv2) take light rows in step order."""
+    heads = max(1, min(H, 256 // (D * eb)))
+    groups = 64 // (heads * D * eb // 16)
+    return AttnShape(N, E, H, D, eb, heads, groups, gat, groups >= (2 if gat else 4))
+
+
+def attn_plan(a, tuning=None, noalloc=False):
+    p = AttnPlan()
+    probe().probe_attn(ctypes.byref(a), ctypes.byref(tuning) if tuning else None, int(noalloc), ctypes.byref(p))
+    return p
+
+
+def cut_of(p):
+    """What decides the bits of a call's results."""
+    return [getattr(p.rule, f) for f, _ in RowRule._fields_] + [p.slots.cap, p.slots.slices, p.tiles]
+
+
+def in_order(p, a):
+    """The workspace's regions follow one another without overlap."""
+    rows = 9 if p.sorted else 0
+    size = {"o_light": 8 * a.N if rows else 0, "o_deg": a.N if rows else 0, "o_win": (a.N + 63) // 64 if p.tiles else 0,
+            "o_ml": p.slots.cap * p.slots.slices * a.slice_heads * 8,
+            "o_acc": p.slots.cap * p.slots.slices * a.slice_heads * a.D * 4}
+    lo = max(p.rule.light_max + 1, 1).bit_length() - 1
+    size["o_long"] = 16 * sum(min(a.E >> c, a.N) for c in range(lo, 31))
+    spans = sorted((getattr(p, k), getattr(p, k) + v) for k, v in size.items() if v) + [(p.bytes, p.bytes)]
+    return spans[0][0] >= 512 and all(x[1] <= y[0] for x, y in zip(spans, spans[1:]))
+
+
+@pytest.mark.parametrize("gat", [False, True])
+def test_plans_of_large_graphs_end_and_fit(gat):
+    """Up to 2^31 - 1 nodes and entries: the plan is found (the light bound that fits is), its regions are apart, the
+    allocation-free entry point's workspace lies within its array, and both entry points cut rows alike wherever
+    the former takes the call."""
+    rng = np.random.default_rng(11 + gat)
+    bounded = 0
+    for _ in range(20000):
+        eb, H, D = SHAPES[rng.integers(len(SHAPES))]
+        N = int(np.exp(rng.uniform(np.log(1 << (10 if rng.random() < 0.3 else 23)), np.log((1 << 31) - 1))))
+        if rng.random() < 0.4:
+            N = int(rng.integers(25_000_000, 34_000_000))  # around where the light rows' order fills the array
+        E = int(min(N * np.exp(rng.uniform(np.log(0.01), np.log(200))), (1 << 31) - 1))
+        t = None
+        if rng.random() < 0.3:
+            t = Tuning(light_max_deg=int(rng.choice([0, 1, 300, 2**31 - 2**16])), dense_tiles=int(rng.choice([0, 1, -1])),
+                       heavy_min_deg=int(rng.choice([0, 1, 5000])), chunk_edges=int(rng.choice([0, 64, 10**6])))
+        a = shape(N, E, eb, H, D, gat)
+        p = attn_plan(a, t)
+        assert in_order(p, a), (N, E, eb, H, D)
+        assert p.rule.light_max >= 1
+        if p.need <= SCRATCH:
+            q = attn_plan(a, t, noalloc=True)
+            assert q.bytes <= SCRATCH and in_order(q, a), (N, E, eb, H, D)
+            assert cut_of(p) == cut_of(q), (N, E, eb, H, D)
+            bounded += 1
+    assert bounded > 2000
+
+
+@pytest.mark.parametrize("eb,H,D,N,E", [(2, 1, 32, 31_000_000, 31_000_000), (4, 4, 32, 31_000_000, 200_000_000)])
+def test_plans_around_thirty_million_nodes_end(eb, H, D, N, E):
+    a = shape(N, E, eb, H, D)
+    p, q = attn_plan(a), attn_plan(a, noalloc=True)
+    assert p.need <= SCRATCH and q.bytes <= SCRATCH and cut_of(p) == cut_of(q)
+    assert p.sorted and not q.sorted
