@@ -262,12 +262,13 @@ struct AttnShape {
 };
 
 // What the allocation-free entry point counts as a call's workspace, for its
-// documented limit: the row lists, and the partial states of rows cut into chunks
-// (of `chunk` entries, by default half the steps that the call's gathers take at
-// 7 TB/s and a microsecond per step, up to 1024 entries, or an eighth of them up
-// to 8192) for all heads at once.  Calls within the limit get a workspace within
-// it; the others are refused.
-size_t noalloc_need(const AttnShape& a, const gt_tuning* tu) {
+// documented limit: two counter sets, a list of all rows (two where a wavefront
+// holds four rows or more), the lists and partial states of rows of `heavy` entries
+// or more cut into chunks (of `chunk` entries, by default half the steps that the
+// call's gathers take at 7 TB/s and a microsecond per step, up to 1024 entries, or
+// an eighth of them up to 8192) for all heads at once, and the windows of the tile
+// path.  Calls within the limit get a workspace within it; the others are refused.
+size_t noalloc_need(const AttnShape& a, bool tiles, const gt_tuning* tu) {
     const int row = a.H * a.D * a.elt_bytes, vecs = row / 16, lanes = vecs < kWave ? vecs : kWave;
     const int rows = kWave / lanes, nv = vecs / lanes;
     int u = 8 / nv > 2 ? 8 / nv : 2;
@@ -286,8 +287,17 @@ size_t noalloc_need(const AttnShape& a, const gt_tuning* tu) {
     if (tu && tu->chunk_edges > 0) chunk = whole(tu->chunk_edges);
     if (heavy <= light) heavy = light + 1;
     const size_t slots = 2 * (size_t)(a.E / chunk) + 1;
-    return (size_t)a.N * sizeof(int32_t) * (rows >= 4 ? 2 : 1) + 16 * ((size_t)(a.E / (chunk + 1)) + 1) +
-           24 * ((size_t)(a.E / heavy) + slots) + slots * a.H * (8 + a.D * 4);
+    const size_t parts[] = {3584,
+                            (size_t)a.N * 4,
+                            16 * ((size_t)(a.E / (chunk + 1)) + 1),
+                            24 * ((size_t)(a.E / heavy) + slots),
+                            slots * a.H * 8,
+                            slots * a.H * a.D * 4,
+                            rows >= 4 ? (size_t)a.N * 4 : 0,
+                            tiles ? (size_t)(a.N + kWave - 1) / kWave : 0};
+    size_t need = 0;
+    for (const size_t bytes : parts) need = align_up(need + bytes, 256);
+    return need;
 }
 
 // Rows, partial states and workspace of a call of the attention forward:
@@ -321,7 +331,7 @@ AttnPlan plan_attn(const AttnShape& a, const gt_tuning* tu, bool noalloc) {
     if (tile_rows && !(tu && tu->light_max_deg > 0)) p.rule.light_max = kWinMaxDeg;
     if (tile_call && p.rule.light_max > kWinMaxDeg) p.rule.light_max = kWinMaxDeg;
 
-    p.need = noalloc_need(a, tu);
+    p.need = noalloc_need(a, tile_call, tu);
     const bool bounded = p.need <= kScratchBytes;
     // Where the light rows' order would not fit the allocation-free entry point's
     // array (more than 26 million nodes), that entry point takes them in id order

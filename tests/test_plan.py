@@ -227,3 +227,15 @@ def test_plans_around_thirty_million_nodes_end(eb, H, D, N, E):
     p, q = attn_plan(a), attn_plan(a, noalloc=True)
     assert p.need <= SCRATCH and q.bytes <= SCRATCH and cut_of(p) == cut_of(q)
     assert p.sorted and not q.sorted
+
+
+def test_allocation_free_limit():
+    """What the entry point counts against its array, to the byte (from the layout that its limit was first stated
+    for): two counter sets, the row lists, the chunks and their states, the window flags, each in whole 256 bytes."""
+    t, c = Tuning(light_max_deg=300), Tuning(chunk_edges=64, heavy_min_deg=100)
+    for eb, H, D, N, E, tuning, need in [(2, 1, 32, 33_553_000, 1000, None, 268957696), (4, 4, 32, 1 << 21, 50_000_000, None, 16009728),
+                                         (2, 2, 64, 1 << 20, 36_000_000, t, 16650496),
+                                         (4, 4, 32, 100_000, 20_000_000, c, 365127680), (2, 4, 512, 1000, 900_000, None, 14598144)]:
+        assert attn_plan(shape(N, E, eb, H, D), tuning).need == need
+    # the least that is refused with 1x32 bf16 features and next to no entries
+    assert attn_plan(shape(33_487_872, 1000, 2, 1, 32)).need <= SCRATCH < attn_plan(shape(33_487_873, 1000, 2, 1, 32)).need
