@@ -147,10 +147,11 @@ gt_status gt_attn_fwd_bf16(const int64_t* rowptr, const int32_t* colidx, const u
  *                   turns the path off.  Rows are grouped in aligned windows
  *                   of 64 ids.  The partition estimates each window's
  *                   entries that point inside the window from a sample (the
- *                   middle entry of every 8th light row) and lists the
- *                   windows estimated to hold at least `dense_tiles` of them
- *                   (with 1: every window with a light row).  The light rows
- *                   of a listed window are computed by the tile kernel: their
+ *                   middle entry of every 8th light row of at most 64 entries)
+ *                   and lists the windows estimated to hold at least
+ *                   `dense_tiles` of them (with 1: every window with such a
+ *                   row).  The light rows of at most 64 entries of a listed
+ *                   window are computed by the tile kernel: their
  *                   in-window entries as masked 64x64 tiles with bf16 MFMA
  *                   (scores and P*V), then each row's remaining entries
  *                   streamed; all other rows by the CSR kernel.  The

@@ -658,7 +658,7 @@ struct TileParams {
     float* lse;
     int64_t N;
     float c;  // scale * log2(e)
-    int32_t light_max;  // <= kWinMaxDeg
+    int32_t tile_max;  // <= kWinMaxDeg
     int32_t min_entries;
     const uint8_t* win_flags;  // [ceil(N / 64)]: 1 for the dense windows the partition found
     const int32_t* counters;   // ROWS_WIN: any window dense (byte 0) / not dense (byte 1)
@@ -803,8 +803,8 @@ gt_tile_kernel(TileParams p) {
     // come straight from colidx (one batch of independent loads, behind the
     // staging loads); the remaining-entry stream reads them again later, so
     // the window needs no LDS copy of its entries.
-    const bool light = r < p.N && (me - mb) <= p.light_max;
-    constexpr int kMaskPer = kWinMaxDeg / 4;  // entries per lane (light_max <= kWinMaxDeg)
+    const bool light = r < p.N && (me - mb) <= p.tile_max;
+    constexpr int kMaskPer = kWinMaxDeg / 4;  // entries per lane (tile_max <= kWinMaxDeg)
     int32_t ent[kMaskPer] = {};
     if (light && me > mb) {
 #pragma unroll
@@ -1554,6 +1554,7 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     if (plan.tiles) {
         pp.win_flags = reinterpret_cast<uint8_t*>(ws + plan.o_win);
         pp.tile_min = plan.tile_min;
+        pp.tile_max = plan.tile_max;
     }
     if (alternate) pp.zero_next = cnt_base + ((cw.block.gen + 1u) & 1u) * kRowsSetWords;
     if ((he = launch_sort_rows(pp, stream)) != hipSuccess) return hip_fail(he, "partition launch");
@@ -1574,7 +1575,7 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
             tp.lse = a.lse;
             tp.N = a.N;
             tp.c = a.scale * 1.4426950408889634f;
-            tp.light_max = w.light_max;
+            tp.tile_max = plan.tile_max;
             tp.min_entries = plan.tile_min;
             tp.win_flags = pp.win_flags;
             tp.counters = w.counters;

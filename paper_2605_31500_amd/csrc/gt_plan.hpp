@@ -311,6 +311,7 @@ struct AttnPlan {
     bool tiles;   // the tile path takes light rows of dense windows
     bool sorted;  // light rows in step order
     int tile_min;
+    int32_t tile_max;  // the tile path's rows have at most this degree; other light rows stay with the row kernel
     size_t o_light, o_deg, o_win, o_long, o_ml, o_acc, bytes;
 };
 
@@ -329,7 +330,6 @@ AttnPlan plan_attn(const AttnShape& a, const gt_tuning* tu, bool noalloc) {
     // (the same light rows with the path off: a row that it streams has the same
     // bits then)
     if (tile_rows && !(tu && tu->light_max_deg > 0)) p.rule.light_max = kWinMaxDeg;
-    if (tile_call && p.rule.light_max > kWinMaxDeg) p.rule.light_max = kWinMaxDeg;
 
     p.need = noalloc_need(a, tile_call, tu);
     const bool bounded = p.need <= kScratchBytes;
@@ -355,6 +355,7 @@ AttnPlan plan_attn(const AttnShape& a, const gt_tuning* tu, bool noalloc) {
     while (bounded && p.rule.light_max < INT32_MAX &&
            off + long_list_rows(a.N, a.E, p.rule.light_max) * sizeof(LongRow) + 4096 > kScratchBytes)
         p.rule.light_max = p.rule.light_max < INT32_MAX / 2 ? 2 * p.rule.light_max + 1 : INT32_MAX;
+    p.tile_max = p.rule.light_max < kWinMaxDeg ? p.rule.light_max : kWinMaxDeg;
     p.o_long = place((size_t)long_list_rows(a.N, a.E, p.rule.light_max) * sizeof(LongRow));
     p.slots = slot_plan(p.rule, slices, slot_bytes, off, bounded);
     const size_t slots = (size_t)p.slots.cap * p.slots.slices;

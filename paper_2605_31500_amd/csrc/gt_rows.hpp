@@ -312,11 +312,12 @@ struct SortParams {
     int32_t step = 1;      // entries per step of the light rows (their step classes)
     uint32_t groups = 1;  // lane groups per wavefront
     // Dense-tile windows (win_flags != nullptr): aligned 64-row windows whose
-    // light rows are estimated to hold >= tile_min entries inside the window
-    // are flagged for the tile kernel, and their light rows left out of the
-    // light-row order.  The estimate reads one entry of every 8th light row.
+    // rows of at most tile_max entries are estimated to hold >= tile_min of them
+    // inside the window are flagged for the tile kernel, and those rows left out
+    // of the light-row order.  The estimate reads one entry of every 8th of them.
     uint8_t* win_flags = nullptr;  // [ceil(N / 64)]
     int32_t tile_min = 0;
+    int32_t tile_max = 0;  // <= kWinMaxDeg and light_max
     // the workspace's other counter set, zeroed by block 0 for the next call
     // that takes this workspace (nullptr: none)
     int32_t* zero_next = nullptr;
@@ -361,13 +362,13 @@ __global__ void __launch_bounds__(kBlock) gt_sort_rows_kernel(SortParams p) {
         }
     }
     // Dense-tile windows.  In iteration k, wave wv holds the 64 rows of one
-    // aligned window (r0 is a multiple of 1024).  The window's light rows hold
-    // ld entries; every 8th light row contributes its middle entry as a
-    // sample, and the in-window share of the sampled rows' entries (self-loops
-    // not counted) estimates the window's in-window entries (the tile kernel
-    // counts them exactly and still streams a window that falls short).  A dense
-    // window's light rows belong to the tile kernel (tiled), all others stay on
-    // this path.
+    // aligned window (r0 is a multiple of 1024).  The window's rows of at most
+    // tile_max entries hold ld of them; every 8th such row contributes its middle
+    // entry as a sample, and the in-window share of the sampled rows' entries
+    // (self-loops not counted) estimates the window's in-window entries (the tile
+    // kernel counts them exactly and still streams a window that falls short).  A
+    // dense window's rows of at most tile_max entries belong to the tile kernel
+    // (tiled), all others stay on this path.
     bool tiled[RPT];
 #pragma unroll
     for (int k = 0; k < RPT; ++k) tiled[k] = false;
@@ -376,13 +377,13 @@ __global__ void __launch_bounds__(kBlock) gt_sort_rows_kernel(SortParams p) {
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
             smp[k] = -1;
-            if (deg[k] > 0 && deg[k] <= w.light_max && (lane & 7) == 0) smp[k] = w.colidx[rb[k] + deg[k] / 2];
+            if (deg[k] > 0 && deg[k] <= p.tile_max && (lane & 7) == 0) smp[k] = w.colidx[rb[k] + deg[k] / 2];
         }
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
             const int64_t r = r0 + k * kBlock + threadIdx.x;
-            const bool lt = deg[k] >= 0 && deg[k] <= w.light_max;
-            // light degrees are <= 64, so a window's sums fit: ld <= 4096 and
+            const bool lt = deg[k] >= 0 && deg[k] <= p.tile_max;
+            // these degrees are <= 64, so a window's sums fit: ld <= 4096 and
             // the sampled sums (8 rows) <= 512, packed two to a word
             const int ld = wave_sum_i32(lt ? (int)deg[k] : 0);
             // a sampled self-loop does not count: every row has at most one,

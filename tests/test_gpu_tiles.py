@@ -55,6 +55,26 @@ def check(rowptr, colidx, Q, K, V, scale, tiles, rows=None):
     return got
 
 
+@pytest.mark.parametrize("light_max_deg", [64, 65, 129, 200])
+@pytest.mark.parametrize("H,D", [(1, 32), (4, 32), (1, 128)])
+def test_light_rows_longer_than_the_tile_path_takes(H, D, light_max_deg):
+    """Dense windows that also hold rows of 60 to 210 entries: with a light bound above 64 these are light rows, but
+    not the tile path's (it reads 64 entries of a row)."""
+    N = 64 * 9 + 11
+    rp, ci = synth.sbm_graph(H + D, N, 64, 4)
+    rows = [list(ci[rp[i]:rp[i + 1]]) for i in range(N)]
+    u = np.floor(synth.uniform01(H + D, synth.STREAM_EXTRA + 4, 210 * N) * N).astype(np.int64).reshape(N, 210)
+    for n, i in enumerate(range(0, N, 5)):
+        length = (60, 64, 65, 66, 100, 129, 130, 200, 201, 210)[n % 10]
+        rows[i] = rows[i] + list(u[i][:length - len(rows[i])])
+    rowptr, colidx = csr_from_rows(rows)
+    Q, K, V = synth.features(7 * H + D, N, H, D, "bf16")
+    scale = np.float32(1 / math.sqrt(D))
+    got = run_gpu(rowptr, colidx, Q, K, V, scale, tuning={"dense_tiles": 1, "light_max_deg": light_max_deg})
+    ref, absagg, _ = oracle.gt_attn_fwd(rowptr, colidx, Q, K, V, scale, want_lse=False)
+    assert gate_error(got, ref, absagg) <= TOL_BF16
+
+
 @pytest.mark.parametrize("H,D", TILE_SHAPES)
 def test_tiles_irregular(H, D):
     rowptr, colidx = irregular_block_graph(H * 100 + D)

@@ -47,7 +47,7 @@ class AttnShape(ctypes.Structure):
 
 class AttnPlan(ctypes.Structure):
     _fields_ = [("need", ctypes.c_size_t), ("rule", RowRule), ("slots", SlotPlan), ("tiles", ctypes.c_bool),
-                ("sorted", ctypes.c_bool), ("tile_min", ctypes.c_int)] + [
+                ("sorted", ctypes.c_bool), ("tile_min", ctypes.c_int), ("tile_max", ctypes.c_int32)] + [
                     (f, ctypes.c_size_t) for f in ("o_light", "o_deg", "o_win", "o_long", "o_ml", "o_acc", "bytes")]
 
 
@@ -212,7 +212,7 @@ def test_plans_of_large_graphs_end_and_fit(gat):
         a = shape(N, E, eb, H, D, gat)
         p = attn_plan(a, t)
         assert in_order(p, a), (N, E, eb, H, D)
-        assert p.rule.light_max >= 1
+        assert p.rule.light_max >= 1 and (not p.tiles or p.tile_max <= min(64, p.rule.light_max))
         if p.need <= SCRATCH:
             q = attn_plan(a, t, noalloc=True)
             assert q.bytes <= SCRATCH and in_order(q, a), (N, E, eb, H, D)
@@ -227,6 +227,12 @@ def test_plans_around_thirty_million_nodes_end(eb, H, D, N, E):
     p, q = attn_plan(a), attn_plan(a, noalloc=True)
     assert p.need <= SCRATCH and q.bytes <= SCRATCH and cut_of(p) == cut_of(q)
     assert p.sorted and not q.sorted
+
+
+def test_tile_rows_stay_short_where_the_light_bound_is_raised():
+    """700 M entries: the class lists fit the array from a light bound of 129 on; the tile path's rows hold 64."""
+    p = attn_plan(shape(8_000_000, 700_000_000, 2, 4, 32))
+    assert p.need <= SCRATCH and p.tiles and p.rule.light_max > 64 and p.tile_max == 64
 
 
 def test_allocation_free_limit():
