@@ -36,8 +36,10 @@
  * A call works on the calling thread's current device: `stream` (0 for the
  * null stream) must belong to it, else GT_ERROR_INVALID_VALUE.
  * `out` must not overlap Q, K or V.  Q, K, V and out must be 16-byte aligned.
- * Workspace (the lists of long and light rows, partial softmax states of split
- * rows and the work-list counters; up to 256 MiB by default) is owned
+ * Workspace (the lists of long and light rows, up to about 9 bytes per node and
+ * one per entry; in the backward 8 bytes per node and head; partial softmax states
+ * of split rows, with default tuning what is left of 256 MiB or 128 MiB; and the
+ * work-list counters) is owned
  * by the library and private to each call while its kernels run: a call
  * takes a free workspace block of the device and, after enqueueing its
  * kernels, hands it back tagged with an event recorded on `stream`.  A later

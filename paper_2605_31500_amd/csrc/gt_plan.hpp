@@ -187,20 +187,26 @@ void set_rule(RowCut& w, const RowRule& r) {
 
 // Partial states and slices per launch.  Where the states of all slices fit
 // kSlicesTogether bytes, the slices share a launch (and a merge); larger calls
-// launch one slice at a time, which reuses the states' memory, up to the
-// workspace of the allocation-free entry point.
+// launch one slice at a time, which reuses the states' memory.
 struct SlotPlan {
     uint32_t cap;
     int slices;  // per launch
 };
 constexpr size_t kSlicesTogether = size_t(192) << 20;
+constexpr size_t kStatesLeast = size_t(128) << 20;    // of calls with a workspace of their own
+constexpr size_t kBoundedStates = size_t(24) << 20;  // of calls that fit the allocation-free entry point
 
-// `bounded`: the call's workspace has to fit the allocation-free entry point.
+// `bounded`: the call's workspace has to fit the allocation-free entry point's
+// array.  The states of the others may fill up a workspace of that size too, and
+// get kStatesLeast however much its lists and statistics take: the longest rows
+// come first, and so many of them keep the device busy (R-MAT scale 20 bf16 4x32
+// backward, all classes in full: 224 MiB).
 SlotPlan slot_plan(const RowRule& r, int slices, size_t slot_bytes, size_t other_bytes, bool bounded) {
     SlotPlan s;
     s.slices = slices;
     s.cap = (uint32_t)r.max_slots;
-    const size_t room = (other_bytes + 1024 < kScratchBytes ? kScratchBytes - other_bytes - 1024 : 0) / slot_bytes;
+    const size_t left = other_bytes + 1024 < kScratchBytes ? kScratchBytes - other_bytes - 1024 : 0;
+    const size_t room = (bounded || left > kStatesLeast ? left : kStatesLeast) / slot_bytes;
     const size_t all = kSlicesTogether / (slot_bytes * slices);
     if (!r.forced) {
         // (a quarter of the most is enough for most graphs; where it is not,
@@ -332,7 +338,7 @@ AttnPlan plan_attn(const AttnShape& a, const gt_tuning* tu, bool noalloc) {
     if (tile_rows && !(tu && tu->light_max_deg > 0)) p.rule.light_max = kWinMaxDeg;
 
     p.need = noalloc_need(a, tile_call, tu);
-    const bool bounded = p.need <= kScratchBytes;
+    const bool bounded = !a.gat && p.need <= kScratchBytes;
     // Where the light rows' order would not fit the allocation-free entry point's
     // array (more than 26 million nodes), that entry point takes them in id order
     // (which changes no result) and neither has the tile path, which needs it.
@@ -351,9 +357,9 @@ AttnPlan plan_attn(const AttnShape& a, const gt_tuning* tu, bool noalloc) {
     }
     p.o_win = place(p.tiles ? (size_t)(a.N + kWave - 1) / kWave : 0);
     // (a larger light bound makes the class lists shorter; the order above leaves
-    // room for none at the least)
+    // room for none and for kBoundedStates at the least)
     while (bounded && p.rule.light_max < INT32_MAX &&
-           off + long_list_rows(a.N, a.E, p.rule.light_max) * sizeof(LongRow) + 4096 > kScratchBytes)
+           off + long_list_rows(a.N, a.E, p.rule.light_max) * sizeof(LongRow) + kBoundedStates > kScratchBytes)
         p.rule.light_max = p.rule.light_max < INT32_MAX / 2 ? 2 * p.rule.light_max + 1 : INT32_MAX;
     p.tile_max = p.rule.light_max < kWinMaxDeg ? p.rule.light_max : kWinMaxDeg;
     p.o_long = place((size_t)long_list_rows(a.N, a.E, p.rule.light_max) * sizeof(LongRow));

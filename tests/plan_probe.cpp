@@ -53,4 +53,8 @@ void probe_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_by
 
 void probe_attn(const AttnShape* a, const gt_tuning* tu, int noalloc, AttnPlan* p) { *p = plan_attn(*a, tu, noalloc != 0); }
 
+void probe_slots(const RowRule* r, int slices, int64_t slot_bytes, int64_t other_bytes, int bounded, SlotPlan* s) {
+    *s = slot_plan(*r, slices, (size_t)slot_bytes, (size_t)other_bytes, bounded != 0);
+}
+
 }  // extern "C"

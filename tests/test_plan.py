@@ -213,12 +213,17 @@ def test_plans_of_large_graphs_end_and_fit(gat):
         p = attn_plan(a, t)
         assert in_order(p, a), (N, E, eb, H, D)
         assert p.rule.light_max >= 1 and (not p.tiles or p.tile_max <= min(64, p.rule.light_max))
-        if p.need <= SCRATCH:
+        states = p.slots.cap * p.slots.slices
+        if p.need <= SCRATCH and not gat:
+            # room for the longest rows' states, within the array
+            assert states >= min(p.rule.max_slots, (23 << 20) // (a.slice_heads * (4 * D + 8)))
             q = attn_plan(a, t, noalloc=True)
             assert q.bytes <= SCRATCH and in_order(q, a), (N, E, eb, H, D)
             assert cut_of(p) == cut_of(q), (N, E, eb, H, D)
             bounded += 1
-    assert bounded > 2000
+        else:
+            assert states >= min(p.rule.max_slots, (128 << 20) // (a.slice_heads * (4 * D + 8)) - H)
+    assert gat or bounded > 2000
 
 
 @pytest.mark.parametrize("eb,H,D,N,E", [(2, 1, 32, 31_000_000, 31_000_000), (4, 4, 32, 31_000_000, 200_000_000)])
@@ -227,6 +232,18 @@ def test_plans_around_thirty_million_nodes_end(eb, H, D, N, E):
     p, q = attn_plan(a), attn_plan(a, noalloc=True)
     assert p.need <= SCRATCH and q.bytes <= SCRATCH and cut_of(p) == cut_of(q)
     assert p.sorted and not q.sorted
+
+
+def test_rows_are_cut_however_large_the_lists_and_statistics_are():
+    """The states of a call with a workspace of its own do not depend on what else is in it: backward of 8 heads of 64
+    fp32 features on 4 M nodes (268 MB of statistics), and a reduction over 40 M nodes."""
+    for N, E, slices, gather, piece, P, slot, other in [
+            (4_000_000, 96_000_000, 8, 512, 2048, 4, 512, 4_000_000 * (8 * 8 + 9) + 96_000_000 // 4),
+            (40_000_000, 1_500_000_000, 2, 256, 3264, 4, 1024, 40_000_000 * 9 + 1_500_000_000)]:
+        _, r = rule(N, E, slices, gather, piece, P)
+        s = SlotPlan()
+        probe().probe_slots(ctypes.byref(r), slices, ctypes.c_int64(slot), ctypes.c_int64(other), 0, ctypes.byref(s))
+        assert s.cap * s.slices * slot >= min(r.max_slots * slot, 127 << 20)
 
 
 def test_tile_rows_stay_short_where_the_light_bound_is_raised():
