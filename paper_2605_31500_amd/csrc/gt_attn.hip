@@ -1513,7 +1513,7 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     int dev = 0;
     if (const gt_status ds = call_device(stream, &dev); ds != GT_SUCCESS) return ds;
     hipError_t he = hipSuccess;
-    const RowGrid rg = row_grid(a.N, a.E, Op::Gm::kP, plan.tiles, attn_resident<T, HS, D, KIND>(dev), tu);
+    const RowGrid rg = row_grid(a.N, a.E, Op::Gm::kP, plan.slots.slices, plan.tiles, attn_resident<T, HS, D, KIND>(dev), tu);
 
     RowWork w;
     w.rowptr = a.rowptr;

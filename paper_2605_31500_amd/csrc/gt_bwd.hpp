@@ -365,7 +365,7 @@ template <typename T, int HS, int D, int MODE>
 gt_status launch_bwd_pass(BwdParams bp, const RowRule& rule, const SlotPlan& sp, int dev, hipStream_t stream) {
     using Op = BwdOp<T, HS, D, MODE>;
     hipError_t he = hipSuccess;
-    const RowGrid rg = row_grid(bp.w.N, bp.w.E, Op::Gm::kP, false, bwd_resident<T, HS, D, MODE>(dev), nullptr);
+    const RowGrid rg = row_grid(bp.w.N, bp.w.E, Op::Gm::kP, sp.slices, false, bwd_resident<T, HS, D, MODE>(dev), nullptr);
     bp.w.long_blocks = rg.long_blocks;
     SortParams pp;
     pp.w = bp.w;

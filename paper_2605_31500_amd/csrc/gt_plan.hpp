@@ -229,26 +229,34 @@ int merge_blocks(const SlotPlan& sp, const RowRule& r, int cus) {
     return (int)(g < cus * 8 ? g : cus * 8);
 }
 
-// Workgroups of a row kernel for one slice.  Light rows: two batches (a row per
-// lane group) per wave, four where the tile path may take them all; many more
-// waves than the device holds, so that the hardware scheduler evens out the
-// per-wave work (1, 2, 4 and 8 batches: R-MAT scale 21 fp32 4x32 5.08, 5.11, 5.33
-// and 5.77 ms).  Long rows: one batch per wave if three quarters of all entries lie
-// in pieces of 64, up to eight times the workgroups the device holds at once (a
-// wave without a batch still costs its prologue).
+// Workgroups of a row kernel for one of the `slices` of a launch.  Light rows: one
+// batch (a row per lane group) per wave while that is at most four times the
+// workgroups that the device holds at once, two beyond (four where the tile path
+// may take the rows): many more waves than it holds, so that the hardware scheduler
+// evens out the per-wave work, but where they are few a second batch only makes
+// the chain longer (one / two batches, us per call: 30 K nodes of degree 26 bf16
+// 1x32 25 / 39, 12 K of degree 40 fp32 8x64 100 / 144; 286 K R-MAT nodes GATv2 fp32
+// 8x32 498 / 469; 1, 2, 4 and 8 on R-MAT scale 21 fp32 4x32 5080, 5110, 5330, 5770).
+// Long rows: a wave per 128 entries if three quarters of all lie in them, up to
+// eight times what the device holds (a wave without a batch still costs its
+// prologue; a wave per 64 entries of each lane group left rows of 65 to 255
+// entries, a wavefront each, queueing up: 16 K nodes of a power law bf16 1x64 31.8
+// -> 26.6, R-MAT of 16 K nodes fp32 4x32 37.4 -> 32.9).
 struct RowGrid {
     uint32_t blocks, long_blocks;
 };
-RowGrid row_grid(int64_t N, int64_t E, int groups, bool tiles, int resident, const gt_tuning* tu) {
+RowGrid row_grid(int64_t N, int64_t E, int groups, int slices, bool tiles, int resident, const gt_tuning* tu) {
     auto blocks = [](int64_t batches, int64_t per_wave) {
         const int64_t g = (batches + per_wave * kWavesPerBlock - 1) / (per_wave * kWavesPerBlock);
         return (uint32_t)((g + kXcds - 1) / kXcds * kXcds);
     };
     RowGrid rg;
-    rg.long_blocks = blocks(3 * (E / 4) / ((int64_t)groups * 64) + 1, 1);
+    const int64_t batches = (N + groups - 1) / groups;
+    const bool few = (int64_t)blocks(batches, 1) * slices <= 4 * (int64_t)resident;
+    rg.long_blocks = blocks(3 * (E / 4) / (groups < 2 ? 64 : 128) + 1, 1);
     const uint32_t most = (uint32_t)(tiles ? 2 : 8) * (uint32_t)resident / kXcds * kXcds;
     if (rg.long_blocks > most) rg.long_blocks = most;
-    rg.blocks = rg.long_blocks + blocks((N + groups - 1) / groups, tiles ? 4 : 2);
+    rg.blocks = rg.long_blocks + blocks(batches, few ? 1 : tiles ? 4 : 2);
     if (tu && tu->grid_blocks > 0) {
         rg.long_blocks = blocks(((int64_t)tu->grid_blocks + 1) / 2 * kWavesPerBlock, 1);
         rg.blocks = 2 * rg.long_blocks;

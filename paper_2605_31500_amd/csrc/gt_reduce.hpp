@@ -255,7 +255,6 @@ gt_status launch_reduce(const ReduceArgs& a, const gt_tuning* tu, hipStream_t st
     int dev = 0;
     if (const gt_status ds = call_device(stream, &dev); ds != GT_SUCCESS) return ds;
     hipError_t he = hipSuccess;
-    const RowGrid rg = row_grid(a.N, a.E, kWave / NVEC, false, reduce_resident<T, NVEC>(dev), tu);
 
     // workspace: counters | light rows | long rows | partial words
     RowWork w;
@@ -271,6 +270,7 @@ gt_status launch_reduce(const ReduceArgs& a, const gt_tuning* tu, hipStream_t st
     const size_t o_long = off;
     off = align_up(off + (size_t)long_list_rows(a.N, a.E, w.light_max) * sizeof(LongRow), 256);
     const SlotPlan sp = slot_plan(rule, slices, kSlotBytes, off, false);
+    const RowGrid rg = row_grid(a.N, a.E, kWave / NVEC, sp.slices, false, reduce_resident<T, NVEC>(dev), tu);
     w.cap_slots = sp.cap;
     const size_t o_part = off;   off = align_up(off + (size_t)sp.cap * sp.slices * kSlotBytes, 256);
 

@@ -57,4 +57,8 @@ void probe_slots(const RowRule* r, int slices, int64_t slot_bytes, int64_t other
     *s = slot_plan(*r, slices, (size_t)slot_bytes, (size_t)other_bytes, bounded != 0);
 }
 
+void probe_grid(int64_t N, int64_t E, int groups, int slices, int tiles, int resident, const gt_tuning* tu, RowGrid* g) {
+    *g = row_grid(N, E, groups, slices, tiles != 0, resident, tu);
+}
+
 }  // extern "C"

@@ -262,3 +262,37 @@ def test_allocation_free_limit():
         assert attn_plan(shape(N, E, eb, H, D), tuning).need == need
     # the least that is refused with 1x32 bf16 features and next to no entries
     assert attn_plan(shape(33_487_872, 1000, 2, 1, 32)).need <= SCRATCH < attn_plan(shape(33_487_873, 1000, 2, 1, 32)).need
+
+
+# ------------------------------------------------------------------------- grids
+
+
+def grid(N, E, groups, slices, tiles=False, resident=1024, tuning=None):
+    g = (ctypes.c_uint32 * 2)()
+    probe().probe_grid(ctypes.c_int64(N), ctypes.c_int64(E), groups, slices, int(tiles), resident,
+                       ctypes.byref(tuning) if tuning else None, ctypes.byref(g))
+    return g[0], g[1]  # workgroups of a slice, and those of them that take long rows
+
+
+@pytest.mark.parametrize("tiles", [False, True])
+@pytest.mark.parametrize("groups,slices", [(1, 4), (2, 2), (4, 1), (4, 8), (8, 1), (16, 1)])
+def test_a_batch_per_wave_until_the_device_is_full(groups, slices, tiles):
+    """Four waves per workgroup, whole eighths of a grid: a call whose light rows take up to four times the resident
+    workgroups with one batch per wave gets that many; larger ones get two batches (four) per wave."""
+    for N in (1, 63, 2000, 5003, 4 * 1024 * 4 * groups // slices - 4 * 8 * groups, 2_000_001):
+        blocks, long_blocks = grid(N, 8 * N, groups, slices, tiles)
+        batches = -(-N // groups)
+        light = blocks - long_blocks
+        assert blocks % 8 == 0 and long_blocks % 8 == 0 and long_blocks >= 8
+        few = -(-batches // 4) * slices <= 4 * 1024 - 8 * slices
+        per_wave = 1 if few else 4 if tiles else 2
+        assert batches / per_wave <= 4 * light < batches / per_wave + 4 * 8 + 4
+
+
+def test_long_rows_get_a_wave_per_128_entries():
+    """12 K rows of 100 entries, a wavefront each: a wave per 128 entries, were three quarters of them in such rows."""
+    for groups in (2, 4, 8, 16):
+        _, long_blocks = grid(12_000, 1_200_000, groups, 2)
+        assert abs(4 * long_blocks - 0.75 * 1_200_000 / 128) <= 4 * 8 + 4
+    assert grid(1 << 20, 1 << 30, 4, 1)[1] == 8 * 1024  # at most eight times what the device holds
+    assert grid(1 << 20, 1 << 30, 4, 1, tiles=True)[1] == 2 * 1024
