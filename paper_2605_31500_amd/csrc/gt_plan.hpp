@@ -113,43 +113,67 @@ constexpr int kRowsSetWords = ROWS_COUNT * kRowsStride;  // one counter set
 struct RowRule {
     int32_t light_max;
     uint32_t split_min, chunk, nq_floor, nq_max, group_len;
-    int64_t max_slots;  // partial states at most, over all graphs of this size
+    int64_t max_slots;     // partial states at most, over all graphs of this size
+    int64_t likely_slots;  // enough for most of them
     bool forced;        // chunk length given by the caller
 };
 
-// Rows are cut into eight pieces from eight times the length at which a piece
-// saves what it costs: `piece_bytes` of its partial state (written and read once),
-// row vectors, list entry and index line.  Its entries, of `gather_bytes` each, hit the L2 with a share `cover` more than in
-// row order, the part of an XCD's eighth of the sources that its L2 holds
-// (uniform sources).  At least eight entries per piece (four where that pays and
-// the sources nearly fit an L2), and 32 per wavefront of `groups` pieces.  Longer
-// rows get pieces of 32 to 64 entries, twice that where the call's gathers take
-// more than about 60 us, and up to 32 of them: beyond that a wavefront reads a
-// piece, since every piece has to be merged.
-// Measured (us per call).  Rows cut from 32 / 64 / 128 entries, with 128-byte
-// slices: fp32 4x32 power law of 16 K nodes 41.6 / 45.4 / 58.3, of 169 K nodes 212
-// / 211 / 218, R-MAT scale 21 4932 / 4730 / 4764; fp32 4x128 power law of 169 K
-// nodes 985 / 880 / 870; bf16 8x64 lognormal 10411 / 10409 / 9910.  At most 16 /
-// 32 / 64 / 256 pieces: power law of 16 K nodes 41.1 / 37.9 / 39.4 / 41.7, R-MAT
-// scale 21 4716 / 4683 / 4693 / 4793, backward of R-MAT scale 20 bf16 4x32 2720 /
-// 2735 / 2736 / 3023.
+// Which rows are cut, and into how many pieces.  Rows of up to light_max entries
+// are read by one lane group; longer ones by a wavefront, or, in classes from
+// split_min on, in eight pieces: on eight XCDs at once, each of which reads its
+// eighth of the sources.  Pieces are of about 64 entries from 512 on (1024 where
+// the call's gathers take more than about 60 us), up to 32 of them; beyond that a
+// wavefront reads a piece, since every piece has to be merged.  A piece costs
+// `piece_bytes` of traffic (its partial state, written and read once, row vectors,
+// list entry and index line) and a chain of its own, an entry `gather_bytes`.
+//   * 64, cut from 128 where a piece is cheap beside two of its entries' gathers,
+//     else from 256 (from 128 / 256 on, us per call: R-MAT scale 21 fp32 4x32 4605 /
+//     4962; minimum of 64 bf16 features, lognormal 518 K nodes 398 / 376; GATv2
+//     bf16 4x64, R-MAT 119 K nodes 179 / 168).  Light rows of up to 128 and 256
+//     entries: 4605 and 4710 on the first.
+//   * Wavefronts of one or two lane groups: no longer rows than 32 entries per
+//     piece and group.
+//   * Where the mean degree passes 32, a usual row may be above 64; the light
+//     bound then goes up with it, so that not every row is cut or takes a
+//     wavefront (light bound 64 and cut from 128 / as here: 12 K nodes of degree 71,
+//     minimum of 256 fp32 features 74 / 64; 20 K of 150, fp32 4x32 198 / 173, GATv2
+//     bf16 4x64 239 / 145.  Every row from 33 entries on in eight pieces, as was
+//     done: 128, 205, 225).
+//   * Mean degrees above 170: cut from 128, or from 512 where an L2 holds the
+//     sources anyway and the rows fill the device (4000 nodes of degree 290, fp32
+//     4x32, from 128 / 512: 72 / 57; 60 K of 201, from 128 / light to 256: 968 / 1250).
+//   * The backward of vast graphs, whose pieces cost most: 128 (R-MAT scale 20 bf16
+//     4x32, light bound 64 / 128: 2781 / 2720).
+// At most 16 / 32 / 64 / 256 pieces: power law of 16 K nodes 41.1 / 37.9 / 39.4 /
+// 41.7, R-MAT scale 21 4716 / 4683 / 4693 / 4793, backward of R-MAT scale 20 bf16
+// 4x32 2720 / 2735 / 2736 / 3023.
 RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_bytes, int groups, const gt_tuning* tu) {
     constexpr double kL2Bytes = 4.0 * 1024 * 1024, kGatherBytesPerSecond = 7.0e12;
-    double cover = kXcds * kL2Bytes / ((double)N * gather_bytes);
-    if (cover > 0.75) cover = 0.75;
-    const double pays = piece_bytes / (gather_bytes * cover);
-    uint32_t len = 32 / groups > 8 ? 32 / groups : pays < 4 && (double)N * gather_bytes <= 2 * kL2Bytes ? 4 : 8;
-    while (len < 32 && 2 * len <= pays) len *= 2;
-    const bool large = (double)E * slices * gather_bytes / kGatherBytesPerSecond > 60e-6;
+    const double mean = (double)E / (double)N, sources = (double)N * gather_bytes;
+    const bool cheap = piece_bytes <= 2 * gather_bytes, vast = sources > 64 * kL2Bytes;
     RowRule r;
-    r.light_max = (int32_t)(kXcds * len);
-    r.split_min = kXcds * len;
+    r.light_max = 64;
+    r.split_min = cheap ? 128 : 256;
+    if (groups <= 2) {
+        r.light_max = groups == 2 ? 128 : 256;
+        r.split_min = r.light_max;
+    } else if (mean > 32 && mean <= 170) {
+        while (r.light_max < 1.2 * mean) r.light_max *= 2;
+        if (r.split_min < 2 * (uint32_t)r.light_max) r.split_min = 2 * r.light_max;
+    } else if (mean > 170) {
+        r.split_min = sources <= kL2Bytes && N * slices >= 4096 ? 512 : 128;
+    } else if (!cheap && vast && piece_bytes > 1024) {
+        r.light_max = 128;
+    }
+    const bool large = (double)E * slices * gather_bytes / kGatherBytesPerSecond > 60e-6;
     r.chunk = large ? 128 : 64;
     r.nq_floor = kXcds;
     r.nq_max = 32;
     r.group_len = r.chunk;
     r.forced = false;
-    r.max_slots = E / (2 * len) + 1;
+    const int64_t eights = kXcds * (E / r.split_min), more = 2 * (E / r.chunk);
+    r.max_slots = (eights > more ? eights : more) + 1;
+    r.likely_slots = mean >= r.split_min ? kXcds * N : r.max_slots / 8;
     if (tu && tu->light_max_deg > 0) r.light_max = tu->light_max_deg;
     if (tu && tu->heavy_min_deg > 0) r.split_min = r.split_min > (uint32_t)tu->heavy_min_deg ? r.split_min : (uint32_t)tu->heavy_min_deg;
     if (tu && tu->chunk_edges > 0) {
@@ -209,9 +233,8 @@ SlotPlan slot_plan(const RowRule& r, int slices, size_t slot_bytes, size_t other
     const size_t room = (bounded || left > kStatesLeast ? left : kStatesLeast) / slot_bytes;
     const size_t all = kSlicesTogether / (slot_bytes * slices);
     if (!r.forced) {
-        // (a quarter of the most is enough for most graphs; where it is not,
-        // rows are cut into fewer pieces)
-        if (all >= (size_t)r.max_slots / 4)
+        // (where they are not enough, rows are cut into fewer pieces)
+        if (all >= (size_t)r.likely_slots)
             s.cap = (uint32_t)(all < (size_t)r.max_slots ? all : (size_t)r.max_slots);
         else
             s.slices = 1;

@@ -32,7 +32,7 @@ class RowCut(ctypes.Structure):
 class RowRule(ctypes.Structure):
     _fields_ = [("light_max", ctypes.c_int32), ("split_min", ctypes.c_uint32), ("chunk", ctypes.c_uint32),
                 ("nq_floor", ctypes.c_uint32), ("nq_max", ctypes.c_uint32), ("group_len", ctypes.c_uint32),
-                ("max_slots", ctypes.c_int64), ("forced", ctypes.c_bool)]
+                ("max_slots", ctypes.c_int64), ("likely_slots", ctypes.c_int64), ("forced", ctypes.c_bool)]
 
 
 class SlotPlan(ctypes.Structure):
@@ -296,3 +296,34 @@ def test_long_rows_get_a_wave_per_128_entries():
         assert abs(4 * long_blocks - 0.75 * 1_200_000 / 128) <= 4 * 8 + 4
     assert grid(1 << 20, 1 << 30, 4, 1)[1] == 8 * 1024  # at most eight times what the device holds
     assert grid(1 << 20, 1 << 30, 4, 1, tiles=True)[1] == 2 * 1024
+
+
+# ------------------------------------------------------------------------- the rule
+
+
+@pytest.mark.parametrize("gather,piece,P", [k for k in KERNELS if k[2] >= 4])
+@pytest.mark.parametrize("N", [2000, 12_000, 100_000, 2_000_000])
+def test_usual_rows_are_light(gather, piece, P, N):
+    """Graphs of one degree or about: up to 170 entries a row, no row up to a fifth longer is cut or takes a
+    wavefront; and with long rows, eight pieces of each have room."""
+    for mean in (1, 7, 32, 34, 50, 53, 60, 71, 99, 107, 150, 170):
+        cut, r = rule(N, N * mean, 2, gather, piece, P)
+        assert r.light_max >= min(1.2 * mean, 256) or 1.2 * mean <= 64
+        assert r.split_min >= max(128, r.light_max + 1)
+    for mean in (190, 290, 505):
+        cut, r = rule(N, N * mean, 2, gather, piece, P)
+        assert r.light_max == 64 and r.split_min in (128, 512)
+        assert r.likely_slots >= min(8 * N, r.max_slots) or mean < r.split_min
+        # an L2 holds the sources, and the rows fill the device
+        assert (r.split_min == 512) == (N * gather <= 4 << 20 and 2 * N >= 4096)
+
+
+def test_states_of_every_class_have_a_place():
+    """max_slots is a bound: rows of one class alone, as many as there can be, in eight pieces each."""
+    for gather, piece, P in KERNELS:
+        for mean in (3, 24, 60, 200):
+            cut, r = rule(100_000, 100_000 * mean, 2, gather, piece, P)
+            for c in range(7, 31):
+                if (1 << c) >= r.split_min:
+                    n = (100_000 * mean) >> c
+                    assert n * min(max((2 << c) // r.chunk, 8), 32) <= r.max_slots + 32
