@@ -1538,6 +1538,7 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     w.light_list = plan.sorted ? reinterpret_cast<LightRow*>(ws + plan.o_light) : nullptr;
     w.light_deg = reinterpret_cast<uint8_t*>(ws + plan.o_deg);
     w.long_blocks = 0;
+    w.light_first = false;
     w.maybe_no_light = plan.tiles;
 
     // (the allocation-free entry point records no profiling events: creating
@@ -1598,6 +1599,7 @@ gt_status launch(const Args& a, const gt_tuning* tu, hipStream_t stream) {
     ap.part_ml = reinterpret_cast<float2*>(ws + plan.o_ml);
     ap.part_acc = reinterpret_cast<float*>(ws + plan.o_acc);
     ap.w.long_blocks = rg.long_blocks;
+    ap.w.light_first = rg.light_first;
     const int merge_grid = merge_blocks(plan.slots, plan.rule, device_cus(dev));
     for (int s = 0; s < slices; s += plan.slots.slices) {
         ap.slice0 = s;

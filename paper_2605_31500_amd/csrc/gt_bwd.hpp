@@ -367,6 +367,7 @@ gt_status launch_bwd_pass(BwdParams bp, const RowRule& rule, const SlotPlan& sp,
     hipError_t he = hipSuccess;
     const RowGrid rg = row_grid(bp.w.N, bp.w.E, Op::Gm::kP, sp.slices, false, bwd_resident<T, HS, D, MODE>(dev), nullptr);
     bp.w.long_blocks = rg.long_blocks;
+    bp.w.light_first = rg.light_first;
     SortParams pp;
     pp.w = bp.w;
     pp.step = Op::kU;
@@ -420,6 +421,7 @@ gt_status launch_bwd(const BwdArgs& a, hipStream_t stream) {
     w.light_deg = reinterpret_cast<uint8_t*>(ws + o_deg);
     w.long_list = reinterpret_cast<LongRow*>(ws + o_long);
     w.long_blocks = 0;
+    w.light_first = false;
     w.maybe_no_light = false;
 
     for (int mode = 0; mode < 2; ++mode) {

@@ -264,9 +264,15 @@ int merge_blocks(const SlotPlan& sp, const RowRule& r, int cus) {
 // eight times what the device holds (a wave without a batch still costs its
 // prologue; a wave per 64 entries of each lane group left rows of 65 to 255
 // entries, a wavefront each, queueing up: 16 K nodes of a power law bf16 1x64 31.8
-// -> 26.6, R-MAT of 16 K nodes fp32 4x32 37.4 -> 32.9).
+// -> 26.6, R-MAT of 16 K nodes fp32 4x32 37.4 -> 32.9).  They come first, since
+// theirs is the longest chain; but on graphs of 16 entries per row or more whose
+// workgroups all but fit the device they come last, where they cost next to
+// nothing if no row is long (long rows first / last: 3000 nodes of degree 99, fp32
+// 4x32 30.4 / 24.3, GATv2 bf16 4x64 40.5 / 32.4; power law of 15 K nodes bf16 8x32
+// 34.9 / 36.8).
 struct RowGrid {
     uint32_t blocks, long_blocks;
+    bool light_first;
 };
 RowGrid row_grid(int64_t N, int64_t E, int groups, int slices, bool tiles, int resident, const gt_tuning* tu) {
     auto blocks = [](int64_t batches, int64_t per_wave) {
@@ -280,6 +286,7 @@ RowGrid row_grid(int64_t N, int64_t E, int groups, int slices, bool tiles, int r
     const uint32_t most = (uint32_t)(tiles ? 2 : 8) * (uint32_t)resident / kXcds * kXcds;
     if (rg.long_blocks > most) rg.long_blocks = most;
     rg.blocks = rg.long_blocks + blocks(batches, few ? 1 : tiles ? 4 : 2);
+    rg.light_first = E >= 16 * N && (int64_t)rg.blocks * slices <= 4 * (int64_t)resident;
     if (tu && tu->grid_blocks > 0) {
         rg.long_blocks = blocks(((int64_t)tu->grid_blocks + 1) / 2 * kWavesPerBlock, 1);
         rg.blocks = 2 * rg.long_blocks;

@@ -283,6 +283,7 @@ gt_status launch_reduce(const ReduceArgs& a, const gt_tuning* tu, hipStream_t st
     w.light_deg = reinterpret_cast<uint8_t*>(ws + o_deg);
     w.long_list = reinterpret_cast<LongRow*>(ws + o_long);
     w.long_blocks = rg.long_blocks;
+    w.light_first = rg.light_first;
     w.maybe_no_light = false;
 
     PhaseEvents ph;

@@ -36,7 +36,8 @@ struct RowWork : RowCut {
     const int64_t* rowptr;
     const int32_t* colidx;
     bool maybe_no_light;  // the tile path may have taken every light row
-    uint32_t long_blocks;  // workgroups of a slice that take the long rows (the first ones)
+    uint32_t long_blocks;  // workgroups of a slice that take the long rows
+    bool light_first;      // these are its last ones (else its first)
     int32_t* counters;
     LongRow* long_list;    // rows of degree > light_max, class after class, the longest first
     // [N] light rows in step order per partition block, row -1 elsewhere, and
@@ -106,8 +107,8 @@ template <int G> struct TileOf {
 // lig, batch), consume(op, batch, j, nvalid), merge_xor(offset), store_out(op,
 // row, lig) and store_partial(op, slot, lig).
 //
-// The first long_blocks workgroups of a slice take the long rows' pieces, the
-// others the light rows.  An XCD's waves (blockIdx.x mod 8) take its batches (one
+// long_blocks workgroups of a slice take the long rows' pieces, the others the
+// light rows.  An XCD's waves (blockIdx.x mod 8) take its batches (one
 // segment per lane group each) in turn: the longest rows first, so that time
 // runs with the source ranges, and the light rows of an eighth of the ids.  (In
 // turn and not in equal consecutive shares, where waves of one workgroup get
@@ -131,9 +132,10 @@ __device__ __forceinline__ void row_loop(const RowWork& w, const Op& op, int32_t
     // ---- this XCD's batches
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t rank = blockIdx.x / kXcds, ranks = gridDim.x / kXcds, long_ranks = w.long_blocks / kXcds;
-    const bool long_rows = rank < long_ranks;
+    const uint32_t second = w.light_first ? ranks - long_ranks : long_ranks;  // the rest starts there
+    const bool long_rows = (rank < second) != w.light_first;
     const uint32_t waves = (long_rows ? long_ranks : ranks - long_ranks) * kWavesPerBlock;
-    uint32_t it = (long_rows ? rank : rank - long_ranks) * kWavesPerBlock +
+    uint32_t it = (rank < second ? rank : rank - second) * kWavesPerBlock +
                   __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint32_t total, l0 = 0;
     ClassPlan pl{};

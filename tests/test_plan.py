@@ -267,11 +267,15 @@ def test_allocation_free_limit():
 # ------------------------------------------------------------------------- grids
 
 
+class RowGrid(ctypes.Structure):
+    _fields_ = [("blocks", ctypes.c_uint32), ("long_blocks", ctypes.c_uint32), ("light_first", ctypes.c_bool)]
+
+
 def grid(N, E, groups, slices, tiles=False, resident=1024, tuning=None):
-    g = (ctypes.c_uint32 * 2)()
+    g = RowGrid()
     probe().probe_grid(ctypes.c_int64(N), ctypes.c_int64(E), groups, slices, int(tiles), resident,
                        ctypes.byref(tuning) if tuning else None, ctypes.byref(g))
-    return g[0], g[1]  # workgroups of a slice, and those of them that take long rows
+    return g.blocks, g.long_blocks
 
 
 @pytest.mark.parametrize("tiles", [False, True])
@@ -296,6 +300,16 @@ def test_long_rows_get_a_wave_per_128_entries():
         assert abs(4 * long_blocks - 0.75 * 1_200_000 / 128) <= 4 * 8 + 4
     assert grid(1 << 20, 1 << 30, 4, 1)[1] == 8 * 1024  # at most eight times what the device holds
     assert grid(1 << 20, 1 << 30, 4, 1, tiles=True)[1] == 2 * 1024
+
+
+def test_long_rows_workgroups_come_last_where_all_fit():
+    """On graphs of 16 entries per row or more, and few workgroups; never on sparse or large ones."""
+    def last(N, E, slices):
+        g = RowGrid()
+        probe().probe_grid(ctypes.c_int64(N), ctypes.c_int64(E), 4, slices, 0, 1024, None, ctypes.byref(g))
+        return g.light_first
+    assert last(3000, 300_000, 2) and last(16_000, 256_000, 2)
+    assert not last(16_000, 120_000, 2) and not last(3000, 300_000, 8) and not last(1_000_000, 30_000_000, 1)
 
 
 # ------------------------------------------------------------------------- the rule
