@@ -270,6 +270,7 @@ int merge_blocks(const SlotPlan& sp, const RowRule& r, int cus) {
 // nothing if no row is long (long rows first / last: 3000 nodes of degree 99, fp32
 // 4x32 30.4 / 24.3, GATv2 bf16 4x64 40.5 / 32.4; power law of 15 K nodes bf16 8x32
 // 34.9 / 36.8).
+constexpr uint32_t kMostBlocks = 1u << 23;  // (a launch holds fewer than 2^32 threads)
 struct RowGrid {
     uint32_t blocks, long_blocks;
     bool light_first;
@@ -286,6 +287,7 @@ RowGrid row_grid(int64_t N, int64_t E, int groups, int slices, bool tiles, int r
     const uint32_t most = (uint32_t)(tiles ? 2 : 8) * (uint32_t)resident / kXcds * kXcds;
     if (rg.long_blocks > most) rg.long_blocks = most;
     rg.blocks = rg.long_blocks + blocks(batches, few ? 1 : tiles ? 4 : 2);
+    if (rg.blocks > kMostBlocks) rg.blocks = kMostBlocks;
     rg.light_first = E >= 16 * N && (int64_t)rg.blocks * slices <= 4 * (int64_t)resident;
     if (tu && tu->grid_blocks > 0) {
         rg.long_blocks = blocks(((int64_t)tu->grid_blocks + 1) / 2 * kWavesPerBlock, 1);

@@ -302,6 +302,15 @@ def test_long_rows_get_a_wave_per_128_entries():
     assert grid(1 << 20, 1 << 30, 4, 1, tiles=True)[1] == 2 * 1024
 
 
+def test_grids_of_the_largest_graphs_can_be_launched():
+    """Fewer than 2^32 threads: 256 per workgroup."""
+    for groups in (1, 2, 4, 8, 16):
+        for N in (1 << 28, 540_000_000, (1 << 31) - 1):
+            for resident in (512, 2048):
+                blocks, long_blocks = grid(N, (1 << 31) - 1, groups, 1, resident=resident)
+                assert blocks * 256 < 1 << 32 and blocks % 8 == 0 and long_blocks < blocks
+
+
 def test_long_rows_workgroups_come_last_where_all_fit():
     """On graphs of 16 entries per row or more, and few workgroups; never on sparse or large ones."""
     def last(N, E, slices):
