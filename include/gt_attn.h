@@ -123,14 +123,19 @@ gt_status gt_attn_fwd_bf16(const int64_t* rowptr, const int32_t* colidx, const u
  *   The features are worked on slice by slice (the heads of 256 bytes, or one
  *   head where that is more), each with the same partition:
  *   light_max_deg : rows of degree <= this are handled by one lane group
- *                   (a sub-wavefront) each (default 32 to 256, by what a
- *                   piece of a longer row saves; 64 where the dense-tile path
- *                   is on)
+ *                   (a sub-wavefront) each (default 64; 128 and 256 where a
+ *                   wavefront holds two groups or one, and up to 256 where the
+ *                   mean degree is between 32 and 170, so that usual rows are
+ *                   light)
  *   heavy_min_deg : rows of degree >= this (and of a degree octave all of which
  *                   are) are split into pieces processed by different lane
  *                   groups, each eighth of a row's pieces on one XCD, and
- *                   merged afterwards; rows in between get one wavefront each
- *                   (default: the power of two above light_max_deg's default)
+ *                   merged afterwards; values below 16 count as 16.  Rows in
+ *                   between get one lane group each up to 64 entries (128 where
+ *                   the gathers of a call take more than about 60 us) and one
+ *                   wavefront beyond (default: 128 or 256 by what a piece costs
+ *                   beside its gathers, twice light_max_deg's default where
+ *                   that follows the mean degree, and up to 512 beyond)
  *   chunk_edges   : CSR entries per piece of a split row at most, rounded up to
  *                   a multiple of 64; a row is cut into at most 32 such pieces,
  *                   so very long rows get longer ones, and rows of a degree
@@ -139,9 +144,9 @@ gt_status gt_attn_fwd_bf16(const int64_t* rowptr, const int32_t* colidx, const u
  *                   where the gathers of a call take more than about 60 us),
  *                   up to 32)
  *   grid_blocks   : workgroups of the attention kernel per slice, rounded up to
- *                   a multiple of 16 (default: a wavefront per two batches of
- *                   light rows, and up to eight times the resident workgroups
- *                   for the longer rows)
+ *                   a multiple of 16 (default: a wavefront per batch of light
+ *                   rows, or per two on large calls, and one per 128 entries of
+ *                   longer rows, up to eight times the resident workgroups)
  *   dense_tiles   : threshold of the matrix-core path for locally dense
  *                   graphs (Section 3.3 and Appendix D.3: block-sparse
  *                   tiles); bf16 features with H*D <= 128 only, ignored

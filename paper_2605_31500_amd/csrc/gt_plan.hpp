@@ -165,6 +165,8 @@ RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_b
     } else if (!cheap && vast && piece_bytes > 1024) {
         r.light_max = 128;
     }
+    // (eight pieces of two entries at the least)
+    if (tu && tu->heavy_min_deg > 0) r.split_min = tu->heavy_min_deg > 16 ? tu->heavy_min_deg : 16;
     const bool large = (double)E * slices * gather_bytes / kGatherBytesPerSecond > 60e-6;
     r.chunk = large ? 128 : 64;
     r.nq_floor = kXcds;
@@ -175,7 +177,6 @@ RowRule row_rule(int64_t N, int64_t E, int slices, int gather_bytes, int piece_b
     r.max_slots = (eights > more ? eights : more) + 1;
     r.likely_slots = mean >= r.split_min ? kXcds * N : r.max_slots / 8;
     if (tu && tu->light_max_deg > 0) r.light_max = tu->light_max_deg;
-    if (tu && tu->heavy_min_deg > 0) r.split_min = r.split_min > (uint32_t)tu->heavy_min_deg ? r.split_min : (uint32_t)tu->heavy_min_deg;
     if (tu && tu->chunk_edges > 0) {
         r.forced = true;
         r.chunk = ((uint32_t)tu->chunk_edges + kWave - 1) / kWave * kWave;

@@ -141,11 +141,13 @@ def test_halved_classes_take_whole_wavefronts():
 
 
 @pytest.mark.parametrize("P", [1, 4, 16])
+@pytest.mark.parametrize("heavy_min_deg", [0, 1, 64])
 @pytest.mark.parametrize("light_max_deg", [1, 2, 40, 0])
-def test_largest_graphs_count_in_32_bits(P, light_max_deg):
+def test_largest_graphs_count_in_32_bits(P, light_max_deg, heavy_min_deg):
     """2^31 - 1 entries in rows of one class, as many as there can be: the lane groups that the partition counts do not
     wrap, and no wave with batches ends early."""
-    cut, r = rule((1 << 31) - 1, (1 << 31) - 1, 1, 1024 // P, 300, P, Tuning(light_max_deg=light_max_deg))
+    cut, r = rule((1 << 31) - 1, (1 << 31) - 1, 1, 1024 // P, 300, P,
+                  Tuning(light_max_deg=light_max_deg, heavy_min_deg=heavy_min_deg))
     for cap in (r.max_slots, 1 << 20, 1 << 10, 0):
         cut.cap_slots = cap
         for c in range(cut.min_class, 31):
@@ -350,3 +352,17 @@ def test_states_of_every_class_have_a_place():
                 if (1 << c) >= r.split_min:
                     n = (100_000 * mean) >> c
                     assert n * min(max((2 << c) // r.chunk, 8), 32) <= r.max_slots + 32
+
+
+@pytest.mark.parametrize("heavy_min_deg", [1, 16, 17, 64, 100, 300, 5000, 2**31 - 2**16])
+def test_heavy_min_deg_is_the_shortest_row_that_is_cut(heavy_min_deg):
+    """Also below the default."""
+    cut, r = rule(100_000, 700_000, 2, 512, 600, 4, Tuning(light_max_deg=4, heavy_min_deg=heavy_min_deg))
+    assert r.split_min == max(16, heavy_min_deg)
+    for c in range(cut.min_class, 31):
+        rows = np.zeros(32)
+        rows[c] = 1
+        cut.cap_slots = 64
+        _, nq, _ = batches(cut, rows, 4) if 700_000 >> c else (0, np.ones(32), 0)
+        if 700_000 >> c:
+            assert (nq[c] >= 8) == ((1 << c) >= max(16, heavy_min_deg))
