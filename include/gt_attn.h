@@ -48,7 +48,7 @@
  * device-side wait on the event; otherwise it allocates a new block from the
  * library's memory pool of the device (hipMallocFromPoolAsync on `stream`).
  * The host never waits for the device, nothing is kept per stream, and free
- * blocks above 1 GiB per device go back to the pool; gt_workspace_release()
+ * blocks above 512 MiB per device go back to the pool; gt_workspace_release()
  * returns all free blocks to the device.  On a stream being captured into a
  * graph the workspace is allocated and freed stream-ordered instead (both
  * become graph nodes).

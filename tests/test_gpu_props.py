@@ -605,3 +605,26 @@ def test_workspace_memory_comes_back_after_many_streams():
     back = free0 - torch.cuda.mem_get_info()[0]
     print("device memory not returned: %d MiB" % (back >> 20), flush=True)
     assert back <= (8 << 20), "%d MiB not returned" % (back >> 20)
+
+
+def test_free_blocks_of_large_calls_stay_bounded():
+    """Calls with about 200 MiB of workspace each on six streams: at most 512 MiB of free blocks are kept (and 256 MiB
+    in the pool)."""
+    import paper_2605_31500_amd as gtm
+    N, deg = 1_000_000, 24
+    rowptr = torch.arange(N + 1, device="cuda", dtype=torch.int64) * deg
+    colidx = (torch.arange(N * deg, device="cuda", dtype=torch.int64) * 7 % N).to(torch.int32)
+    x = torch.zeros((N, 1, 32), device="cuda")
+    outs = [torch.empty_like(x) for _ in range(6)]
+    torch.cuda.synchronize()  # the inputs are made on the default stream
+    gtm.gt_workspace_release()
+    for out in outs:
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            gtm.gt_attn_fwd_ex(rowptr, colidx, x, x, x, out, 0.1)
+    torch.cuda.synchronize()
+    reserved, used = gtm.gt_workspace_pool_stats()
+    print("pool after six large calls: reserved %d MiB, used %d MiB" % (reserved >> 20, used >> 20), flush=True)
+    gtm.gt_workspace_release()
+    assert used == 0 and (192 << 20) <= reserved <= (768 << 20) + (64 << 20)
+    assert all(bool((out == 0).all()) for out in outs)
