@@ -1627,7 +1627,7 @@ using LaunchFn = gt_status (*)(const Args&, const gt_tuning*, hipStream_t);
 constexpr int kSliceBytes = 256;
 
 template <typename T, int KIND>
-LaunchFn pick_hd(int32_t H, int32_t D) {
+LaunchFn pick_hd(int32_t H, int32_t D, bool wide = false) {
     constexpr bool kBf16 = std::is_same<T, bf16_tag>::value;
     constexpr int kFit = kSliceBytes / Elt<T>::kBytes;  // elements
     if (H != 1 && H != 2 && H != 4 && H != 8) return nullptr;
@@ -1642,7 +1642,10 @@ LaunchFn pick_hd(int32_t H, int32_t D) {
             if constexpr (kFit >= 128)
                 if (H >= 2) return &launch<T, 2, 64, KIND>;
             return &launch<T, 1, 64, KIND>;
-        case 128: return &launch<T, 1, 128, KIND>;
+        case 128:
+            if constexpr (KIND == KIND_GATV2 && !kBf16)
+                if (wide) return &launch<T, 2, 128, KIND>;
+            return &launch<T, 1, 128, KIND>;
         case 256: return &launch<T, 1, 256, KIND>;
         case 512:  // a head must fit 64 lanes of 16 bytes
             if constexpr (kBf16)
@@ -1682,7 +1685,8 @@ gt_status run(gt_dtype dtype, const Args& a, const gt_tuning* tu, hipStream_t st
     if (a.kind == KIND_GATV2 && !std::isfinite(a.slope)) return fail(GT_ERROR_INVALID_VALUE, "slope must be finite");
     LaunchFn fn;
     if (a.kind == KIND_GATV2)
-        fn = dtype == GT_DTYPE_F32 ? pick_hd<float, KIND_GATV2>(a.H, a.D) : pick_hd<bf16_tag, KIND_GATV2>(a.H, a.D);
+        fn = dtype == GT_DTYPE_F32 ? pick_hd<float, KIND_GATV2>(a.H, a.D, wide_slices(a.N, a.E, (int64_t)a.H * a.D * 4))
+                                   : pick_hd<bf16_tag, KIND_GATV2>(a.H, a.D);
     else
         fn = dtype == GT_DTYPE_F32 ? pick_hd<float, KIND_GT>(a.H, a.D)
              : (tu && tu->bf16_weights) ? pick_hd<bf16_tag, KIND_GT_BF16W>(a.H, a.D)
@@ -1765,7 +1769,8 @@ gt_status run_reduce(gt_dtype dtype, int op, const ReduceArgs& a0, const gt_tuni
     if (a0.N < 0 || a0.N >= (int64_t(1) << 31)) return fail(GT_ERROR_INVALID_VALUE, "N must be in [0, 2^31)");
     if (a0.E < 0 || a0.E >= (int64_t(1) << 31)) return fail(GT_ERROR_INVALID_VALUE, "E must be in [0, 2^31)");
     if (a0.F < 1) return fail(GT_ERROR_INVALID_VALUE, "F must be positive");
-    ReduceFn fn = dtype == GT_DTYPE_F32 ? pick_reduce<float>(a0.F) : pick_reduce<bf16_tag>(a0.F);
+    const bool wide = wide_slices(a0.N, a0.E, (int64_t)a0.F * (dtype == GT_DTYPE_F32 ? 4 : 2));
+    ReduceFn fn = dtype == GT_DTYPE_F32 ? pick_reduce<float>(a0.F, wide) : pick_reduce<bf16_tag>(a0.F, wide);
     if (!fn)
         return fail(GT_ERROR_NOT_SUPPORTED, "unsupported F = " + std::to_string(a0.F) +
                                                 "; rows of 64 B to 4 KiB in powers of two (fp32 F in {16..1024}, "

@@ -297,6 +297,19 @@ RowGrid row_grid(int64_t N, int64_t E, int groups, int slices, bool tiles, int r
     return rg;
 }
 
+// Whether rows that are gathered once per entry (GATv2, the reduction) are worked on
+// in slices of 1 KB instead of 256 bytes.  Each slice reads the row's list entry and
+// indices again, and rows of a few entries have nothing for a second XCD to find in
+// its L2: four slices of a 4 KB row cost less than sixteen there (256 bytes / 1 KB, us
+// per call: GATv2 fp32 8x128, 60 K nodes of degree 4 216 / 201, R-MAT of 500 K of
+// degree 5 2215 / 1690; minimum of 1024 fp32 features 241 / 219 and 2414 / 1920), but
+// not from 7 entries on (300 K lognormal nodes, minimum: 1574 / 1640), on small
+// graphs (8 K R-MAT nodes: 51 / 60; 33 K of a power law, 2048 bf16 features: 169 /
+// 217) or of shorter rows (1 KB, power law of 60 K nodes: 78 / 98).
+bool wide_slices(int64_t N, int64_t E, int64_t row_bytes) {
+    return row_bytes >= 4096 && N >= 48 * 1024 && 2 * E < 11 * N;
+}
+
 // One call of the attention forward: its sizes and its row kernel.
 struct AttnShape {
     int64_t N, E;

@@ -321,9 +321,9 @@ gt_status launch_reduce(const ReduceArgs& a, const gt_tuning* tu, hipStream_t st
 using ReduceFn = gt_status (*)(const ReduceArgs&, const gt_tuning*, hipStream_t);
 
 // Row sizes of 64 B .. 4 KiB: fp32 F in {16, ..., 1024}, bf16 F in {32, ..., 2048};
-// slices of 256 bytes, or the row.
+// slices of 256 bytes, or the row (1 KB where wide_slices says so).
 template <typename T>
-ReduceFn pick_reduce(int32_t F) {
+ReduceFn pick_reduce(int32_t F, bool wide) {
     constexpr int EPV = 16 / Elt<T>::kBytes;
     if (F <= 0 || F % EPV != 0) return nullptr;
     switch (F / EPV) {
@@ -332,8 +332,8 @@ ReduceFn pick_reduce(int32_t F) {
         case 16:
         case 32:
         case 64:
-        case 128:
-        case 256: return &launch_reduce<T, 16>;
+        case 128: return &launch_reduce<T, 16>;
+        case 256: return wide ? &launch_reduce<T, 64> : &launch_reduce<T, 16>;
         default: return nullptr;
     }
 }

@@ -61,4 +61,6 @@ void probe_grid(int64_t N, int64_t E, int groups, int slices, int tiles, int res
     *g = row_grid(N, E, groups, slices, tiles != 0, resident, tu);
 }
 
+int probe_wide(int64_t N, int64_t E, int64_t row_bytes) { return wide_slices(N, E, row_bytes); }
+
 }  // extern "C"

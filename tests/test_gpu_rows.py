@@ -73,3 +73,24 @@ def test_backward_at_partition_edges(dtype, H, D, kind):
     scale = np.float32(1 / math.sqrt(D))
     got = run_gpu_fwd_bwd(rowptr, colidx, Q, K, V, dO, scale)
     check_grads(rowptr, colidx, Q, K, V, dO, scale, got, dtype)
+
+
+@pytest.mark.parametrize("op,dtype,width", [("reduce", "f32", 1024), ("reduce", "bf16", 2048), ("gatv2", "f32", 1024)])
+def test_wide_slices_of_short_rows(op, dtype, width):
+    """4 KB rows of four entries on average, worked on in slices of 1 KB (one lane group per wavefront), some of them
+    long enough to be cut."""
+    N = 48 * 1024 + 61
+    rng = np.random.default_rng(17)
+    deg = rng.integers(0, 8, N)
+    longs = rng.permutation(N)[:30]
+    deg[longs] = np.resize([255, 256, 257, 511, 513, 700, 1500, 4100], 30)
+    rowptr, colidx = synth.csr_from_degrees(19, N, deg, self_loops=False)
+    assert 2 * colidx.size < 11 * N
+    rows = np.unique(np.concatenate([longs, rng.integers(0, N, 1500), [0, N - 1]]))
+    if op == "reduce":
+        from tests.test_gpu_reduce import check, features
+        check(rowptr, colidx, features(5, N, width, dtype), dtype, "min", rows=rows)
+    else:
+        from tests.test_gpu_gatv2 import SLOPE, attention_vector, check
+        L, R, _ = synth.features(6, N, 8, width // 8, dtype)
+        check(rowptr, colidx, L, R, attention_vector(7, 8, width // 8), SLOPE, dtype, rows=rows)

@@ -366,3 +366,10 @@ def test_heavy_min_deg_is_the_shortest_row_that_is_cut(heavy_min_deg):
         _, nq, _ = batches(cut, rows, 4) if 700_000 >> c else (0, np.ones(32), 0)
         if 700_000 >> c:
             assert (nq[c] >= 8) == ((1 << c) >= max(16, heavy_min_deg))
+
+
+def test_wide_slices_are_for_short_wide_rows_of_large_graphs():
+    def wide(N, E, row):
+        return bool(probe().probe_wide(ctypes.c_int64(N), ctypes.c_int64(E), ctypes.c_int64(row)))
+    assert wide(60_000, 240_000, 4096) and wide(49152, 0, 4096) and wide(2**31 - 1, 2**31 - 1, 8192)
+    assert not wide(60_000, 330_000, 4096) and not wide(49151, 0, 4096) and not wide(60_000, 240_000, 2048)
