@@ -94,3 +94,32 @@ def test_wide_slices_of_short_rows(op, dtype, width):
         from tests.test_gpu_gatv2 import SLOPE, attention_vector, check
         L, R, _ = synth.features(6, N, 8, width // 8, dtype)
         check(rowptr, colidx, L, R, attention_vector(7, 8, width // 8), SLOPE, dtype, rows=rows)
+
+
+@pytest.mark.parametrize("op,dtype,H,D", [("fwd", "bf16", 8, 128), ("bwd", "f32", 8, 64)])
+def test_classes_short_of_partial_states(op, dtype, H, D):
+    """6200 rows of 600 entries want eight pieces each, more partial states than the launch has: they get four, too long
+    for one lane group, and every piece takes a wavefront (tests/test_plan.py shows that this graph does so)."""
+    N, n_long = 60_000, 6200
+    rng = np.random.default_rng(23)
+    deg = rng.integers(0, 4, N)
+    longs = np.sort(rng.permutation(N)[:n_long])
+    deg[longs] = 600
+    rowptr = np.zeros(N + 1, dtype=np.int64)
+    rowptr[1:] = np.cumsum(deg)
+    colidx = rng.integers(0, N, rowptr[-1]).astype(np.int32)
+    for r in longs:
+        colidx[rowptr[r]:rowptr[r + 1]].sort()
+    Q, K, V = synth.features(31, N, H, D, dtype)
+    scale = np.float32(1 / math.sqrt(D))
+    rows = np.unique(np.concatenate([longs[::17], longs[-20:], rng.integers(0, N, 300)]))
+    if op == "fwd":
+        got = run_gpu(rowptr, colidx, Q, K, V, scale)[rows]
+        ref, absagg, _ = oracle.gt_attn_fwd(rowptr, colidx, Q, K, V, scale, rows=rows, want_lse=False)
+        assert np.all(np.isfinite(got)) and gate_error(got, ref, absagg) <= TOL_BF16
+    else:
+        from tests.helpers import run_gpu_fwd_bwd
+        from tests.test_gpu_bwd import check_grads
+        dO, _, _ = synth.features(32, N, H, D, dtype)
+        got = run_gpu_fwd_bwd(rowptr, colidx, Q, K, V, dO, scale)
+        check_grads(rowptr, colidx, Q, K, V, dO, scale, got, dtype, rows=rows, cols=rows[::9])

@@ -373,3 +373,27 @@ def test_wide_slices_are_for_short_wide_rows_of_large_graphs():
         return bool(probe().probe_wide(ctypes.c_int64(N), ctypes.c_int64(E), ctypes.c_int64(row)))
     assert wide(60_000, 240_000, 4096) and wide(49152, 0, 4096) and wide(2**31 - 1, 2**31 - 1, 8192)
     assert not wide(60_000, 330_000, 4096) and not wide(49151, 0, 4096) and not wide(60_000, 240_000, 2048)
+
+
+@pytest.mark.parametrize("case", ["fwd", "bwd"])
+def test_a_graph_whose_classes_get_fewer_and_longer_pieces(case):
+    """6200 rows of 600 entries among 60 K (the graph of a GPU test): the rule wants eight pieces each, the states of
+    one launch hold four, and those are spread over wavefronts."""
+    N, E = 60_000, 6200 * 600 + 53_800 * 3 // 2
+    if case == "fwd":  # bf16 8x128
+        p = attn_plan(shape(N, E, 2, 8, 128))
+        r, cap, slices, P = p.rule, p.slots.cap, p.slots.slices, 4
+        cut, _ = rule(N, E, 8, 512, 972, 4)
+    else:  # fp32 8x64
+        cut, r = rule(N, E, 8, 512, 2 * 512 + 1024, 4)
+        s = SlotPlan()
+        probe().probe_slots(ctypes.byref(r), 8, ctypes.c_int64(512), ctypes.c_int64(8 * 8 * N + 10 * N + E // 2), 0, ctypes.byref(s))
+        cap, slices, P = s.cap, s.slices, 4
+    assert slices == 8
+    cut.cap_slots = cap
+    rows = np.zeros(32)
+    rows[9] = 6200
+    bound, nq, total = batches(cut, rows, P)
+    assert nq[9] == 4 and 1024 // 4 > cut.group_len and int(total.max()) <= bound
+    # the waves of the long rows reach past what eight pieces by lane group would have asked for
+    assert grid(N, E, P, slices)[1] // 8 * 4 > 6200 * 8 // (8 * P) + 32
