@@ -19,7 +19,8 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 
 @pytest.mark.skip(reason="the program ended once in a host abort (double free or corruption) whose cause is not known; "
-                         "its host side is clean under AddressSanitizer against a stub HIP runtime")
+                         "its whole host side, library included, is clean under AddressSanitizer over a stub runtime "
+                         "(tests/test_sanitizers.py)")
 @pytest.mark.skipif(shutil.which("gcc") is None, reason="gcc not installed")
 def test_standalone_c_program_matches_the_oracle(tmp_path):
     import oracle

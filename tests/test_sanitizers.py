@@ -1,7 +1,7 @@
 """Host code under AddressSanitizer and UndefinedBehaviorSanitizer (CPU only).
 
-Two drivers, each built here with the sanitizers and -fno-sanitize-recover
-and run in a child process:
+Two drivers, built here with the sanitizers and -fno-sanitize-recover
+and run in child processes:
   * tests/sanitize/oracle_driver.c with oracle/gt_oracle.c and synth/synth.c
     (gcc, no OpenMP): every generator and every oracle function on small
     graphs with empty rows, repeated entries, a single row and row subsets;
@@ -9,9 +9,15 @@ and run in a child process:
     on the host compilation only): every entry point's host validation,
     status strings, per-thread error messages, and the pool and profiler
     calls that need no device.
+A third run takes the stand-alone C program of the GPU tests (tests/c_caller_gpu.c)
+and the library's host code through the program's whole call sequence, release
+and process exit included, over tests/sanitize/hip_stub.cpp: a runtime whose
+device memory is host memory of the exact size, whose kernels do nothing and
+whose handles are checked against a second free or destroy.
 Builds are kept under _build/sanitize/, keyed by a hash of their sources."""
 import hashlib
 import os
+import re
 import shutil
 import subprocess
 
@@ -72,3 +78,37 @@ def test_library_host_code_under_asan_ubsan():
         "-Xarch_host", "-fno-sanitize-recover=all", "-I", os.path.join(ROOT, "include"),
         os.path.join(csrc, "gt_attn.hip"), os.path.join(SAN, "abi_driver.cpp"), "-o", out])
     run_clean(exe)
+
+
+def test_c_program_host_side_under_asan(tmp_path):
+    llvm = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "lib", "llvm", "bin")
+    hipcc = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
+    if not os.path.exists(hipcc) or not os.path.exists(os.path.join(llvm, "clang")):
+        pytest.skip("hipcc not available")
+    rocm_inc = ["-D__HIP_PLATFORM_AMD__", "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
+                "-I", os.path.join(ROOT, "include")]
+    csrc = os.path.join(ROOT, "paper_2605_31500_amd", "csrc", "gt_attn.hip")
+
+    def run(cmd):
+        r = subprocess.run(cmd, capture_output=True, text=True, timeout=900, cwd=tmp_path)
+        assert r.returncode == 0, (r.stdout + r.stderr)[-4000:]
+        return r.stdout
+
+    asan = ["-O1", "-g", "-fno-omit-frame-pointer", "-fsanitize=address"]
+    run([hipcc, "--offload-arch=gfx950", "--offload-host-only", "-O1", "-g", "-std=c++17",
+         "-Xarch_host", "-fsanitize=address", "-I", os.path.join(ROOT, "include"), "-c", csrc, "-o", "lib.o"])
+    run([os.path.join(llvm, "clang++"), "-std=c++17"] + asan + rocm_inc + ["-c", os.path.join(SAN, "hip_stub.cpp"), "-o", "stub.o"])
+    for src, obj in ((os.path.join(ROOT, "tests", "c_caller_gpu.c"), "prog.o"),
+                     (os.path.join(ROOT, "oracle", "gt_oracle.c"), "oracle.o")):
+        run([os.path.join(llvm, "clang"), "-std=gnu11"] + asan + rocm_inc + ["-c", src, "-o", obj])
+    # (the device code's image, which a host-only compilation leaves out)
+    image = [l.split()[-1] for l in run(["nm", "lib.o"]).splitlines() if "__hip_fatbin_" in l and " U " in l and "wrapper" not in l]
+    run([os.path.join(llvm, "clang++"), "-fsanitize=address", "lib.o", "stub.o", "prog.o", "oracle.o", "-lm", "-lpthread",
+         "-o", "prog"] + ["-Wl,--defsym=%s=0" % s for s in image])
+    r = subprocess.run([str(tmp_path / "prog")], capture_output=True, text=True, timeout=300,
+                       env=dict(os.environ, ASAN_OPTIONS="detect_leaks=1"))
+    out = r.stdout + r.stderr
+    # the four calls return, no kernel has run (their outputs are as they were: NaN), the release and the exit are clean
+    assert r.returncode == 1 and out.count("gate error nan") == 4, out[-4000:]
+    # (the scratch array stays)
+    assert "AddressSanitizer" not in out and re.search(r"hip stub: [1-9]\d* launches, 1 allocations left", out), out[-4000:]
