@@ -56,7 +56,7 @@ CAPTURES = {
                   summary="gt_attn_kernel_{w}-csr"),
     "c4": dict(args=["--config", "4"], kernels=["gt_attn_kernel"], key="{w}",
                title="Graph-transformer attention forward", model=GT_MODEL, summary="gt_attn_kernel_{w}"),
-    "bwd": dict(args=["--backward", "--config", "1"], kernels=["gt_bwd_kernel"], key="{w}:backward",
+    "bwd": dict(args=["--backward", "--config", "1"], kernels=["gt_bwd_kernel"], key="{w}:backward", passes=2,
                 title="Graph-transformer attention backward (both passes)", model="backward per-edge model",
                 summary="gt_bwd_kernel_{w}"),
     "reduce": dict(args=["--reduce", "min", "--config", "1"], kernels=["gt_reduce_kernel"], key="{g}:reduce-min-f512",
@@ -187,17 +187,26 @@ def kernel_table(trace_dir, kernels):
     return table
 
 
-def counters(d, group, kernels):
-    """Per call: each counter summed over the named kernels (each kernel's
-    dispatches averaged); also the dispatch count averaged."""
-    per = {}
+# one partition per call (one per pass in the backward): large calls launch their
+# row kernel once per slice
+CALL_KERNEL = "gt_sort_rows_kernel"
+
+
+def counters(d, group, kernels, passes=1):
+    """Per call: each counter summed over the named kernels' dispatches, over
+    the number of calls (without a partition among the dispatches, each
+    kernel's are averaged); also the largest dispatch count of a kernel."""
+    per, sorts = {}, {}
     for r in rows(one(os.path.join(d, group_dir(group), "*_counter_collection.csv"))):
-        if not any(short(r["Kernel_Name"]).startswith(k) for k in kernels):
+        name = short(r["Kernel_Name"])
+        if name.startswith(CALL_KERNEL):
+            sorts[r["Counter_Name"]] = sorts.get(r["Counter_Name"], 0) + 1
+        if not any(name.startswith(k) for k in kernels):
             continue
-        per.setdefault((short(r["Kernel_Name"]), r["Counter_Name"]), []).append(float(r["Counter_Value"]))
+        per.setdefault((name, r["Counter_Name"]), []).append(float(r["Counter_Value"]))
     out, n = {}, 0
     for (_, c), v in per.items():
-        out[c] = out.get(c, 0.0) + sum(v) / len(v)
+        out[c] = out.get(c, 0.0) + sum(v) / (sorts[c] / passes if c in sorts else len(v))
         n = max(n, len(v))
     missing = [c for c in group if c not in out]
     if missing:
@@ -218,14 +227,17 @@ def summarize(out, mode, source_hash):
     main = [k for k in table if k[6]]
     if not main:
         raise SystemExit("no %s dispatch in the trace of %s" % (kernels, mode))
-    kavg = sum(k[2] for k in main)  # per call: the named kernels' average durations, summed
+    passes = spec.get("passes", 1)
+    calls = sum(k[1] for k in table if k[0].startswith(CALL_KERNEL)) / passes
+    # per call: the named kernels' durations, summed
+    kavg = sum(k[1] * k[2] / calls if calls else k[2] for k in main)
     cf, cw, fscale, wscale = copy_scales(out)
-    fetch, nd = counters(d, ["FETCH_SIZE"], kernels)
-    write, _ = counters(d, ["WRITE_SIZE"], kernels)
-    l2, _ = counters(d, ["TCC_HIT_sum", "TCC_MISS_sum"], kernels)
-    sq, _ = counters(d, SQ_GROUP, kernels)
-    ta, _ = counters(d, TA_GROUP, kernels)
-    tcp, _ = counters(d, TCP_GROUP, kernels)
+    fetch, nd = counters(d, ["FETCH_SIZE"], kernels, passes)
+    write, _ = counters(d, ["WRITE_SIZE"], kernels, passes)
+    l2, _ = counters(d, ["TCC_HIT_sum", "TCC_MISS_sum"], kernels, passes)
+    sq, _ = counters(d, SQ_GROUP, kernels, passes)
+    ta, _ = counters(d, TA_GROUP, kernels, passes)
+    tcp, _ = counters(d, TCP_GROUP, kernels, passes)
     fb = fetch["FETCH_SIZE"] * 1024 * fscale
     wb = write["WRITE_SIZE"] * 1024 * wscale
     alg = live["roofline"]["algorithmic_bytes_per_launch"]
@@ -257,7 +269,7 @@ def summarize(out, mode, source_hash):
           "Calibration: a plain %d MiB device copy (`__amd_rocclr_copyBuffer`) reads FETCH_SIZE = %.0f KiB and "
           "WRITE_SIZE = %.0f KiB per dispatch for %d KiB moved each way, so the scale factors are %.4f (fetch) "
           "and %.4f (write)." % (COPY_MIB, cf, cw, COPY_MIB * 1024, fscale, wscale), "",
-          "| per call of %s (%d dispatches averaged per kernel) | counter | value |" % (kl, nd), "|---|---|---|",
+          "| per call of %s (%d dispatches of a kernel at most) | counter | value |" % (kl, nd), "|---|---|---|",
           "| HBM fetch | FETCH_SIZE %.0f KiB × %.4f | %.4f GB |" % (fetch["FETCH_SIZE"], fscale, fb / 1e9),
           "| HBM write | WRITE_SIZE %.0f KiB × %.4f | %.4f GB |" % (write["WRITE_SIZE"], wscale, wb / 1e9),
           "| HBM total | | %.4f GB |" % ((fb + wb) / 1e9),

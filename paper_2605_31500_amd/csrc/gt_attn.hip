@@ -612,10 +612,10 @@ __global__ void __launch_bounds__(kBlock) gt_merge_kernel(AttnParams p) {
 // neighbourhoods into tiles for matrix cores; this is a gfx950 design of the
 // same idea, not the paper's 16x8 TCB format).  Rows are grouped in aligned
 // windows of 64; the window's own 64 ids are its tile columns.  The partition
-// kernel flags the windows whose light rows it estimates to be dense (a
-// sample of one entry in every 8th light row); this kernel takes every light
-// row of a flagged window (one workgroup per window), the CSR kernel every
-// other row:
+// kernel flags the windows whose rows of at most tile_max entries it estimates
+// to be dense (a sample of one entry in every 8th of them); this kernel takes
+// these rows of a flagged window ("light rows" here; one workgroup per window),
+// the row kernel every other row:
 //   1. stage the window's rowptr, its K rows and its V rows (transposed) in
 //      LDS with independent loads, and each light row's entries in registers;
 //   2. per light row, a 64-bit mask of its in-window entries (a row with a
@@ -630,7 +630,6 @@ __global__ void __launch_bounds__(kBlock) gt_merge_kernel(AttnParams p) {
 //   4. every light row then streams its remaining entries (all of them for a
 //      row without a tile) with the CSR online-softmax step, continuing from
 //      the tile's (m, l, acc), and writes its output.
-// Non-light rows are left to the wave items of the CSR kernel.
 //
 // MFMA operand layout of v_mfma_f32_16x16x32_bf16 (64 lanes, l = lane):
 //   A (16x32): lane l holds A[l%16][8*(l/16) + j], j = 0..7
@@ -1145,7 +1144,7 @@ struct PhaseEvents {
     }
 };
 
-// Workspace.  Every call takes a workspace block (degree-bin lists, partial
+// Workspace.  Every call takes a workspace block (row lists, partial
 // states of split rows, work-list counters) for its own use and hands it back
 // once its kernels are enqueued; the block is then tagged with an event
 // recorded on the call's stream after those kernels.  A later call, on any

@@ -12,8 +12,8 @@
 //     dV_j += alpha_e * dO_i              (pass 1)
 // The paper's kernel walks the transposed graph and adds dK with atomics;
 // here both passes are gathers over rows (the transposed structure is an
-// input, as the paper's cached transposed adjacency), split rows are summed
-// in chunk order, and the results are bitwise reproducible.
+// input, as the paper's cached transposed adjacency), the pieces of cut rows are
+// summed in a fixed order, and the results are bitwise reproducible.
 //
 // Both passes have the same per-entry shape, with (a, b) the row's own
 // vectors and (x, y) the gathered ones:
@@ -25,9 +25,9 @@
 // entry of pass 1 reads one line for both.  Like the forward, the passes gather
 // two random rows per entry and are bound by the path from L2 to the fabric;
 // us per call with whole rows in row order, and with slices and source ranges:
-// R-MAT scale 20 bf16 4x32 3760 -> 2735, 300 K nodes fp32 4x32 1544 -> 1271;
-// lognormal 200 K nodes bf16 8x64 3753 -> 3683; power law fp32 4x32 of 169 K nodes
-// 478 -> 443, of 16 K nodes 74 -> 72.
+// R-MAT scale 20 bf16 4x32 3772 -> 2728, 300 K R-MAT nodes fp32 4x32 1794 -> 1373;
+// lognormal 200 K nodes bf16 8x64 3798 -> 3631; power law fp32 4x32 of 169 K nodes
+// 478 -> 442, of 16 K nodes 71 -> 66.
 
 struct BwdParams {
     RowWork w;      // rows of this pass (CSR or transposed CSR)

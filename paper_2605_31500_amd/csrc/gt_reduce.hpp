@@ -18,10 +18,10 @@
 // kernel instead of 64-bit atomics.  Padding entries of a step repeat a valid
 // entry, which a minimum absorbs, so they need no mask.
 // Min with sources, whole rows in row order -> slices and source ranges (us per
-// call): R-MAT scale 20, 128 fp32 features 1702 -> 1412; lognormal 500 K nodes, 512
-// fp32 5339 -> 4763; power law 20 K nodes, 1024 bf16 130 -> 86, 169 K nodes, 512 fp32
-// 510 -> 492.  Slices of 128 / 256 / 512 bytes: 1518 / 1412 / 1376, 5095 / 4763 /
-// 4705, 93 / 86 / 94 and 506 / 492 / 505.
+// call): R-MAT scale 20, 128 fp32 features 1640 -> 1366; lognormal 500 K nodes, 512
+// fp32 5316 -> 4486; power law 20 K nodes, 1024 bf16 138 -> 93, 169 K nodes, 512 fp32
+// 502 -> 462.  Slices of 128 / 256 / 512 bytes (with rows cut from 65 entries on):
+// 1518 / 1412 / 1376, 5095 / 4763 / 4705, 93 / 86 / 94 and 506 / 492 / 505.
 // This file is included by gt_attn.hip inside its anonymous namespace.
 
 constexpr uint64_t kRedEmpty = ~0ull;  // no entry yet: source 0xFFFFFFFF is never valid

@@ -2,9 +2,9 @@
 // row, and on which XCD (included by gt_attn.hip inside its anonymous
 // namespace).
 //
-// What bounds these kernels is the path from L2 to the fabric.  A probe that
-// gathers random rows reads 31 TB/s where they lie in an XCD's 4 MB L2 and
-// 7.0-7.8 TB/s from anywhere beyond it, the Infinity Cache as slowly as HBM and
+// What bounds these kernels is the path from L2 to the fabric.  Gathers of random
+// pieces read 24-27 TB/s where the table lies in an XCD's 4 MB L2, 7.0-7.3 TB/s
+// from one of 128 MB (in the Infinity Cache) and 6.2-6.4 TB/s from one of 4 GB,
 // pieces of 128 to 1024 bytes alike.  So the order of the work is built for L2
 // hits:
 //   * Feature slices.  A call runs over slices of the feature row (256 bytes, or
@@ -15,11 +15,14 @@
 //     long row is cut into nq = 8m pieces, and XCD x takes pieces xm .. xm+m-1
 //     of every long row, all rows' first pieces first: at any time an L2 holds
 //     an eighth of the sources or less, where it would otherwise see them all.
-//     (Unsorted rows lose only the locality.)
-// Simulated L2 hit rate of the long rows' gathers (4 MB L2s, 128-byte slices of
-// fp32 4x32 rows): R-MAT scale 21 18 % in row order, 37 % with slices, 77 % with
-// both; a power-law graph of 169 K nodes and uniform sources 3, 9 and 50 %.  The
-// whole fp32 4x32 forward on R-MAT scale 21: 6.37 -> 4.75 ms.
+//     (Unsorted rows have no such locality and still pay for the pieces.  Listed
+//     graphs with each row's entries shuffled, speed against whole rows in row
+//     order: R-MAT scale 21 fp32 1.02, bf16 0.97, power law of 169 K nodes 0.98,
+//     lognormal 1.16, backward of R-MAT scale 20 1.12.)
+// Counted L2 hit rate and bytes beyond the L2 of a fp32 4x32 forward, whole rows
+// in row order -> so: R-MAT scale 21 16.5 -> 42.8 %, 46.1 -> 32.1 GB, 6.13 -> 4.43
+// ms; a power-law graph of 169 K nodes with uniform sources 8.6 -> 15.9 %, 1.45 ->
+// 1.35 GB, 200 -> 189 us: 7.2 TB/s before and after.
 //
 // A row of degree d <= light_max is one segment.  Longer rows are listed by
 // degree octave (class c: 2^c <= d < 2^(c+1)); all rows of a class are cut into

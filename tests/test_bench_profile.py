@@ -96,3 +96,24 @@ def test_bench_reads_the_entry_only_for_matching_sources(capture, monkeypatch):
 def test_unknown_mode_is_refused():
     with pytest.raises(SystemExit):
         bp.main(["summarize", "nope"])
+
+
+def test_calls_of_several_launches_are_summed(capture):
+    """Two launches of the row kernel per partition: their counters and durations add up."""
+    out, prof = capture
+    d = out / "gt"
+    k = "void (anonymous namespace)::gt_attn_kernel<bf16, 2, 64, 0>((anonymous namespace)::AttnParams)"
+    sort = "void (anonymous namespace)::gt_sort_rows_kernel<8>((anonymous namespace)::SortParams)"
+    write_csv(str(d / "trace/bench_kernel_stats.csv"),
+              ["Name", "Calls", "TotalDurationNs", "AverageNs", "Percentage", "MinNs", "MaxNs", "StdDev"],
+              [[k, 20, 2000000, 100000, 90, 95000, 110000, 1], [sort, 10, 100000, 10000, 10, 9000, 11000, 1]])
+    hdr = ["Kernel_Name", "Counter_Name", "Counter_Value"]
+    write_csv(str(d / "pmc_FETCH_SIZE/x_counter_collection.csv"), hdr,
+              counter_rows(k, {"FETCH_SIZE": 1000.0}, 6) + counter_rows(sort, {"FETCH_SIZE": 1e9}, 3))
+    _, entry = bp.summarize(str(out), "gt", "abcd")
+    assert entry["fetch_bytes_per_launch"] == 2 * 1000 * 1024 * 2
+    text = (prof / "gt_attn_kernel_wl-test.md").read_text()
+    assert "rocprofv3 average: 200.00 µs" in text
+    # backward: two partitions per call
+    got, _ = bp.counters(str(d), ["FETCH_SIZE"], ["gt_attn_kernel"], passes=2)
+    assert got["FETCH_SIZE"] == 4 * 1000.0
